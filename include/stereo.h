@@ -297,8 +297,9 @@ stereo_status stereo_damage_mask(stereo_plan_t plan, const float* disp_t, float 
  * Many pairs of uneven size and disparity range (each with its own plan) in
  * one workspace and one captured graph.  Per pair, results are bitwise those
  * of stereo_match with the same plan.  The aggregation + WTA of both volumes
- * of all pairs runs as one persistent launch per (R, guide type) group that
- * takes 32x32 tiles of all pairs from a work queue, largest range first. */
+ * of all pairs runs as one launch per radius R (engines 0 and 1: per R and
+ * guide type) over the strip segments (tiles) of all its pairs, longest
+ * first. */
 typedef struct stereo_batch_s* stereo_batch_t;
 typedef struct {
   stereo_plan_t plan;      /* the pair's plan (copied at create)                */
@@ -317,10 +318,10 @@ stereo_status stereo_batch_workspace_bytes(stereo_batch_t b, size_t* bytes);
  * gives the same bits as its pairs' stereo_match when both use the same
  * engine), "wg_per_cu" (persistent workgroups per CU of
  * the vector-ALU engine, 1..8, default 2), "agg_levels_u8", "agg_levels_f32"
- * (8 or 16), "tile_band" (matrix-core engines: the tile list of a pair runs
- * in bands of this many 16-pixel tile columns, row by row; 1, 2, 4, 8, 16
- * or 32, default 4; changes only the order of independent tiles, never the
- * results), "ncc_levels" (levels per workgroup of the batch's NCC launches:
+ * (8 or 16), "tile_band" (matrix-core engines: the tile or strip list of a
+ * pair runs in bands of this many 16-pixel columns of tiles, row by row; 1, 2,
+ * 4, 8, 16 or 32, default 4; changes only the order of independent work, never
+ * the results), "ncc_levels" (levels per workgroup of the batch's NCC launches:
  * 0 = automatic, default, or 16, 32, 64; never changes the results),
  * "group_overlap" (split-FP16 engine: 1, default, runs the aggregation of
  * the radii below the largest on a second stream, a graph branch when

@@ -1,5 +1,6 @@
 // C ABI: plans (pure host state), parameter validation, workspace layout and
 // the enqueue entry points declared in include/stereo.h.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -97,12 +98,18 @@ void layout(Plan& P) {
   // the cost volume region holds either the quad-interleaved FP32 volume
   // (engines 0 and 1) or the two split-FP16 volumes (engine 2)
   P.h2_pitch = h2_pitch(P.R, W);
-  P.h2_tar_off = align256(sizeof(uint16_t) * 2 * 16 * (size_t)((D + 15) / 16) * H * P.h2_pitch);
+  P.h2_plane = 16 * (int64_t)h2_rows(P.R, H) * P.h2_pitch;
+  P.h2_tar_off = align256(sizeof(uint16_t) * 2 * (size_t)((D + 15) / 16) * (size_t)P.h2_plane);
   const size_t quad_bytes = sizeof(float) * 4 * (size_t)((D + 3) / 4) * H * P.cw;
   const size_t h2_bytes = 2 * P.h2_tar_off;
   P.off_cvol = o;  o = align256(o + (quad_bytes > h2_bytes ? quad_bytes : h2_bytes));
   P.off_dT = o;    o = align256(o + sizeof(int16_t) * (size_t)W * H);
   P.off_dsub = o;  o = align256(o + sizeof(float) * (size_t)W * H);
+  // selection state of ranges above 64 levels: both volumes of a match, or the
+  // soft-argmin forward of a float plan
+  const int state = P.p.dtype == STEREO_F32 ? std::max(2 * h2_state_floats(D, 1), h2_state_floats(D, 2))
+                                            : 2 * h2_state_floats(D, 1);
+  P.off_state = o; o = align256(o + sizeof(float) * (size_t)state * W * H);
   P.off_road = o;  o = align256(o + sizeof(double) * 10 * (size_t)P.road_blocks);
   P.ws_bytes = grad_layout(P, o);
 }
@@ -370,7 +377,7 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
     // target-anchored one (each stored by the column it is aggregated at).
     uint16_t* vR = at<uint16_t>(ws, P.off_cvol);
     uint16_t* vT = at<uint16_t>(ws, P.off_cvol + P.h2_tar_off);
-    const int64_t plane = 16 * (int64_t)P.H * P.h2_pitch;
+    const int64_t plane = P.h2_plane;
     STEREO_HIP(launch_ncc(P, ref, tarw, m.zX, m.isdX, m.zY, m.isdY, reinterpret_cast<float*>(vR),
                           ncc_both_extent(P.h2_pitch, 0, P.D), P.h2_pitch, plane, 0, stream, 0,
                           -1, 4, P.R, lr ? reinterpret_cast<float*>(vT) : nullptr),
@@ -398,10 +405,10 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
   a.guide_pitch = P.p.pitch_ref;
   a.dint = dint_R;
   a.dsub = ds;
-  STEREO_HIP(launch_bilateral(P, a, 1, stream), "bilateral + WTA (reference)");
-  STEREO_HIP(mark(4), "event record");
+  a.state = at<float>(ws, P.off_state);
+  BilArgs v[2] = {a, a};
   if (lr) {
-    BilArgs b = a;
+    BilArgs& b = v[1];
     if (a.h2) b.h2 = at<uint16_t>(ws, P.off_cvol + P.h2_tar_off);
     else b.shift = 1;
     b.guide = tarw;
@@ -409,7 +416,19 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
     b.guide_pitch = P.W;
     b.dint = dT;
     b.dsub = nullptr;
-    STEREO_HIP(launch_bilateral(P, b, 1, stream), "bilateral + WTA (target)");
+    b.state = a.state + (size_t)h2_state_floats(P.D, 1) * P.W * P.H;
+  }
+  // both volumes in one launch on the split-FP16 matrix cores (more segments
+  // to spread over the chip), unless the stages are timed apart
+  if (a.h2 && !ev) {
+    STEREO_HIP(launch_bilateral_h2(P, v, lr ? 2 : 1, 1, stream), "bilateral + WTA");
+  } else {
+    auto run = [&](const BilArgs& b) {
+      return b.h2 ? launch_bilateral_h2(P, &b, 1, 1, stream) : launch_bilateral(P, b, 1, stream);
+    };
+    STEREO_HIP(run(v[0]), "bilateral + WTA (reference)");
+    STEREO_HIP(mark(4), "event record");
+    if (lr) STEREO_HIP(run(v[1]), "bilateral + WTA (target)");
   }
   STEREO_HIP(mark(5), "event record");
   if (valid || disp)

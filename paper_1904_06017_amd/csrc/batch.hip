@@ -24,9 +24,17 @@ struct Group {
   stereo_dtype gdt;
   int levels;
   std::vector<int> tiles;     // (pair descriptor index, x0, y0) triples, vector-ALU tiles
-  std::vector<int> tiles_m;   // the same over the matrix-core tiles
+  std::vector<int> tiles_m;   // the same over the FP32 matrix-core tiles
   size_t tiles_off;           // in the workspace
   size_t tiles_m_off;
+};
+
+// The split-FP16 engine's groups: every volume of one radius, both guide
+// types, as strip segments sorted longest first.
+struct SegGroup {
+  int R;
+  std::vector<Seg> segs;
+  size_t off;                 // in the workspace
 };
 
 // One batched launch of a cheap stage: its jobs (pair, and for statistics
@@ -56,6 +64,7 @@ struct stereo_batch_s {
   std::vector<Plan> plans;             // copies of the pairs' plans
   std::vector<size_t> pair_ws;         // offset of each pair's plan workspace
   std::vector<Group> groups;
+  std::vector<SegGroup> seg_groups;
   std::vector<JobList> lists;
   size_t desc_off = 0, desc_bytes = 0; // per-volume descriptors (2 per pair)
   size_t counter_off = 0;
@@ -63,7 +72,7 @@ struct stereo_batch_s {
   std::vector<char> host_desc;         // descriptors bound to the last workspace
   void* bound_ws = nullptr;
   int wg_per_cu = 2;
-  int tile_band = 4;                   // tile columns per band of the matrix-core tile list
+  int tile_band = 4;                   // tile columns (strips) per band of the matrix-core lists
   int ncc_levels = 0;                  // NCC levels per workgroup (0: automatic)
   int overlap = 1;                     // split-FP16 engine: the aggregation of the
                                        // smaller radii beside the largest radius's NCC
@@ -90,33 +99,70 @@ T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
-// Block prefix of the NCC job lists for the batch's engine: the quad volume
-// covers the extended columns (anchor 0 only); the split-FP16 engine writes
-// both anchors' volumes (the target-anchored one when the pair has an LR
-// check) from one job over the stored row plus the levels.
-// Levels per NCC workgroup of a job list: the both-anchors form of the
-// split-FP16 engine runs at most 32 (its register count fits two 16-wave
-// workgroups per CU only below that).
-int ncc_dc(const stereo_batch_s& b, const JobList& L) {
-  if (b.ncc_levels) return b.ncc_levels;
-  return b.engine == 2 ? std::min(L.dc, 32) : L.dc;
-}
+// Block prefix of the NCC job lists: engines 0 and 1 compute the quad volume
+// over the extended columns; the split-FP16 engine launches the NCC per pair.
+int ncc_dc(const stereo_batch_s& b, const JobList& L) { return b.ncc_levels ? b.ncc_levels : L.dc; }
 
 void ncc_blocks(stereo_batch_s& b) {
   for (JobList& L : b.lists) {
     if (L.kind != JK_NCC) continue;
     for (size_t k = 0; k < L.pair.size(); ++k) {
       const Plan& P = b.plans[L.pair[k]];
-      int blocks = 0;
-      if (b.engine == 2) {
-        if (L.which[k] == 0)
-          blocks = ncc_job_blocks(P, ncc_both_extent(P.h2_pitch, 0, P.D), 0, P.D,
-                                  ncc_dc(b, L), 4);
-      } else if (L.which[k] == 0) {
-        blocks = ncc_job_blocks(P, P.W + P.D - 1, 0, P.D, L.dc, 1);
-      }
-      L.first[k + 1] = L.first[k] + blocks;
+      L.first[k + 1] = L.first[k] + ncc_job_blocks(P, P.W + P.D - 1, 0, P.D, ncc_dc(b, L));
     }
+  }
+}
+
+// Strip segments of the split-FP16 engine.  Per radius, a pair's strips are
+// cut so that the whole group makes about four segments per workgroup (a
+// segment fills and drains its pipeline of block rows, so short ones cost
+// more), listed in bands of tile_band adjacent strips of one vertical range
+// (their halo columns meet in an XCD's L2) and sorted by cost, longest first.
+void seg_tables(stereo_batch_s& b) {
+  constexpr int kFill = 6;             // phases a segment takes beyond its block rows
+  constexpr double kShares = 4.0 * 256.0;
+  struct V { int pair, vol; double w; };
+  struct S { double cost; Seg seg; };
+  b.seg_groups.clear();
+  std::vector<std::vector<V>> vols;
+  for (int i = 0; i < (int)b.plans.size(); ++i) {
+    const Plan& P = b.plans[i];
+    size_t g = 0;
+    while (g < b.seg_groups.size() && b.seg_groups[g].R != P.R) ++g;
+    if (g == b.seg_groups.size()) {
+      SegGroup G;
+      G.R = P.R;
+      G.off = 0;
+      b.seg_groups.push_back(G);
+      vols.emplace_back();
+    }
+    // a phase: the weights once per sweep of 64 levels, the products per 16
+    const int nblk = (P.D + 15) / 16;
+    for (int vol = 0; vol < (P.p.lr_check ? 2 : 1); ++vol)
+      vols[g].push_back({i, vol, 2.0 * ((nblk + 3) / 4) + nblk});
+  }
+  for (size_t g = 0; g < b.seg_groups.size(); ++g) {
+    double total = 0.0;
+    for (const V& v : vols[g]) {
+      const Plan& P = b.plans[v.pair];
+      total += v.w * ((P.W + kSegW - 1) / kSegW) * ((P.H + kSegRow - 1) / kSegRow);
+    }
+    std::vector<S> all;
+    for (const V& v : vols[g]) {
+      const Plan& P = b.plans[v.pair];
+      const int tx = (P.W + kSegW - 1) / kSegW, br = (P.H + kSegRow - 1) / kSegRow;
+      const int want = std::max(8, (int)(total / kShares / v.w));
+      const int n = std::max(1, (br + want - 1) / want), len = (br + n - 1) / n;
+      for (int xb = 0; xb < tx; xb += b.tile_band)
+        for (int r = 0; r < br; r += len)
+          for (int x = xb; x < std::min(tx, xb + b.tile_band); ++x) {
+            const int l = std::min(len, br - r);
+            all.push_back({v.w * (l + kFill), {2 * v.pair + v.vol, x * kSegW, r, l}});
+          }
+    }
+    std::stable_sort(all.begin(), all.end(), [](const S& a, const S& c) { return a.cost > c.cost; });
+    b.seg_groups[g].segs.clear();
+    for (const S& e : all) b.seg_groups[g].segs.push_back(e.seg);
   }
 }
 
@@ -173,6 +219,11 @@ void build_layout(stereo_batch_s& b) {
     table(per[gi], b.groups[gi].tiles, b.groups[gi].tiles_off);
     table(per_m[gi], b.groups[gi].tiles_m, b.groups[gi].tiles_m_off);
   }
+  seg_tables(b);
+  for (SegGroup& G : b.seg_groups) {
+    G.off = o;
+    o = align256(o + sizeof(Seg) * G.segs.size());
+  }
   b.counter_off = o;
   o = align256(o + sizeof(unsigned int) * std::max<size_t>(1, b.groups.size()));
   // job lists of the cheap stages, in launch order
@@ -207,16 +258,13 @@ void build_layout(stereo_batch_s& b) {
     Lt.r = std::max(Lt.r, P.r);
   }
   // NCC: the level block of the list's smallest pair (the smallest block that
-  // holds its levels, at most 64); two job slots per pair (which = 0: the
-  // job, covering both anchors with the split-FP16 engine; which = 1 has no
-  // blocks), their blocks set per engine by ncc_blocks
+  // holds its levels, at most 64)
   for (int i = 0; i < n; ++i) {
     const Plan& P = b.plans[i];
     JobList& L = list_of(JK_NCC, P.p.dtype, P.r);
     const int dc = P.D > 32 ? 64 : P.D > 16 ? 32 : 16;
     L.dc = L.pair.empty() ? dc : std::min(L.dc, dc);
     push(L, i, 0, 0);
-    push(L, i, 1, 0);
   }
   ncc_blocks(b);
   for (int i = 0; i < n; ++i)
@@ -252,7 +300,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     BilArgs a{};
     if (b.engine == 2) {
       a.h2 = at<uint16_t>(pws, P.off_cvol);
-      a.h2_plane = 16 * (int64_t)P.H * P.h2_pitch;
+      a.h2_plane = P.h2_plane;
       a.h2_pitch = P.h2_pitch;
     } else {
       a.C = at<float>(pws, P.off_cvol);
@@ -266,6 +314,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     a.guide_pitch = P.p.pitch_ref;
     a.dint = b.items[i].dint_R;
     a.dsub = at<float>(pws, P.off_dsub);
+    a.state = at<float>(pws, P.off_state);
     bilateral_pair(P, a, b.host_desc.data() + (2 * i) * pb);
     BilArgs t = a;
     if (b.engine == 2) t.h2 = at<uint16_t>(pws, P.off_cvol + P.h2_tar_off);
@@ -275,6 +324,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     t.guide_pitch = P.W;
     t.dint = at<int16_t>(pws, P.off_dT);
     t.dsub = nullptr;
+    t.state = a.state + (size_t)h2_state_floats(P.D, 1) * P.W * P.H;
     bilateral_pair(P, t, b.host_desc.data() + (2 * i + 1) * pb);
   }
   BHIP(hipMemcpyAsync(at<char>(ws, b.desc_off), b.host_desc.data(), b.desc_bytes,
@@ -303,20 +353,9 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
             : stats_job(P, tarw, P.W, st + 2 * sn, st + 3 * sn);
         memcpy(dst, &J, sizeof(J));
       } else if (L.kind == JK_NCC) {
-        NccJob J;
-        if (b.engine == 2) {
-          // both anchored split volumes from one job (which = 0; the second
-          // job of the pair has no blocks)
-          J = ncc_job(P, b.items[i].ref, tarw, st, st + sn, st + 2 * sn, st + 3 * sn,
-                      at<float>(pws, P.off_cvol), ncc_both_extent(P.h2_pitch, 0, P.D),
-                      P.h2_pitch, 16 * (int64_t)P.H * P.h2_pitch, 0, 0, P.D, 4,
-                      P.p.lr_check ? at<float>(pws, P.off_cvol + P.h2_tar_off) : nullptr, ws);
-          J.pad = P.R;
-        } else {
-          J = ncc_job(P, b.items[i].ref, tarw, st, st + sn, st + 2 * sn, st + 3 * sn,
-                      at<float>(pws, P.off_cvol), P.W + P.D - 1, P.cw, (int64_t)P.H * P.cw, 0,
-                      0, P.D, 1, nullptr, ws);
-        }
+        const NccJob J = ncc_job(P, b.items[i].ref, tarw, st, st + sn, st + 2 * sn, st + 3 * sn,
+                                 at<float>(pws, P.off_cvol), P.W + P.D - 1, P.cw,
+                                 (int64_t)P.H * P.cw, 0, P.D, ws);
         memcpy(dst, &J, sizeof(J));
       } else {
         const LrJob J = lr_job(P, b.items[i].dint_R,
@@ -337,6 +376,9 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
                         sizeof(int) * G.tiles_m.size(), hipMemcpyHostToDevice, s),
          "upload matrix-core tiles");
   }
+  for (const SegGroup& G : b.seg_groups)
+    BHIP(hipMemcpyAsync(at<char>(ws, G.off), G.segs.data(), sizeof(Seg) * G.segs.size(),
+                        hipMemcpyHostToDevice, s), "upload strip segments");
   BHIP(hipStreamSynchronize(s), "synchronise after upload");
   b.bound_ws = ws;
   return STEREO_OK;
@@ -355,7 +397,7 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
     const size_t sn = (size_t)P.stats_w * P.H;
     BHIP(launch_ncc(P, b.items[i].ref, tarw, st, st + sn, st + 2 * sn, st + 3 * sn,
                     at<float>(pws, P.off_cvol), ncc_both_extent(P.h2_pitch, 0, P.D), P.h2_pitch,
-                    16 * (int64_t)P.H * P.h2_pitch, 0, s, 0, -1, 4, P.R,
+                    P.h2_plane, 0, s, 0, -1, 4, P.R,
                     P.p.lr_check ? at<float>(pws, P.off_cvol + P.h2_tar_off) : nullptr),
          "batch ncc (per pair)");
     return STEREO_OK;
@@ -383,14 +425,13 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
           // start-up outweighs the launches it saves (64 mixed pairs: 6.4
           // against 8.9 ms)
           for (size_t k = 0; k < L.pair.size(); ++k) {
-            if (L.which[k] != 0) continue;
             stereo_status st = ncc_pair(L.pair[k]);
             if (st != STEREO_OK) return st;
           }
           break;
         }
-        BHIP(launch_ncc_jobs(L.r, L.dt, 1, ncc_dc(b, L), static_cast<const NccJob*>(jobs), first,
-                             nj, blocks, static_cast<char*>(ws), s),
+        BHIP(launch_ncc_jobs(L.r, L.dt, ncc_dc(b, L), static_cast<const NccJob*>(jobs), first, nj, blocks,
+                             static_cast<char*>(ws), s),
              "batch ncc");
         break;
       case JK_LR:
@@ -402,11 +443,21 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
   };
   // warp first (the target statistics read its output), then statistics, NCC
   unsigned int* ctr = at<unsigned int>(ws, b.counter_off);
-  const int ng = (int)b.groups.size();
+  const int nc = (int)b.groups.size();               // tile counters (engines 0 and 1)
+  const int ng = b.engine == 2 ? (int)b.seg_groups.size() : nc;
   const void* desc = at<char>(ws, b.desc_off);
+  auto group_R = [&](int g) { return b.engine == 2 ? b.seg_groups[g].R : b.groups[g].R; };
   auto run_group = [&](int g, hipStream_t st) -> stereo_status {
+    if (b.engine == 2) {                 // one workgroup per CU holds the whole LDS
+      const SegGroup& G = b.seg_groups[g];
+      const int n = (int)G.segs.size();
+      BHIP(launch_bilateral_h2_queue(G.R, desc, at<Seg>(ws, G.off), n,
+                                     std::max(1, std::min(n, b.cu_count)), st),
+           "batch aggregation");
+      return STEREO_OK;
+    }
     const Group& G = b.groups[g];
-    if (b.engine >= 1) {                 // one workgroup per CU holds the whole LDS
+    if (b.engine == 1) {                 // one workgroup per CU holds the whole LDS
       const int nt = (int)G.tiles_m.size() / 3;
       const int groups = std::max(1, std::min(nt, b.cu_count));
       BHIP(launch_bilateral_persistent(b.engine, G.R, G.gdt, G.levels, desc,
@@ -436,13 +487,10 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
           stereo_status st = run_list(L);
           if (st != STEREO_OK) return st;
         }
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, ctr, ng);
-    BHIP(hipGetLastError(), "zero counters");
     auto ncc_pairs = [&](bool small) -> stereo_status {
       for (const JobList& L : b.lists) {
         if (L.kind != JK_NCC) continue;
         for (size_t k = 0; k < L.pair.size(); ++k) {
-          if (L.which[k] != 0) continue;
           const int i = L.pair[k];
           if ((b.plans[i].R < rmax) != small) continue;
           stereo_status st = ncc_pair(i);
@@ -456,11 +504,11 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
     BHIP(hipEventRecord(b.fork, s), "event record");
     BHIP(hipStreamWaitEvent(b.side, b.fork, 0), "stream wait");
     for (int g = 0; g < ng; ++g)
-      if (b.groups[g].R < rmax && (st = run_group(g, b.side)) != STEREO_OK) return st;
+      if (group_R(g) < rmax && (st = run_group(g, b.side)) != STEREO_OK) return st;
     BHIP(hipEventRecord(b.join, b.side), "event record");
     if ((st = ncc_pairs(false)) != STEREO_OK) return st;
     for (int g = 0; g < ng; ++g)
-      if (b.groups[g].R == rmax && (st = run_group(g, s)) != STEREO_OK) return st;
+      if (group_R(g) == rmax && (st = run_group(g, s)) != STEREO_OK) return st;
     BHIP(hipStreamWaitEvent(s, b.join, 0), "stream wait");
   } else {
     for (JobKind k : {JK_WARP, JK_STATS, JK_NCC})
@@ -469,8 +517,10 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
           stereo_status st = run_list(L);
           if (st != STEREO_OK) return st;
         }
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, ctr, ng);
-    BHIP(hipGetLastError(), "zero counters");
+    if (b.engine != 2) {
+      hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, ctr, nc);
+      BHIP(hipGetLastError(), "zero counters");
+    }
     if (ev) BHIP(hipEventRecord(ev[0], s), "event record");
     for (int g = 0; g < ng; ++g) {
       stereo_status st = run_group(g, s);

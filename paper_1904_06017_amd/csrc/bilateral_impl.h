@@ -91,6 +91,8 @@ struct BilPair {
   int W, H, D;
   float ks2, kr2;
   BilOut o;
+  int g_u8;                         // guide of uint8 (else FP32)
+  float* state;                     // selection state between sweeps (see BilArgs)
   const uint16_t* h2;               // split-FP16 volume (see BilArgs)
   int64_t h2_plane;
   int h2_pitch;
@@ -489,6 +491,8 @@ inline BilPair make_pair(const Plan& P, const BilArgs& a) {
   BilPair b;
   b.C = a.C; b.c_slice = a.c_slice; b.c_pitch = a.c_pitch; b.shift = a.shift; b.quad = a.quad;
   b.guide = a.guide; b.g_pitch = a.guide_pitch;
+  b.g_u8 = a.guide_dt == STEREO_U8;
+  b.state = a.state;
   b.W = P.W; b.H = P.H; b.D = a.levels > 0 ? a.levels : P.D;
   b.ks2 = c.ks2; b.kr2 = c.kr2;
   BilOut& o = b.o;

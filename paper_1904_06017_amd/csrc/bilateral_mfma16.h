@@ -25,11 +25,16 @@
 //
 // Costs.  The NCC writes two split-FP16 volumes, reference-anchored and
 // target-anchored, so both volumes stage the same way.  Each is stored in
-// blocks of 16 levels, [block][part][row][column quad][16 levels][4 columns]
-// (columns shifted by R so that a tile's halo starts at a column quad): one
-// operand read (16 levels x 4 columns of a row) is 128 contiguous bytes, and
-// one halo row of a block part is HXP / 4 x 128 contiguous bytes.  A
-// workgroup (12 waves) owns a 16 x 12 pixel tile; each pass of 16 levels
+// blocks of 16 levels, [block][part][row pair][column quad][16 levels][2 rows]
+// [4 columns] (columns shifted by R and rows by R & 1, so that a block's
+// union starts at a column quad and a row pair): the 8 values of a lane's
+// patch are 16 contiguous bytes, one operand read (16 levels x a patch) is
+// 256 contiguous bytes read by ds_read_b128, and one halo row pair of a block
+// part is HXP / 4 x 256 contiguous bytes.  The LDS returns 209 bytes per
+// cycle to 16-byte reads but 119 to 8-byte ones (12 waves, this access
+// pattern): with rows stored singly (two 8-byte reads per patch and part) the
+// products of a pass took 2630 cycles, now 2000, near the 1800 of the matrix
+// cores alone.  A workgroup (12 waves) owns a 16 x 12 pixel tile; each pass of 16 levels
 // copies the halo slab (2 parts x (12 + 2R) rows x HXP columns x 16 levels)
 // global -> LDS with direct-to-LDS loads into one of two buffers while the
 // other is being multiplied, one barrier per pass.  Rows outside the image
@@ -70,29 +75,34 @@ struct HGeom {
   static constexpr int HY = kTH + 2 * R;                // halo rows
   static constexpr int HXP = (4 * (kTW / 4 - 1) + UW + 7) & ~7;   // halo columns
   static constexpr int NQH = HXP / 4;                   // column quads per halo row
-  static constexpr int ROWB = NQH * 128;                // bytes per halo row of a part
-  static constexpr int PARTB = HY * ROWB;               // bytes per part of a slab
-  static constexpr int CPR = NQH * 8;                   // 16-byte chunks per row
-  static constexpr int NCH = 2 * HY * CPR;              // chunks per slab
-  static constexpr int NWC = (NCH + 63) / 64;           // wave copies per slab
+  static constexpr int HP = HY / 2;                     // halo row pairs
+  static constexpr int PAIRB = NQH * 256;               // bytes per halo row pair of a part
+  static constexpr int PARTB = HP * PAIRB;              // bytes per part of a slab
+  static constexpr int NWC = 2 * HY;                    // wave copies per slab
   static constexpr int KPW = (NWC + kWaves - 1) / kWaves;
   static constexpr int BUF = 2 * PARTB / 4;             // dwords per slab
-  // guide row stride (floats) = 4 NQH: a patch's guide offset (floats) is
-  // 4 x its offset in 128-byte units
-  static constexpr int GS = HXP;
-  static constexpr int GUIDE = HY * GS;
+  // the guide tile is laid out like a level of the slab, [row pair][column
+  // quad][2 rows][4 columns] floats: a patch's guide offset (floats) is 8 x
+  // its offset in 256-byte units
+  static constexpr int GUIDE = HY * HXP;
   static constexpr int GPT = (GUIDE + kThreads - 1) / kThreads;
-  static constexpr int SCR = kWaves * 16 * 20;          // per-wave [pixel][20] scratch
   static constexpr int STAB = NI * 64 * 8;              // spatial terms [i][lane][slot]
-  static constexpr size_t base_bytes = sizeof(float) * (2 * (size_t)BUF + 2 * GUIDE + SCR);
+  static constexpr size_t base_bytes = sizeof(float) * (2 * (size_t)BUF + 2 * GUIDE);
   // the spatial terms are tabulated in LDS where it has room
   static constexpr bool kTable = base_bytes + sizeof(float) * STAB <= 160 * 1024;
   static constexpr size_t lds_bytes = base_bytes + (kTable ? sizeof(float) * STAB : 0);
-  static_assert(kTW + 2 * R <= GS && 4 * (kTW / 4 - 1) + UW <= GS, "guide rows");
-  static_assert(HY * NQH < 256, "patch offsets are packed in 8 bits");
+  static_assert(kTW + 2 * R <= HXP && 4 * (kTW / 4 - 1) + UW <= HXP, "halo columns");
+  static_assert(kTH % 2 == 0 && HY % 2 == 0, "halo rows come in pairs");
+  static_assert(HP * NQH < 256, "patch offsets are packed in 8 bits");
   static_assert(lds_bytes <= 160 * 1024, "LDS budget");
   static_assert(PARTB < 65536, "lo-part offset must fit a DS immediate");
 };
+
+// Position (floats) of halo row yy, column xx in a guide tile.
+template <int R>
+__device__ __forceinline__ int guide_pos(int yy, int xx) {
+  return ((yy >> 1) * HGeom<R>::NQH + (xx >> 2)) * 8 + 4 * (yy & 1) + (xx & 3);
+}
 
 template <int R>
 inline int h2_pitch_for(int W) {
@@ -102,12 +112,14 @@ inline int h2_pitch_for(int W) {
 // The fields one tile needs; uniform across the workgroup.
 struct View {
   const uint16_t* V;              // split-FP16 volume
-  int64_t plane;                  // halves per block part: 16 H pitch
+  int64_t plane;                  // halves per block part: 16 h2_rows(R, H) pitch
   int pitch;                      // columns per row (a multiple of 8)
   const void* guide;
   int64_t g_pitch;
+  int g_u8;                       // guide of uint8 (else FP32)
   int W, H, D;
   float ks2, kr2;
+  float4* state;                  // selection state between sweeps of the levels
   int16_t* dint;                  // selection (mode 1)
   float* dsub;
   float* sm_m;                    // soft-argmin (mode 2)
@@ -125,6 +137,8 @@ __host__ __device__ inline View view_of(const BilPair& a) {
   v.pitch = a.h2_pitch;
   v.guide = a.guide;
   v.g_pitch = a.g_pitch;
+  v.g_u8 = a.g_u8;
+  v.state = reinterpret_cast<float4*>(a.state);
   v.W = a.W; v.H = a.H; v.D = a.D;
   v.ks2 = a.ks2;
   v.kr2 = a.kr2;
@@ -141,68 +155,44 @@ __host__ __device__ inline View view_of(const BilPair& a) {
 }
 
 // Slab of levels [d0, d0 + 16) (one stored block) of the tile at (x0, y0)
-// into buf: [part][row][column quad][16 levels][4 columns] halves.  Chunk c
-// (16 bytes) is part c / (HY CPR), row (c / CPR) % HY, bytes 16 (c % CPR) of
-// the row, the same bytes as in the stored block row.  Rows clamp to the
-// image.
+// into buf: [part][row pair][column quad][16 levels][2 rows][4 columns]
+// halves, the same bytes as in the stored block.  One wave copy is half a
+// halo row pair of one part (NQH x 128 bytes; with 24 halo columns 48 of the
+// 64 lanes take part): copy k = wave + kWaves m is half k % HY of part k / HY.
+// Row pairs clamp to the stored ones (image row y is row (y + (R & 1)) & 1 of
+// pair (y + (R & 1)) >> 1; a row of the first or last pair outside the image
+// holds zeros).  A copy's address is scalar but for the lane, so the border
+// needs no path of its own.
 template <int R>
-__device__ __forceinline__ void stage(const View& v, int x0, int y0, int d0, float* buf,
-                                      int wave, int lane, const int (&coff)[HGeom<R>::KPW],
-                                      bool fast) {
+struct Slab {
   using G = HGeom<R>;
-  const int64_t rows = 16 * (int64_t)v.pitch;          // halves per stored row
-  if (fast && y0 >= R && y0 + kTH + R <= v.H) {
-    const uint16_t* base = v.V + (int64_t)(2 * (d0 >> 4)) * v.plane + (int64_t)(y0 - R) * rows +
-                           16 * x0;
-    if constexpr (G::CPR == 64) {
-      // one wave copy = one halo row of one part: (part, row) = (k / HY, k % HY)
-#pragma unroll
-      for (int m = 0; m < G::KPW; ++m) {
-        const int k = wave + kWaves * m;
-        if (k < G::NWC) {
-          const int pr = k / G::HY, row = k - pr * G::HY;
-          __builtin_amdgcn_global_load_lds(
-              (BILM_GLOBAL void*)(base + pr * v.plane + row * rows + 8 * lane),
-              (BILM_LOCAL void*)(buf + k * 256), 16, 0, 0);
-        }
-      }
-    } else {
-      // interior rows: the lane's chunk offsets relative to the slab origin
-      // were formed once per kernel
-#pragma unroll
-      for (int m = 0; m < G::KPW; ++m) {
-        const int k = wave + kWaves * m;
-        if (k < G::NWC && coff[m] >= 0)
-          __builtin_amdgcn_global_load_lds((BILM_GLOBAL void*)(base + coff[m]),
-                                           (BILM_LOCAL void*)(buf + k * 256), 16, 0, 0);
-      }
-    }
-    return;
-  }
-  // border tiles: rows clamped; recomputed per call so that nothing of it
-  // stays live
-  int ln = lane;
-  asm volatile("" : "+v"(ln));
-#pragma unroll
-  for (int m = 0; m < G::KPW; ++m) {
+  const uint16_t* base;           // block of d0, part 0, column quad of x0
+  int64_t plane, rows;            // halves per part, per stored row pair
+  int pair0, last;                // first halo row pair, last stored one
+
+  __device__ __forceinline__ Slab(const View& v, int x0, int y0, int d0)
+      : base(v.V + (int64_t)(2 * (d0 >> 4)) * v.plane + 32 * x0), plane(v.plane),
+        rows(32 * (int64_t)v.pitch), pair0((y0 >> 1) - (R >> 1)),
+        last((v.H - 1 + (R & 1)) >> 1) {}
+
+  __device__ __forceinline__ void copy(int m, float* buf, int wave, int lane) const {
     const int k = wave + kWaves * m;
     if (k < G::NWC) {
-      const int c = k * 64 + ln;
-      if (c < G::NCH) {
-        const int pr = c / (G::HY * G::CPR);
-        const int w = c - pr * (G::HY * G::CPR);
-        const int row = w / G::CPR;
-        const int cr = w - row * G::CPR;
-        int gy = y0 - R + row;
-        gy = gy < 0 ? 0 : (gy >= v.H ? v.H - 1 : gy);
-        const int64_t off = (int64_t)(2 * (d0 >> 4) + pr) * v.plane + (int64_t)gy * rows +
-                            16 * x0 + 8 * cr;
-        __builtin_amdgcn_global_load_lds((BILM_GLOBAL void*)(v.V + off),
-                                         (BILM_LOCAL void*)(buf + k * 256), 16, 0, 0);
-      }
+      const int pr = k >= G::HY ? 1 : 0, h = k - pr * G::HY;
+      int gp = pair0 + (h >> 1);
+      gp = gp < 0 ? 0 : (gp > last ? last : gp);
+      const uint16_t* src = base + pr * plane + gp * rows + (h & 1) * (G::NQH * 64);
+      if (G::NQH == 8 || lane < G::NQH * 8)
+        __builtin_amdgcn_global_load_lds((BILM_GLOBAL void*)(src + 8 * lane),
+                                         (BILM_LOCAL void*)(buf + k * (G::NQH * 32)), 16, 0, 0);
     }
   }
-}
+  // every copy of this wave
+  __device__ __forceinline__ void all(float* buf, int wave, int lane) const {
+#pragma unroll
+    for (int m = 0; m < G::KPW; ++m) copy(m, buf, wave, lane);
+  }
+};
 
 // Guide of a tile's halo: the raw values are loaded into registers
 // (unconditionally, clamped addresses) and turned into the scaled guide
@@ -222,7 +212,7 @@ __device__ __forceinline__ void guide_load(const View& v, int x0, int y0, GuideR
 #pragma unroll
   for (int k = 0; k < G::GPT; ++k) {
     const int i = threadIdx.x + k * kThreads;
-    const int yy = i / G::GS, xx = i % G::GS;
+    const int yy = i / G::HXP, xx = i % G::HXP;
     const int cy = min(max(y0 - R + yy, 0), v.H - 1), cx = min(max(x0 - R + xx, 0), v.W - 1);
     g.raw[k] = src[(int64_t)cy * v.g_pitch + cx];
   }
@@ -247,10 +237,10 @@ __device__ __forceinline__ void guide_store(float* gs, const GuideRaw<R, GT>& g,
 #pragma unroll
   for (int k = 0; k < G::GPT; ++k) {
     const int i = threadIdx.x + k * kThreads;
-    const int yy = i / G::GS, xx = i % G::GS;
+    const int yy = i / G::HXP, xx = i % G::HXP;
     const int gy = y0 - R + yy, gx = x0 - R + xx;
     const bool in = xx < kTW + 2 * R && gy >= 0 && gy < v.H && gx >= 0 && gx < v.W;
-    if (i < G::GUIDE) gs[i] = in ? guide_value(g.raw[k], z) * kr : kFar;
+    if (i < G::GUIDE) gs[guide_pos<R>(yy, xx)] = in ? guide_value(g.raw[k], z) * kr : kFar;
   }
 }
 
@@ -276,486 +266,10 @@ __device__ __forceinline__ void split8(const float (&w)[8], u4& hi, u4& lo) {
   }
 }
 
-// MODE 1: winner-take-all and the parabola (Eq. 13) -> dint, dsub.  MODE 2:
-// the soft-argmin head over the normalised costs (P = softmax_d(-E/T)) -> the
-// soft level, its state (max, log Z) and the shifted disparity.
-template <int R, typename GT, int QUEUE, int MODE>
-__global__ void __launch_bounds__(kThreads, 1)
-agg_mfma16_kernel(View one, const BilPair* __restrict__ pairs, const int* __restrict__ tiles,
-                  int n_tiles, unsigned int* __restrict__ counter) {
-  using G = HGeom<R>;
-  constexpr int NI = G::NI;
-  extern __shared__ float lds[];
-  float* const buf0 = lds;
-  float* const buf1 = lds + G::BUF;
-  float* const gbuf0 = lds + 2 * G::BUF;
-  float* const gbuf1 = gbuf0 + G::GUIDE;
-  float* const scr = gbuf1 + G::GUIDE;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int by = wave >> 2, bx = wave & 3;
-  const int li = lane & 15, lk = lane >> 4;      // MFMA roles: row/column 16, k-group 4
-  const int pr = li >> 2, pc = li & 3;
-  const int P = lane >> 2, Q = lane & 3;         // selection roles: pixel, level quarter
-  float* sc = scr + wave * (16 * 20);
-  const float* prow = sc + P * 20;
-
-  // offset (128-byte units: one row of a column quad) of this lane's patch
-  // 4 i + lk for every product i, four per register (zero-weight padding
-  // patches read patch 0); the operand of level li is 128 poff + 8 li bytes
-  // into a slab part, the patch's guide 4 poff floats into the guide tile
-  unsigned poff[(NI + 3) / 4];
-#pragma unroll
-  for (int i = 0; i < NI; i += 4) {
-    unsigned v4 = 0;
-#pragma unroll
-    for (int h = 0; h < 4 && i + h < NI; ++h) {
-      int p = 4 * (i + h) + lk;
-      p = p < G::NP ? p : 0;
-      const int rp = p / G::NCQ, cq = p - rp * G::NCQ;
-      v4 |= (unsigned)((4 * by + 2 * rp) * G::NQH + bx + cq) << (8 * h);
-    }
-    poff[i / 4] = v4;
-  }
-  const int lbase = 8 * li;
-  // unpacked at every use (opaque to the compiler): hoisted, the twelve
-  // unpacked offsets would stay live across the tile loop and spill
-  auto patch_off = [&](int i) -> int {
-    unsigned pk = poff[i >> 2];
-    asm volatile("" : "+v"(pk));
-    return (int)((pk >> (8 * (i & 3))) & 0xFFu);
-  };
-  // chunk offsets (halves) of this lane's slab copies relative to the slab
-  // origin (interior tiles; -1: the chunk is past the slab)
-  int coff[G::KPW];
-  if constexpr (G::CPR != 64) {
-    const int64_t vplane = QUEUE ? 0 : one.plane;
-    const int64_t rows = QUEUE ? 0 : 16 * (int64_t)one.pitch;
-#pragma unroll
-    for (int m = 0; m < G::KPW; ++m) {
-      const int c = (wave + kWaves * m) * 64 + lane;
-      const int pr = c / (G::HY * G::CPR);
-      const int w = c - pr * (G::HY * G::CPR);
-      const int row = w / G::CPR;
-      const int cr = w - row * G::CPR;
-      coff[m] = c < G::NCH ? (int)(pr * vplane + row * rows) + 8 * cr : -1;
-    }
-  }
-  // spatial terms of this lane's slots, tabulated once per launch in LDS
-  // (where it has room): per-pair launches keep the exponent
-  // 12 - |p - q|^2 log2(e) / sigma_s^2, queued launches (whose pairs may
-  // differ in sigma_s) the squared distance |p - q|^2; -inf / +inf outside
-  // the pixel's window and for padding patches
-  float* const stab = scr + G::SCR;
-  auto dist2 = [&](int i, int s) -> float {
-    const int p = 4 * i + lk;
-    const int rp = p / G::NCQ, cq = p - rp * G::NCQ;
-    const int ty = 2 * rp + (s >> 2) - pr - R, tx = 4 * cq + (s & 3) - pc - R;
-    return (p < G::NP && ty >= -R && ty <= R && tx >= -R && tx <= R) ? (float)(ty * ty + tx * tx)
-                                                                     : __builtin_inff();
-  };
-  constexpr bool kTab = G::kTable;
-  if constexpr (kTab) {
-    if (wave == 0) {
-#pragma unroll 1
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const float d2 = dist2(i, s);
-          stab[(i * 64 + lane) * 8 + s] = QUEUE ? d2 : fmaf(-d2, one.ks2, kLog2WScale);
-        }
-    }
-  }
-
-  // tiles of this workgroup.  QUEUE = 1: (pair, x0, y0) triples of a list
-  // sorted longest first, dealt one per workgroup and round (below), so that
-  // every workgroup's share costs nearly the same.  A shared counter would balance at run time, but an atomic that
-  // returns its value waits behind the direct-to-LDS copies in flight and
-  // stalls the whole workgroup once per tile.  QUEUE = 0, the tiles of one
-  // pair: XCD x walks the tile columns of band x row by row.
-  int tx = 1, n1 = n_tiles, per = 0, c0 = 0, bc = 1, nb = 0;
-  if (!QUEUE) {
-    tx = __builtin_amdgcn_readfirstlane((one.W + kTW - 1) / kTW);
-    n1 = __builtin_amdgcn_readfirstlane(tx * ((one.H + kTH - 1) / kTH));
-    if (gridDim.x % 8 == 0) {
-      per = gridDim.x / 8;
-      const int bw = (tx + 7) / 8;
-      c0 = (blockIdx.x % 8) * bw;
-      bc = tx - c0 < bw ? (tx - c0 > 0 ? tx - c0 : 0) : bw;
-      nb = bc * (n1 / tx);
-    }
-  }
-  auto arith_tile = [&](int k) -> int {
-    if (QUEUE) {
-      // round k of G workgroups covers entries [k G, (k + 1) G); workgroup b
-      // (XCD b % 8) takes entry k G + (b % 8) G / 8 + b / 8, so that each XCD
-      // works on a contiguous run of the list: the host orders a pair's tiles
-      // in bands of a few tile columns walked row by row, so a run is a 2-D
-      // patch of tiles whose halos meet in that XCD's L2
-      const int G = (int)gridDim.x;
-      if (G % 8 == 0) return k * G + ((int)blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8;
-      return (int)blockIdx.x + G * k;
-    }
-    if (per) {
-      const int idx = (int)blockIdx.x / 8 + per * k;
-      if (idx >= nb) return n1;
-      const int row = __builtin_amdgcn_readfirstlane(idx / bc);
-      return row * tx + c0 + (idx - row * bc);
-    }
-    return (int)blockIdx.x + (int)gridDim.x * k;
-  };
-  auto resolve = [&](int t, View& v, int& x0, int& y0) {
-    if (QUEUE) {
-      const int* e = tiles + 3 * t;
-      v = view_of(pairs[e[0]]);
-      x0 = e[1]; y0 = e[2];
-    } else {
-      v = one;
-      const int ty = __builtin_amdgcn_readfirstlane(t / tx);
-      x0 = (t - ty * tx) * kTW;
-      y0 = ty * kTH;
-    }
-  };
-
-  int cur = arith_tile(0);
-  if (cur >= n1) return;                         // uniform
-  {
-    View cv;
-    int cx0, cy0;
-    resolve(cur, cv, cx0, cy0);
-    GuideRaw<R, GT> g;
-    stage<R>(cv, cx0, cy0, 0, buf0, wave, lane, coff, !QUEUE || G::CPR == 64);
-    guide_load<R, GT>(cv, cx0, cy0, g);
-    guide_store<R, GT>(gbuf0, g, cv, cx0, cy0);
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-
-  int par = 0, gpar = 0;
-  for (int k = 0;; ++k) {
-    // weights of this wave's block, split in FP16 halves: lane (li, lk)
-    // holds w(pixel li, slot s of patch 4 i + lk) in ahi[i][s], alo[i][s]
-    u4 ahi[NI], alo[NI];
-    float wsum = 0.0f;
-    // queued launches read this tile's descriptor once, keeping scalar loads
-    // out of the pass loop, where they would hold up the operand reads that
-    // share their wait counter; per-pair launches take the kernel argument
-    View tv;
-    int tx0, ty0;
-    resolve(cur, tv, tx0, ty0);
-    {
-      View cv;
-      int cx0, cy0;
-      if (QUEUE) cv = tv; else resolve(cur, cv, cx0, cy0);
-      const float* gs = gpar ? gbuf1 : gbuf0;
-      const float Gp = gs[(4 * by + pr + R) * G::GS + 4 * bx + pc + R];
-      float ks2 = cv.ks2;
-      asm volatile("" : "+v"(ks2));
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        // opaque per product: keeps the guide and table reads next to their use
-        const float* gp = gs + 4 * patch_off(i);
-        const float4 g0 = *reinterpret_cast<const float4*>(gp);
-        const float4 g1 = *reinterpret_cast<const float4*>(gp + G::GS);
-        float sv[8];
-        if constexpr (kTab) {
-          int to = (i * 64 + lane) * 8;
-          asm volatile("" : "+v"(to));
-          const float* tp = stab + to;
-          const float4 s0 = *reinterpret_cast<const float4*>(tp);
-          const float4 s1 = *reinterpret_cast<const float4*>(tp + 4);
-          sv[0] = s0.x; sv[1] = s0.y; sv[2] = s0.z; sv[3] = s0.w;
-          sv[4] = s1.x; sv[5] = s1.y; sv[6] = s1.z; sv[7] = s1.w;
-          if constexpr (QUEUE) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) sv[q] = fmaf(-sv[q], ks2, kLog2WScale);
-          }
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) sv[q] = fmaf(-dist2(i, q), ks2, kLog2WScale);
-        }
-        const float gq[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        float w[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const float g = Gp - gq[q];
-          w[q] = __builtin_amdgcn_exp2f(fmaf(-g, g, sv[q]));
-        }
-        split8(w, ahi[i], alo[i]);
-        if constexpr (MODE == 2) {
-          const h8 wh = __builtin_bit_cast(h8, ahi[i]), wl = __builtin_bit_cast(h8, alo[i]);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) wsum += (float)wh[q] + (float)wl[q];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // soft-argmin: 1 / W_p of selection pixel P (W_p = sum of its weights:
-    // a lane's slots, then the four lanes of pixel li)
-    float rinvP = 1.0f, zscale = 0.0f;
-    if constexpr (MODE == 2) {
-      View cv;
-      int cx0, cy0;
-      if (QUEUE) cv = tv; else resolve(cur, cv, cx0, cy0);
-      zscale = -cv.invT * 1.4426950408889634f;
-      float ws = wsum;
-      ws += __shfl_xor(ws, 16);
-      ws += __shfl_xor(ws, 32);
-      rinvP = 1.0f / __shfl(ws, P);
-    }
-    // no barrier here: the weights read only this tile's guide (complete since
-    // the last pass's barrier) and the spatial table
-    const int nxt = arith_tile(k + 1);
-    const bool has_next = nxt < n1;
-    View nv = tv;
-    int nx0 = 0, ny0 = 0;
-    if (QUEUE && has_next) resolve(nxt, nv, nx0, ny0);
-
-    float bestE = 3.402823466e38f, Em = 0.f, Ep = 0.f, lastE = 0.f;
-    int bestD = 0;
-    bool pending = false;
-    constexpr float kNeg = -3.402823466e38f;
-    float mr = kNeg, Zr = 0.0f, Sr = 0.0f;
-    int D, passes;
-    {
-      View cv;
-      int cx0, cy0;
-      if (QUEUE) cv = tv; else resolve(cur, cv, cx0, cy0);
-      D = cv.D;
-      passes = (D + 15) / 16;
-    }
-    for (int p = 0; p < passes; ++p) {
-      // the pass reads one buffer while the copies fill the other; as
-      // __restrict__ parameters the compiler knows that they do not alias
-      // and does not wait for the copies before the pass's first LDS read
-      // (1280x720, D = 64, R = 7: 0.272 -> 0.257 ms per launch)
-      auto pass_body = [&](float* __restrict__ cbuf, float* __restrict__ obuf) {
-      const int d0 = 16 * p;
-      const bool last = p + 1 == passes;
-      GuideRaw<R, GT> gq;
-      if (!last || has_next) {
-        View sv;
-        int sx0, sy0;
-        if (QUEUE) {
-          sv = last ? nv : tv;
-          sx0 = last ? nx0 : tx0;
-          sy0 = last ? ny0 : ty0;
-        } else {
-          resolve(last ? nxt : cur, sv, sx0, sy0);
-        }
-        stage<R>(sv, sx0, sy0, last ? 0 : d0 + 16, obuf, wave, lane, coff, !QUEUE || G::CPR == 64);
-        if (last) guide_load<R, GT>(sv, sx0, sy0, gq);
-      }
-      const char* cb = reinterpret_cast<const char*>(cbuf);
-      // two accumulators (products i even / odd): halves the dependent chain
-      f4 acc = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-      // operands of product i + 1 are read while product i is multiplied
-      u4 bh[2], bl[2];
-      auto load_b = [&](int i, u4& h, u4& l) {
-        const char* a = cb + lbase + 128 * patch_off(i);
-        const uint2 h0 = *reinterpret_cast<const uint2*>(a);
-        const uint2 h1 = *reinterpret_cast<const uint2*>(a + G::ROWB);
-        const uint2 l0 = *reinterpret_cast<const uint2*>(a + G::PARTB);
-        const uint2 l1 = *reinterpret_cast<const uint2*>(a + G::PARTB + G::ROWB);
-        h = u4{h0.x, h0.y, h1.x, h1.y};
-        l = u4{l0.x, l0.y, l1.x, l1.y};
-      };
-      __builtin_amdgcn_sched_barrier(0);
-      load_b(0, bh[0], bl[0]);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        if (i + 1 < NI) load_b(i + 1, bh[(i + 1) & 1], bl[(i + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        const h8 bH = __builtin_bit_cast(h8, bh[i & 1]);
-        const h8 bL = __builtin_bit_cast(h8, bl[i & 1]);
-        const h8 aH = __builtin_bit_cast(h8, ahi[i]);
-        const h8 aL = __builtin_bit_cast(h8, alo[i]);
-        f4& ac = (i & 1) ? acc1 : acc;
-        ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(aH, bH, ac, 0, 0, 0);
-        ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(aH, bL, ac, 0, 0, 0);
-        ac = __builtin_amdgcn_mfma_f32_16x16x32_f16(aL, bH, ac, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      acc += acc1;
-      // lane holds pixel 4 lk + v, level d0 + li
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sc[(4 * lk + v) * 20 + li] = acc[v];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if constexpr (MODE == 1) {
-        // first minimum over the pass: a quad of lanes per pixel, four levels
-        // per lane, then merged across the quad (lower level wins ties)
-        const float4 e4 = *reinterpret_cast<const float4*>(prow + 4 * Q);
-        const int nvl = D - d0 - 4 * Q;
-        const float inf = __builtin_inff();
-        const float e0 = nvl > 0 ? e4.x : inf, e1 = nvl > 1 ? e4.y : inf;
-        const float e2 = nvl > 2 ? e4.z : inf, e3 = nvl > 3 ? e4.w : inf;
-        float m = fminf(fminf(e0, e1), fminf(e2, e3));
-        int idx = 4 * Q + (e0 == m ? 0 : (e1 == m ? 1 : (e2 == m ? 2 : 3)));
-        {
-          const float om = bilm::dpp_f<0xB1>(m);
-          const int oi = __builtin_amdgcn_mov_dpp(idx, 0xB1, 0xF, 0xF, false);
-          const bool take = om < m || (om == m && oi < idx);
-          m = take ? om : m;
-          idx = take ? oi : idx;
-        }
-        {
-          const float om = bilm::dpp_f<0x4E>(m);
-          const int oi = __builtin_amdgcn_mov_dpp(idx, 0x4E, 0xF, 0xF, false);
-          const bool take = om < m || (om == m && oi < idx);
-          m = take ? om : m;
-          idx = take ? oi : idx;
-        }
-        if (pending) Ep = prow[0];               // level after a best at the previous pass's end
-        if (m < bestE) {
-          Em = idx > 0 ? prow[idx > 0 ? idx - 1 : 0] : lastE;
-          Ep = prow[idx < 15 ? idx + 1 : 15];
-          bestE = m;
-          bestD = d0 + idx;
-          pending = idx == 15;
-        } else {
-          pending = false;
-        }
-        lastE = prow[D - d0 < 16 ? D - d0 - 1 : 15];
-      } else {
-        // soft-argmin: each lane keeps the running state (max, Z, S) of its
-        // quarter of every pass's levels; the quad is merged once per tile
-        const float4 e4 = *reinterpret_cast<const float4*>(prow + 4 * Q);
-        const int nvl = D - d0 - 4 * Q;
-        const float zv[4] = {nvl > 0 ? e4.x * rinvP * zscale : kNeg, nvl > 1 ? e4.y * rinvP * zscale : kNeg,
-                             nvl > 2 ? e4.z * rinvP * zscale : kNeg, nvl > 3 ? e4.w * rinvP * zscale : kNeg};
-        const float M = fmaxf(mr, fmaxf(fmaxf(zv[0], zv[1]), fmaxf(zv[2], zv[3])));
-        const float a = __builtin_amdgcn_exp2f(mr - M);
-        Zr *= a;
-        Sr *= a;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float e = nvl > j ? __builtin_amdgcn_exp2f(zv[j] - M) : 0.0f;
-          Zr += e;
-          Sr = fmaf((float)(d0 + 4 * Q + j), e, Sr);
-        }
-        mr = M;
-      }
-      if (last && has_next) {
-        View gv = nv;
-        int gx0 = nx0, gy0 = ny0;
-        if (!QUEUE) resolve(nxt, gv, gx0, gy0);
-        guide_store<R, GT>(gpar ? gbuf0 : gbuf1, gq, gv, gx0, gy0);
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      };
-      pass_body(par ? buf1 : buf0, par ? buf0 : buf1);
-      par ^= 1;
-    }
-    if constexpr (MODE == 2) {
-      auto merge = [&](float om, float oZ, float oS) {
-        const float M = fmaxf(mr, om);
-        const float a = __builtin_amdgcn_exp2f(mr - M), b = __builtin_amdgcn_exp2f(om - M);
-        Zr = fmaf(Zr, a, oZ * b);
-        Sr = fmaf(Sr, a, oS * b);
-        mr = M;
-      };
-      merge(bilm::dpp_f<0xB1>(mr), bilm::dpp_f<0xB1>(Zr), bilm::dpp_f<0xB1>(Sr));
-      merge(bilm::dpp_f<0x4E>(mr), bilm::dpp_f<0x4E>(Zr), bilm::dpp_f<0x4E>(Sr));
-    }
-    if (MODE == 2 && Q == 0) {
-      View cv;
-      int cx0, cy0;
-      resolve(cur, cv, cx0, cy0);
-      const int py = cy0 + 4 * by + (P >> 2), px = cx0 + 4 * bx + (P & 3);
-      if (py < cv.H && px < cv.W) {
-        const int64_t pix = (int64_t)py * cv.W + px;
-        const float ln2 = 0.6931471805599453f;
-        const float dh = Sr / Zr;
-        cv.sm_m[pix] = mr * ln2;
-        cv.sm_logZ[pix] = __builtin_amdgcn_logf(Zr) * ln2;
-        cv.sm_dh[pix] = dh;
-        const double dd = dh;
-        cv.disp[pix] = (float)(dd - cv.delta_p + (cv.c0 + cv.c1 * ((double)px - dd + cv.delta_p) +
-                                                  cv.c2 * (double)py));
-      }
-    }
-    if (MODE == 1 && Q == 0) {
-      View cv;
-      int cx0, cy0;
-      resolve(cur, cv, cx0, cy0);
-      const int py = cy0 + 4 * by + (P >> 2), px = cx0 + 4 * bx + (P & 3);
-      if (py < cv.H && px < cv.W) {
-        cv.dint[(int64_t)py * cv.W + px] = (int16_t)bestD;
-        if (cv.dsub) {
-          float off = 0.0f;
-          if (bestD > 0 && bestD < D - 1) {
-            const float den = 2.0f * Em + 2.0f * Ep - 4.0f * bestE;
-            if (den > 0.0f) off = (Em - Ep) / den;
-          }
-          cv.dsub[(int64_t)py * cv.W + px] = (float)bestD + off;
-        }
-      }
-    }
-    if (!has_next) break;
-    cur = nxt;
-    gpar ^= 1;
-  }
-}
-
-template <int R, typename GT, int QUEUE, int MODE>
-hipError_t set_lds_attr() {
-  static bool done = false;
-  if (!done) {
-    hipError_t e = hipFuncSetAttribute((const void*)agg_mfma16_kernel<R, GT, QUEUE, MODE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)HGeom<R>::lds_bytes);
-    if (e != hipSuccess) return e;
-    done = true;
-  }
-  return hipSuccess;
-}
-
-// One pair: persistent, one workgroup per CU.
-template <int R, typename GT, int MODE>
-hipError_t launch_pair(const BilPair& a, hipStream_t s) {
-  if (!a.h2 || a.h2_pitch < h2_pitch_for<R>(a.W) || (a.h2_pitch & 7) ||
-      a.h2_plane < 16 * (int64_t)a.H * a.h2_pitch)
-    return hipErrorInvalidValue;
-  hipError_t e = set_lds_attr<R, GT, 0, MODE>();
-  if (e != hipSuccess) return e;
-  const int n = ((a.W + kTW - 1) / kTW) * ((a.H + kTH - 1) / kTH);
-  const int cus = bilm::cu_count_of_current_device();
-  int grid = std::min(n, cus > 0 ? cus : 256);
-  if (grid >= 8) grid -= grid % 8;               // whole XCD bands
-  hipLaunchKernelGGL((agg_mfma16_kernel<R, GT, 0, MODE>), dim3(grid), dim3(kThreads),
-                     HGeom<R>::lds_bytes, s, view_of(a), (const BilPair*)nullptr,
-                     (const int*)nullptr, 0, (unsigned int*)nullptr);
-  return hipGetLastError();
-}
-
-// Queue of (pair, x0, y0) tiles over many pairs (x0 a multiple of kTW, y0 of kTH).
-template <int R, typename GT>
-hipError_t launch_queue(const BilPair* pairs, const int* tiles, int n_tiles, unsigned int* counter,
-                        int n_groups, hipStream_t s) {
-  hipError_t e = set_lds_attr<R, GT, 1, 1>();
-  if (e != hipSuccess) return e;
-  View none{};
-  hipLaunchKernelGGL((agg_mfma16_kernel<R, GT, 1, 1>), dim3(n_groups), dim3(kThreads),
-                     HGeom<R>::lds_bytes, s, none, pairs, tiles, n_tiles, counter);
-  return hipGetLastError();
-}
-
-template <int R>
-hipError_t launch_args(const Plan& P, const BilArgs& a, int mode, hipStream_t s) {
-  const BilPair b = bil::make_pair(P, a);
-  if (mode == 2)
-    return a.guide_dt == STEREO_U8 ? launch_pair<R, uint8_t, 2>(b, s) : launch_pair<R, float, 2>(b, s);
-  return a.guide_dt == STEREO_U8 ? launch_pair<R, uint8_t, 1>(b, s) : launch_pair<R, float, 1>(b, s);
-}
-
-template <int R>
-hipError_t launch_queue_r(stereo_dtype gdt, const BilPair* pairs, const int* tiles, int n_tiles,
-                          unsigned int* counter, int n_groups, hipStream_t s) {
-  return gdt == STEREO_U8 ? launch_queue<R, uint8_t>(pairs, tiles, n_tiles, counter, n_groups, s)
-                          : launch_queue<R, float>(pairs, tiles, n_tiles, counter, n_groups, s);
+// v of another lane of the wave (index taken modulo 64).
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
+                                       4 * lane, __builtin_bit_cast(int, v)));
 }
 
 }  // namespace bilh

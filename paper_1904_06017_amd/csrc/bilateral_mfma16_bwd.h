@@ -66,13 +66,15 @@ __host__ __device__ inline float cprime_scale(unsigned int bits) {
   return s;
 }
 
-// One level block of a tile, [16 levels][kTH rows][kTW columns] floats: pass
-// 2 stages the costs at the tile's pixels in it and collects its outputs in
-// two more, so that both move between HBM and LDS in whole 64-byte rows.
+// One level block of a tile, [16 levels][kTH rows][kTW columns] dwords: both
+// passes collect their outputs in two of them (pass 1 C' as packed FP16 halves,
+// pass 2 dC), so that they leave for HBM in whole runs; pass 2 also stages the
+// costs at the tile's pixels.
 constexpr int kTileBlk = 16 * kTH * kTW;
+constexpr int kScr = kWaves * 16 * 20;          // per-wave scratch (floats)
 template <int R, int PASS>
 constexpr size_t bwd_lds_bytes() {
-  return HGeom<R>::lds_bytes + (PASS == 2 ? sizeof(float) * 2 * kTileBlk : 0);
+  return HGeom<R>::lds_bytes + sizeof(float) * kScr + sizeof(float) * 2 * kTileBlk;
 }
 
 template <int R, int PASS>
@@ -86,11 +88,11 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
   float* const gbuf0 = lds + 2 * G::BUF;
   float* const gbuf1 = gbuf0 + G::GUIDE;
   float* const scr = gbuf1 + G::GUIDE;
-  float* const stab = scr + G::SCR;
-  float* const tout = stab + G::STAB;             // pass 2: two output blocks
+  float* const stab = scr + kScr;
+  float* const tout = stab + G::STAB;             // two output blocks
   static_assert(G::kTable, "the backward keeps the spatial terms in LDS");
   static_assert(bwd_lds_bytes<R, PASS>() <= 160 * 1024, "LDS budget");
-  static_assert(kTileBlk + kWaves * 32 <= G::SCR, "pass 2's cost block and sums fit the scratch");
+  static_assert(kTileBlk + kWaves * 32 <= kScr, "pass 2's cost block and sums fit the scratch");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int by = wave >> 2, bx = wave & 3;
@@ -106,28 +108,16 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
       int p = 4 * (i + h) + lk;
       p = p < G::NP ? p : 0;
       const int rp = p / G::NCQ, cq = p - rp * G::NCQ;
-      v4 |= (unsigned)((4 * by + 2 * rp) * G::NQH + bx + cq) << (8 * h);
+      v4 |= (unsigned)((2 * by + rp) * G::NQH + bx + cq) << (8 * h);
     }
     poff[i / 4] = v4;
   }
-  const int lbase = 8 * li;
+  const int lbase = 16 * li;
   auto patch_off = [&](int i) -> int {
     unsigned pk = poff[i >> 2];
     asm volatile("" : "+v"(pk));
     return (int)((pk >> (8 * (i & 3))) & 0xFFu);
   };
-  int coff[G::KPW];
-  if constexpr (G::CPR != 64) {
-#pragma unroll
-    for (int m = 0; m < G::KPW; ++m) {
-      const int c = (wave + kWaves * m) * 64 + lane;
-      const int pr2 = c / (G::HY * G::CPR);
-      const int w = c - pr2 * (G::HY * G::CPR);
-      const int row = w / G::CPR;
-      const int cr = w - row * G::CPR;
-      coff[m] = c < G::NCH ? (int)(pr2 * one.plane + row * 16 * (int64_t)one.pitch) + 8 * cr : -1;
-    }
-  }
   if (wave == 0) {
 #pragma unroll 1
     for (int i = 0; i < NI; ++i)
@@ -183,7 +173,7 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
     int cx0, cy0;
     origin(cur, cx0, cy0);
     GuideRaw<R, float> g;
-    stage<R>(one, cx0, cy0, 0, buf0, wave, lane, coff, true);
+    Slab<R>(one, cx0, cy0, 0).all(buf0, wave, lane);
     guide_load<R, float>(one, cx0, cy0, g);
     guide_store<R, float>(gbuf0, g, one, cx0, cy0);
   }
@@ -199,12 +189,12 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
     float wsum = 0.0f;
     {
       const float* gs = gpar ? gbuf1 : gbuf0;
-      const float Gp = gs[(4 * by + pr + R) * G::GS + 4 * bx + pc + R];
+      const float Gp = gs[guide_pos<R>(4 * by + pr + R, 4 * bx + pc + R)];
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        const float* gp = gs + 4 * patch_off(i);
+        const float* gp = gs + 8 * patch_off(i);
         const float4 g0 = *reinterpret_cast<const float4*>(gp);
-        const float4 g1 = *reinterpret_cast<const float4*>(gp + G::GS);
+        const float4 g1 = *reinterpret_cast<const float4*>(gp + 4);
         int to = (i * 64 + lane) * 8;
         asm volatile("" : "+v"(to));
         const float4 s0 = *reinterpret_cast<const float4*>(stab + to);
@@ -278,25 +268,46 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
     // a pass's outputs leave at the start of the next pass (or after the
     // last): issued before the copies, they have a pass to complete before
     // the wait at its end instead of holding it up
-    float ov[4] = {0.f, 0.f, 0.f, 0.f};
-    int oaddr = -1;                               // pass 1: the lane's (level, row) in C' S
-    int opass = -1;                               // pass 2: level block held in tout
-    int obuf_sel = 0;                             //   and which of the two
+    int opass = -1;                               // level block held in tout
+    int obuf_sel = 0;                             // and which of the two
     auto flush = [&]() {
       if constexpr (PASS == 1) {
-        // level li of stored columns x + R (x = px0 + v), both halves; a
-        // column quad of the layout straddles two of the block's columns
-        // unless R is a multiple of 4, so the halves go out one by one
-        if (oaddr >= 0) {
+        // chunk (row pair, column quad, level, row): the 4 columns of a level
+        // of a stored row, 8 bytes of each half; 32 lanes write a quad's 256
+        // bytes.  The tile's 16 columns start R & 3 into a stored quad and its
+        // rows R & 1 into a pair: chunks shared with a neighbouring tile go
+        // out value by value.
+        if (opass >= 0) {
+          constexpr int e = R & 1, QO = R & 3;
+          constexpr int NPR = (kTH + e + 1) / 2, NQ = (kTW + QO + 3) / 4;
+          const unsigned* to = reinterpret_cast<const unsigned*>(tout) + obuf_sel * kTileBlk;
+          int tid = threadIdx.x;
+          asm volatile("" : "+v"(tid));
+#pragma unroll 1
+          for (int n = 0; n < (NPR * NQ * 32 + kThreads - 1) / kThreads; ++n) {
+            const int c = tid + n * kThreads;
+            const int prn = c / (NQ * 32), rem = c - prn * (NQ * 32);
+            const int q = rem >> 5, l = (rem >> 1) & 15, par2 = rem & 1;
+            const int row = 2 * prn + par2 - e, c0 = 4 * q - QO;
+            if (prn >= NPR || row < 0 || row >= kTH || y0 + row >= one.H) continue;
+            const unsigned* src = to + (l * kTH + row) * kTW;
+            const int64_t o = (int64_t)(2 * opass) * one.plane +
+                              (int64_t)((y0 >> 1) + prn) * 32 * one.pitch +
+                              128 * (((x0 + R) >> 2) + q) + 8 * l + 4 * par2;
+            if (c0 >= 0 && c0 + 3 < kTW && x0 + c0 + 3 < one.W) {
+              const unsigned w0 = src[c0], w1 = src[c0 + 1], w2 = src[c0 + 2], w3 = src[c0 + 3];
+              *reinterpret_cast<uint2*>(b.h2out + o) =
+                  make_uint2((w0 & 0xFFFFu) | (w1 << 16), (w2 & 0xFFFFu) | (w3 << 16));
+              *reinterpret_cast<uint2*>(b.h2out + o + one.plane) =
+                  make_uint2((w0 >> 16) | (w1 & 0xFFFF0000u), (w2 >> 16) | (w3 & 0xFFFF0000u));
+            } else {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            if (px0 + v < one.W) {
-              const int sc = px0 + v + R;
-              const int o = oaddr + 64 * (sc >> 2) + (sc & 3);
-              const _Float16 hi = (_Float16)ov[v];
-              const _Float16 lo = (_Float16)(ov[v] - (float)hi);
-              b.h2out[o] = __builtin_bit_cast(uint16_t, hi);
-              b.h2out[o + (int)one.plane] = __builtin_bit_cast(uint16_t, lo);
+              for (int v = 0; v < 4; ++v) {
+                if (c0 + v < 0 || c0 + v >= kTW || x0 + c0 + v >= one.W) continue;
+                const unsigned w = src[c0 + v];
+                b.h2out[o + v] = (uint16_t)w;
+                b.h2out[o + one.plane + v] = (uint16_t)(w >> 16);
+              }
             }
           }
         }
@@ -323,8 +334,7 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
       flush();
       GuideRaw<R, float> gq;
       if (!last || has_next) {
-        stage<R>(one, last ? nx0 : x0, last ? ny0 : y0, last ? 0 : d0 + 16, obuf, wave, lane,
-                 coff, true);
+        Slab<R>(one, last ? nx0 : x0, last ? ny0 : y0, last ? 0 : d0 + 16).all(obuf, wave, lane);
         if (last) guide_load<R, float>(one, nx0, ny0, gq);
       }
       if constexpr (PASS == 2) {
@@ -351,16 +361,10 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
       // so the next low part is read while the high part's four run
       u4 bh, bl;
       auto load_h = [&](int i) {
-        const char* a = cb + lbase + 128 * patch_off(i);
-        const uint2 h0 = *reinterpret_cast<const uint2*>(a);
-        const uint2 h1 = *reinterpret_cast<const uint2*>(a + G::ROWB);
-        bh = u4{h0.x, h0.y, h1.x, h1.y};
+        bh = *reinterpret_cast<const u4*>(cb + lbase + 256 * patch_off(i));
       };
       auto load_l = [&](int i) {
-        const char* a = cb + lbase + 128 * patch_off(i) + G::PARTB;
-        const uint2 l0 = *reinterpret_cast<const uint2*>(a);
-        const uint2 l1 = *reinterpret_cast<const uint2*>(a + G::ROWB);
-        bl = u4{l0.x, l0.y, l1.x, l1.y};
+        bl = *reinterpret_cast<const u4*>(cb + lbase + 256 * patch_off(i) + G::PARTB);
       };
       __builtin_amdgcn_sched_barrier(0);
       load_l(0);
@@ -392,7 +396,7 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
       const bool rowin = py < one.H;
       int so = 4 * lk;
       asm volatile("" : "+v"(so));                 // read here, not hoisted
-      float ca[4], cb2[4];
+      float ca[4], cb2[4], ov[4];
       if constexpr (PASS == 1) {
         const float gscale = b.one_minus_c1 * (-b.invT);
 #pragma unroll
@@ -408,9 +412,17 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
           ca[v] = dE * e;
           cb2[v] = dE * ag[v];
         }
-        // offsets below 2^31: at most 64 levels (4 blocks) of one tile
-        oaddr = rowin && px0 < one.W ? (int)((2 * p) * one.plane) + py * 16 * one.pitch + 4 * li
-                                     : -1;
+        unsigned pk[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const _Float16 hi = (_Float16)ov[v];
+          const _Float16 lo = (_Float16)(ov[v] - (float)hi);
+          pk[v] = (unsigned)__builtin_bit_cast(uint16_t, hi) |
+                  ((unsigned)__builtin_bit_cast(uint16_t, lo) << 16);
+        }
+        *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(tout) + (gpass & 1) * kTileBlk +
+                                  (li * kTH + 4 * by + lk) * kTW + 4 * bx) =
+            make_uint4(pk[0], pk[1], pk[2], pk[3]);
       } else {
         // the costs at (level li, block row lk, columns v); the outputs into
         // the tile's output block at (level li, tile row 4 by + lk, columns 4 bx + v)
@@ -426,14 +438,14 @@ __global__ void __launch_bounds__(kThreads, 1) agg_mfma16_bwd_kernel(BView b) {
           ca[v] = 0.0f;
           cb2[v] = in ? cv[v] * ag[v] : 0.0f;
         }
-        // output blocks alternate with every pass of the launch (not of the
-        // tile), so a block is rewritten only after the barrier that follows
-        // its last read
         *reinterpret_cast<float4*>(tout + (gpass & 1) * kTileBlk + bo) =
             make_float4(ov[0], ov[1], ov[2], ov[3]);
-        opass = p;
-        obuf_sel = gpass & 1;
       }
+      // output blocks alternate with every pass of the launch (not of the
+      // tile), so a block is rewritten only after the barrier that follows
+      // its last read
+      opass = p;
+      obuf_sel = gpass & 1;
       // this pass's per-pixel sums over its 16 levels (lanes li), added to the
       // wave's running sums by the lanes li = 0
 #pragma unroll

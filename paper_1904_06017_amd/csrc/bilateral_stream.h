@@ -1,0 +1,740 @@
+// Bilateral cost aggregation, Eqs. (10)-(11), fused with winner-take-all
+// selection and sub-pixel refinement (Sec. 3.2.2, Eq. 13) or the soft-argmin
+// head, on the matrix cores with FP16 operands split in two: the products of
+// bilateral_mfma16.h (same operands, same order, so the same bits), streamed
+// down strips of the image.
+//
+// A workgroup owns a strip of kTW = 16 columns and walks down it one 4-row
+// block row per phase.  The cost volume's row pairs pass through a ring in
+// LDS, all NB level blocks (16 levels each) of a pair together, so each row
+// pair of the halo is copied once per strip instead of once per tile, and a
+// block's sums over all its levels form at the same time in NB accumulators.
+// The K loop of a block (its window union, NI products of 32 positions) runs
+// from top to bottom over S phases; the S groups of four waves (one wave per
+// 4x4 block across the strip) hold S consecutive block rows, one phase apart,
+// so that all of them read the same few row pairs at any time.  In every
+// phase a wave forms the weights of its next NI / S products and multiplies
+// them right away with the NB level blocks: weights (vector ALU), operand
+// reads (LDS) and products (matrix cores) overlap in every wave and across
+// the waves of a SIMD, and no weight is kept for longer than its product.
+//
+// What bounds it (1280x720, D = 64, R = 7, per block row and SIMD): about
+// 2400 cycles of weights on the vector ALU, 2400 of products and 2600 of LDS
+// reads, close to each other.  The form before (a tile's weights kept in
+// registers over passes of one level block each, every wave in the same
+// phase between barriers) spent 10200 cycles on the first pass of a tile,
+// vector ALU only, and 3600 on each other, matrix cores and LDS only.
+#pragma once
+#include "bilateral_mfma16.h"
+
+namespace stereo {
+namespace bils {
+
+using bil::BilPair;
+using bilh::f4;
+using bilh::h8;
+using bilh::HGeom;
+using bilh::kFar;
+using bilh::kLog2WScale;
+using bilh::kTW;
+using bilh::lane_value;
+using bilh::u4;
+using bilh::View;
+
+constexpr int kMaxNB = 4;               // level blocks per sweep
+static_assert(kTW == kSegW, "strips as the batch's segments");
+
+// Products of the S states of a block and the row pairs they read, relative
+// to the block's first: state k takes products [ps(k), ps(k + 1)).  In phase
+// t state k works on block row t - k, so it reads pairs lo(k) - 2 k .. hi(k) -
+// 2 k relative to pair 2 t.
+template <int R>
+struct Sched {
+  using G = HGeom<R>;
+  static constexpr int S = G::NI >= 4 ? 4 : 2;
+  // The group in state 0 also selects the levels of its last block: it gets
+  // one product less than an even share where that leaves it one.
+  static constexpr int ps(int k) {
+    return k == 0 ? 0 : k == S ? G::NI : (G::NI / S > 1 || G::NI % S ? -1 : 0) +
+           k * (G::NI / S) + (k < G::NI % S ? k : G::NI % S);
+  }
+  static constexpr int lo(int k) { return 4 * ps(k) / G::NCQ; }
+  static constexpr int hi(int k) {
+    return (4 * ps(k + 1) < G::NP ? 4 * ps(k + 1) - 1 : G::NP - 1) / G::NCQ;
+  }
+  static constexpr int wlo() {
+    int m = 0;
+    for (int k = 0; k < S; ++k) m = lo(k) - 2 * k < m ? lo(k) - 2 * k : m;
+    return m;
+  }
+  static constexpr int whi() {
+    int m = 0;
+    for (int k = 0; k < S; ++k) m = hi(k) - 2 * k > m ? hi(k) - 2 * k : m;
+    return m;
+  }
+};
+
+template <int R, int NB>
+struct SGeom {
+  using G = HGeom<R>;
+  using C = Sched<R>;
+  static constexpr int S = C::S;
+  static constexpr int kWaves = 4 * S, kThreads = 64 * kWaves;
+  static constexpr int WLO = C::wlo(), WHI = C::whi();
+  static constexpr int NSLOT = WHI - WLO + 1 + 2;        // pairs of a phase + the next two
+  static constexpr int CHB = G::NQH * 256;               // bytes: a pair of one block and part
+  static constexpr int SLOTB = NB * 2 * CHB;
+  // guide ring: a block's own pixels lie below the pairs of its first state
+  static constexpr int GHI = WHI > (R + 3) / 2 ? WHI : (R + 3) / 2;
+  static constexpr int NGS = GHI - WLO + 1 + 2;
+  static constexpr int GSB = G::NQH * 32;                // bytes: a pair of the guide
+  static constexpr int NGV = 2 * 2 * G::HXP;             // guide values of two pairs
+  static constexpr int NCP = 8 * NB;                     // wave copies of two pairs
+  static constexpr int KPW = (NCP + kWaves - 1) / kWaves;
+  // selection scratch of the group that finishes: a row of levels per pixel
+  static constexpr int EROW = 64 * NB + 16;
+  static constexpr size_t lds_bytes = (size_t)NSLOT * SLOTB + (size_t)NGS * GSB +
+                                      sizeof(float) * G::STAB + 64 * (size_t)EROW;
+  static_assert(lds_bytes <= 160 * 1024, "LDS budget");
+  static_assert((2 * NB - 1) * CHB < 65536, "operand offsets must fit a DS immediate");
+  static_assert(NGV <= kThreads, "one guide value per thread");
+};
+
+// LDS of a launch, laid out for kMaxNB blocks whatever a sweep takes: ring,
+// guide ring, spatial terms, selection scratch.
+template <int R>
+struct Lds {
+  using Z = SGeom<R, kMaxNB>;
+  static constexpr int gring = Z::NSLOT * Z::SLOTB;
+  static constexpr int tab = gring + Z::NGS * Z::GSB;
+  static constexpr int scratch = tab + (int)sizeof(float) * HGeom<R>::STAB;
+  static constexpr size_t bytes = Z::lds_bytes;
+};
+
+// A per-pair launch: the volumes of a pair (reference, then target), each cut
+// into strips and each strip into nseg segments of len block rows.  A queued
+// launch: n segments of many volumes, dealt one per workgroup and round.
+struct Args {
+  View v[2];
+  int nvol, nseg, len, tx, br;
+  int banded;                           // 1: XCD x owns a band of strips
+  const BilPair* descs;
+  const Seg* segs;
+  int n;
+};
+
+// Level blocks per sweep for nblk blocks: even shares of at most kMaxNB.
+inline __host__ __device__ int sweep_blocks(int nblk) {
+  const int n = (nblk + kMaxNB - 1) / kMaxNB;
+  return (nblk + n - 1) / n;
+}
+
+// x = hi + lo in FP16 for a pair of values (the conversions of bilh::split8,
+// left to the compiler so that it sees the hazards of the matrix cores
+// reading them); m1 = -1, opaque, keeps the remainder one mixed-precision FMA.
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_pair(float a, float b, float m1, unsigned& hi, unsigned& lo) {
+  const h2 h = __builtin_convertvector((f2{a, b}), h2);
+  const f2 r = {fmaf((float)h[0], m1, a), fmaf((float)h[1], m1, b)};
+  hi = __builtin_bit_cast(unsigned, h);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector(r, h2));
+}
+
+// value of lane q of this lane's row of 16
+template <int Q>
+__device__ __forceinline__ float row_value(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x150 + Q /* row_newbcast */, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ int lane_int(int v, int lane) {
+  return __builtin_amdgcn_ds_bpermute(4 * lane, v);
+}
+
+// the smallest of three, a NaN giving way to a number (one instruction; fminf
+// would quiet every operand first)
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// Priority of a wave with r products of the phase still to do: the waves of a
+// SIMD then end a phase together instead of the oldest first and the youngest
+// alone.
+__device__ __forceinline__ void priority(int r) {
+  if (r >= 3) __builtin_amdgcn_s_setprio(3);
+  else if (r == 2) __builtin_amdgcn_s_setprio(2);
+  else if (r == 1) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
+template <int K>
+struct Int {
+  static constexpr int value = K;
+};
+
+template <int R, int MODE, int NB>
+struct Worker {
+  using G = HGeom<R>;
+  using C = Sched<R>;
+  using Z = SGeom<R, NB>;
+  static constexpr int S = C::S;
+
+  char* ring;
+  char* gring;
+  char* scratch;
+  const float* tab;
+  int lane, wave, group, bx, li, lk;
+
+  __device__ __forceinline__ explicit Worker(float* lds)
+      : ring(reinterpret_cast<char*>(lds)), gring(ring + Lds<R>::gring),
+        scratch(ring + Lds<R>::scratch),
+        tab(reinterpret_cast<const float*>(ring + Lds<R>::tab)) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    group = wave >> 2;
+    bx = wave & 3;
+    li = lane & 15;
+    lk = lane >> 4;
+  }
+
+  __device__ __forceinline__ int wrap(int s, int n) const { return s < 0 ? s + n : s >= n ? s - n : s; }
+
+  // Block rows [b0, b0 + len) of the strip at column x0, levels [16 q0, 16
+  // (q0 + NB)) of the volume's nblk level blocks.  first / last: the first /
+  // last sweep of the strip's levels; between sweeps the selection state of a
+  // pixel is kept in v.state.
+  __device__ __forceinline__ void sweep(const View& v, int x0, int b0, int len, int q0, int nblk) {
+    const bool first = q0 == 0, last = q0 + NB >= nblk;
+    const int pair0 = 2 * b0 - (R >> 1);             // stored pair of ring pair 0
+    const int plast = (v.H - 1 + (R & 1)) >> 1;
+    const uint32_t rows = 32u * (uint32_t)v.pitch;    // halves per row pair
+    // this wave's copies of two row pairs: copy c = half c & 1 of part (c >> 1)
+    // & 1 of block (c >> 2) % NB of pair c / (4 NB)
+    const uint16_t* csrc[Z::KPW];
+    int cdst[Z::KPW], cpair[Z::KPW];
+#pragma unroll
+    for (int m = 0; m < Z::KPW; ++m) {
+      const int c = wave + Z::kWaves * m;
+      cpair[m] = c >= 4 * NB ? 1 : 0;
+      const int w = c - cpair[m] * 4 * NB, q = w >> 2, part = (w >> 1) & 1, half = w & 1;
+      const int blk = q0 + q < nblk ? q0 + q : nblk - 1;
+      csrc[m] = v.V + (int64_t)(2 * blk + part) * v.plane + 32 * x0 + half * (G::NQH * 64);
+      cdst[m] = (2 * q + part) * Z::CHB + half * (Z::CHB / 2);
+    }
+    // ring pairs j, j + 1 (j + 1 <= jmax) into their slots; slot: of pair j
+    const int jmax = 2 * (len - 1) + G::NRP - 1;
+    auto copy_pairs = [&](int j, int slot, char* __restrict__ wr) {
+#pragma unroll
+      for (int m = 0; m < Z::KPW; ++m) {
+        const int pj = j + cpair[m];
+        if (wave + Z::kWaves * m < Z::NCP && pj <= jmax) {
+          int gp = pair0 + pj;
+          gp = gp < 0 ? 0 : (gp > plast ? plast : gp);
+          const int sl = wrap(slot + cpair[m], Z::NSLOT);
+          const uint16_t* src = csrc[m] + (uint64_t)(uint32_t)gp * rows;
+          if (G::NQH == 8 || lane < G::NQH * 8)
+            __builtin_amdgcn_global_load_lds((BILM_GLOBAL void*)(src + 8 * lane),
+                                             (BILM_LOCAL void*)(wr + sl * Z::SLOTB + cdst[m]),
+                                             16, 0, 0);
+        }
+      }
+    };
+    // one value of guide pairs j, j + 1 per thread: raw, then scaled into LDS.
+    // The thread's place is worked out at each use: kept, it would cost
+    // registers of the products, and a spilled register's reload waits for
+    // every copy in flight.
+    const bool gw = wave < (Z::NGV + 63) / 64;       // waves that load guide values
+    const float kr = sqrtf(v.kr2);
+    auto guide_place = [&](int& gpr, int& grow, int& gcol) {
+      int gi = threadIdx.x;
+      asm volatile("" : "+v"(gi));
+      gpr = gi / (2 * G::HXP);
+      const int rem = gi - gpr * (2 * G::HXP);
+      grow = rem / G::HXP;
+      gcol = rem - grow * G::HXP;
+      return gi < Z::NGV;
+    };
+    auto guide_raw = [&](int j) -> unsigned {
+      int gpr, grow, gcol;
+      guide_place(gpr, grow, gcol);
+      const int y = 4 * b0 - R + 2 * (j + gpr) + grow, x = x0 - R + gcol;
+      const int64_t o = (int64_t)min(max(y, 0), v.H - 1) * v.g_pitch + min(max(x, 0), v.W - 1);
+      return v.g_u8 ? (unsigned)static_cast<const uint8_t*>(v.guide)[o]
+                    : static_cast<const unsigned*>(v.guide)[o];
+    };
+    auto guide_put = [&](int j, int slot, unsigned raw) {
+      int gpr, grow, gcol;
+      const bool mine = guide_place(gpr, grow, gcol);
+      const int y = 4 * b0 - R + 2 * (j + gpr) + grow, x = x0 - R + gcol;
+      const float f = v.g_u8 ? (float)raw : __builtin_bit_cast(float, raw);
+      const bool in = gcol < kTW + 2 * R && y >= 0 && y < v.H && x >= 0 && x < v.W;
+      const int sl = wrap(slot + gpr, Z::NGS);
+      if (mine)
+        *reinterpret_cast<float*>(gring + sl * Z::GSB + (gcol >> 2) * 32 + grow * 16 +
+                                  (gcol & 3) * 4) = in ? f * kr : kFar;
+    };
+
+    // the pairs of phase 0
+#pragma unroll
+    for (int j = 0; j <= Z::WHI; j += 2) copy_pairs(j, j, ring);
+#pragma unroll
+    for (int j = 0; j <= Z::GHI; j += 2)
+      if (gw) guide_put(j, j, guide_raw(j));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    f4 acc[NB][2];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q][0] = acc[q][1] = f4{0.f, 0.f, 0.f, 0.f};
+    float Gp = 0.f, wsum = 0.f;
+    // lane parts of the operand and guide addresses (patch column lk)
+    const int olane = (bx + lk) * 256 + 16 * li, olane0 = bx * 256 + 16 * li;
+    const int glane = (bx + lk) * 32 + 4 * (li & 7), glane0 = bx * 32 + 4 * (li & 7);
+
+    // Selection state of the sweep before (E, E-, E+, E of the last level; its
+    // level), read one phase ahead: at its use it would wait behind the copies.
+    float4 st = make_float4(3.402823466e38f, 0.f, 0.f, 0.f);
+    int stD = 0;
+    auto fetch_state = [&](int b) {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int py = 4 * (b0 + b) + ((ln >> 2) & 3), px = x0 + 4 * bx + (ln & 3);
+      const int64_t pix = py < v.H && px < v.W ? (int64_t)py * v.W + px : 0;
+      if (MODE == 1) {
+        st = v.state[pix];
+        stD = v.dint[pix];
+      } else {
+        st = v.state[4 * pix + (ln >> 4)];
+      }
+    };
+    // Selection over the block's levels: the lane holds E of pixel li at
+    // levels 16 (q0 + q) + 4 lk .. + 3 in acc[q].
+    auto finish = [&](int b) {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));                  // worked out here, not kept live
+      const int lk = ln >> 4, pr = (ln >> 2) & 3, pc = ln & 3, lane = ln;
+      const int py = 4 * (b0 + b) + pr, px = x0 + 4 * bx + pc;
+      const bool in = py < v.H && px < v.W;
+      const int64_t pix = in ? (int64_t)py * v.W + px : 0;
+      f4 e[NB];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) e[q] = acc[q][0] + acc[q][1];
+      if constexpr (MODE == 1) {
+        // the pixel's levels into the wave's scratch row, for the two around
+        // the minimum
+        char* const row = scratch + (bx * 16 + li) * Z::EROW;
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+          *reinterpret_cast<f4*>(row + 64 * q + 16 * lk) = e[q];
+        if (v.D < 16 * (q0 + NB)) {                    // uniform: levels past the range
+#pragma unroll
+          for (int q = 0; q < NB; ++q) {
+            const int nvl = v.D - 16 * (q0 + q) - 4 * lk;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[q][j] = nvl > j ? e[q][j] : __builtin_inff();
+          }
+        }
+        float m = 3.402823466e38f;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          m = min3(m, e[q][0], e[q][1]);
+          m = min3(m, e[q][2], e[q][3]);
+        }
+        m = min3(m, m, lane_value(m, lane ^ 16));
+        m = min3(m, m, lane_value(m, lane ^ 32));
+        // its first level: of the lane's, then of the pixel's four lanes
+        int first_at = 16 * NB;
+#pragma unroll
+        for (int q = NB - 1; q >= 0; --q)
+#pragma unroll
+          for (int j = 3; j >= 0; --j) first_at = e[q][j] == m ? 16 * q + j : first_at;
+        first_at += first_at < 16 * NB ? 4 * lk : 0;
+        first_at = min(first_at, lane_int(first_at, lane ^ 16));
+        first_at = min(first_at, lane_int(first_at, lane ^ 32));
+        first_at = first_at < 16 * NB ? first_at : 0;  // no level below the largest float
+        float bestE = m;
+        int bestD = 16 * q0 + first_at;
+        float Em = first_at > 0 ? *reinterpret_cast<const float*>(row + 4 * max(first_at - 1, 0)) : st.w;
+        float Ep = *reinterpret_cast<const float*>(row + 4 * min(first_at + 1, 16 * NB - 1));
+        if (!first) {
+          // a minimum at the last level of the sweep before takes its upper
+          // neighbour from this one
+          if (stD == 16 * q0 - 1) st.z = *reinterpret_cast<const float*>(row);
+          if (!(bestE < st.x)) {
+            bestE = st.x; bestD = stD; Em = st.y; Ep = st.z;
+          }
+        }
+        if (!last) {
+          const float top = *reinterpret_cast<const float*>(row + 64 * NB - 4);
+          if (lk == 0 && in) {
+            v.state[pix] = make_float4(bestE, Em, Ep, top);
+            v.dint[pix] = (int16_t)bestD;
+          }
+        } else if (lk == 0 && in) {
+          v.dint[pix] = (int16_t)bestD;
+          if (v.dsub) {
+            float off = 0.0f;
+            if (bestD > 0 && bestD < v.D - 1) {
+              const float den = 2.0f * Em + 2.0f * Ep - 4.0f * bestE;
+              if (den > 0.0f) off = (Em - Ep) / den;
+            }
+            v.dsub[pix] = (float)bestD + off;
+          }
+        }
+      } else {
+        // soft-argmin: each lane keeps (max, Z, S) of its quarter of every
+        // block's levels; the four lanes of a pixel merge at the end
+        constexpr float kNeg = -3.402823466e38f;
+        float mr = kNeg, Zr = 0.0f, Sr = 0.0f, rinvP;
+        if (first) {
+          float ws = wsum;                             // W_p: the pixel's weights
+          ws += __shfl_xor(ws, 16);
+          ws += __shfl_xor(ws, 32);
+          rinvP = 1.0f / ws;
+        } else {
+          mr = st.x; Zr = st.y; Sr = st.z; rinvP = st.w;
+        }
+        const float zscale = -v.invT * 1.4426950408889634f;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int dq = 16 * (q0 + q) + 4 * lk;
+          const int nvl = v.D - dq;
+          if (16 * (q0 + q) >= v.D) break;             // uniform
+          float zv[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) zv[j] = nvl > j ? e[q][j] * rinvP * zscale : kNeg;
+          const float M = fmaxf(mr, fmaxf(fmaxf(zv[0], zv[1]), fmaxf(zv[2], zv[3])));
+          const float a = __builtin_amdgcn_exp2f(mr - M);
+          Zr *= a;
+          Sr *= a;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float ez = nvl > j ? __builtin_amdgcn_exp2f(zv[j] - M) : 0.0f;
+            Zr += ez;
+            Sr = fmaf((float)(dq + j), ez, Sr);
+          }
+          mr = M;
+        }
+        if (!last) {
+          if (in) v.state[4 * pix + lk] = make_float4(mr, Zr, Sr, rinvP);
+          return;
+        }
+        auto merge = [&](float om, float oZ, float oS) {
+          const float M = fmaxf(mr, om);
+          const float a = __builtin_amdgcn_exp2f(mr - M), c = __builtin_amdgcn_exp2f(om - M);
+          Zr = fmaf(Zr, a, oZ * c);
+          Sr = fmaf(Sr, a, oS * c);
+          mr = M;
+        };
+        merge(lane_value(mr, lane ^ 16), lane_value(Zr, lane ^ 16), lane_value(Sr, lane ^ 16));
+        merge(lane_value(mr, lane ^ 32), lane_value(Zr, lane ^ 32), lane_value(Sr, lane ^ 32));
+        if (lk == 0 && in) {
+          const float ln2 = 0.6931471805599453f;
+          const float dh = Sr / Zr;
+          v.sm_m[pix] = mr * ln2;
+          v.sm_logZ[pix] = __builtin_amdgcn_logf(Zr) * ln2;
+          v.sm_dh[pix] = dh;
+          const double dd = dh;
+          v.disp[pix] = (float)(dd - v.delta_p + (v.c0 + v.c1 * ((double)px - dd + v.delta_p) +
+                                                  v.c2 * (double)py));
+        }
+      }
+    };
+
+    float m1 = -1.0f;
+    asm volatile("" : "+s"(m1));
+    int base = 0, gbase = 0;                          // ring slots of pair 2 t
+    // State k of a block in the current phase: its products.
+    auto products = [&](auto kc, const char* __restrict__ rd, const char* __restrict__ grd,
+                        const float* __restrict__ tb) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (k == 0) {
+        wsum = 0.f;
+        // the guide at the lane's own pixel
+        const int hr = (li >> 2) + R, hc = 4 * bx + (li & 3) + R;
+        const int s0 = wrap(gbase + (R >> 1), Z::NGS);
+        int sl = s0 + (hr >> 1) - (R >> 1);
+        sl = sl >= Z::NGS ? sl - Z::NGS : sl;
+        Gp = *reinterpret_cast<const float*>(grd + sl * Z::GSB + (hc >> 2) * 32 + (hr & 1) * 16 +
+                                             (hc & 3) * 4);
+      }
+#pragma unroll
+      for (int i = C::ps(k); i < C::ps(k + 1); ++i) {
+        priority(C::ps(k + 1) - 1 - i);
+        // patch 4 i + lk lies in pair r0 (lanes lk < thr) or r0 + 1, at column
+        // lk + (4 i - NCQ pair)
+        const int r0 = 4 * i / G::NCQ, thr = G::NCQ * (r0 + 1) - 4 * i;
+        const int a0 = 4 * i - G::NCQ * r0, a1 = a0 - G::NCQ;
+        const int rel = r0 - 2 * k;
+        const int so = wrap(base + rel, Z::NSLOT) * Z::SLOTB;
+        const int go = wrap(gbase + rel, Z::NGS) * Z::GSB;
+        int oa = so + 256 * a0 + olane, ga = go + 32 * a0 + glane;
+        if (thr < 4) {
+          if (4 * i + 3 < G::NP) {
+            const int so1 = wrap(base + rel + 1, Z::NSLOT) * Z::SLOTB;
+            const int go1 = wrap(gbase + rel + 1, Z::NGS) * Z::GSB;
+            oa = lk < thr ? oa : so1 + 256 * a1 + olane;
+            ga = lk < thr ? ga : go1 + 32 * a1 + glane;
+          } else if (4 * i + thr < G::NP) {
+            const int so1 = wrap(base + rel + 1, Z::NSLOT) * Z::SLOTB;
+            const int go1 = wrap(gbase + rel + 1, Z::NGS) * Z::GSB;
+            oa = lk < thr ? oa : lk < G::NP - 4 * i ? so1 + 256 * a1 + olane : so + olane0;
+            ga = lk < thr ? ga : lk < G::NP - 4 * i ? go1 + 32 * a1 + glane : go + glane0;
+          }
+        }
+        if (4 * i + 3 >= G::NP && !(thr < 4 && 4 * i + thr < G::NP)) {
+          // padding patches (zero weights) read the pair's first column
+          oa = lk < G::NP - 4 * i ? oa : so + olane0;
+          ga = lk < G::NP - 4 * i ? ga : go + glane0;
+        }
+        // weights of the product: 8 slots of the lane's patch
+        const float gl = *reinterpret_cast<const float*>(grd + ga);
+        const float4 s0 = *reinterpret_cast<const float4*>(tb + (i * 64 + lane) * 8);
+        const float4 s1 = *reinterpret_cast<const float4*>(tb + (i * 64 + lane) * 8 + 4);
+        const float g[8] = {row_value<0>(gl) - Gp, row_value<1>(gl) - Gp, row_value<2>(gl) - Gp,
+                            row_value<3>(gl) - Gp, row_value<4>(gl) - Gp, row_value<5>(gl) - Gp,
+                            row_value<6>(gl) - Gp, row_value<7>(gl) - Gp};
+        const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+        float w[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[q] = __builtin_amdgcn_exp2f(fmaf(-g[q], g[q], sv[q]));
+        u4 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          unsigned hb, lb;
+          split_pair(w[2 * j], w[2 * j + 1], m1, hb, lb);
+          hi[j] = hb;
+          lo[j] = lb;
+        }
+        const h8 aH = __builtin_bit_cast(h8, hi), aL = __builtin_bit_cast(h8, lo);
+        if constexpr (MODE == 2) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) wsum += (float)aH[q] + (float)aL[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const u4 bh = *reinterpret_cast<const u4*>(rd + oa + 2 * q * Z::CHB);
+          const u4 bl = *reinterpret_cast<const u4*>(rd + oa + (2 * q + 1) * Z::CHB);
+          const h8 bH = __builtin_bit_cast(h8, bh), bL = __builtin_bit_cast(h8, bl);
+          f4 c = i < 2 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][i & 1];
+          // costs as the first operand: the result has a pixel per lane column
+          // and four consecutive levels per lane
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, aH, c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(bL, aH, c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, aL, c, 0, 0, 0);
+          acc[q][i & 1] = c;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
+    // Phase t: block row t enters, the groups hold block rows t - k in state
+    // k; the copies of the next two pairs are in flight meanwhile.  A block's
+    // selection runs at the start of the phase after its last products, so
+    // that its stores have a phase to complete.
+    int k = group == 0 ? 0 : S - group;               // state of this wave's group
+    // The copies fill slots that no wave reads in the phase; as __restrict__
+    // parameters the compiler knows that and does not wait for them before
+    // the phase's first LDS read.
+    auto phase = [&](int t, char* __restrict__ wr, const char* __restrict__ rd,
+                     const char* __restrict__ grd, const float* __restrict__ tb) {
+      const int b = t - k;                            // block row of this wave
+      const int js = wrap(base + Z::WHI + 1, Z::NSLOT), gs = wrap(gbase + Z::GHI + 1, Z::NGS);
+      copy_pairs(2 * t + Z::WHI + 1, js, wr);
+      unsigned raw = 0;
+      if (gw) raw = guide_raw(2 * t + Z::GHI + 1);
+      if (!first && k == S - 1 && b >= 0) fetch_state(b);
+      if (k == 0 && b >= S) {
+        priority(3);
+        finish(b - S);
+      }
+      if (b >= 0 && b < len) {
+        if (k == 0) products(Int<0>{}, rd, grd, tb);
+        else if (k == 1) products(Int<1>{}, rd, grd, tb);
+        else if constexpr (S > 2) {
+          if (k == 2) products(Int<2>{}, rd, grd, tb);
+          else products(Int<3>{}, rd, grd, tb);
+        }
+      }
+      if (gw) guide_put(2 * t + Z::GHI + 1, gs, raw);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    };
+    for (int t = 0; t < len + S; ++t) {
+      phase(t, ring, ring, gring, tab);
+      base = wrap(base + 2, Z::NSLOT);
+      gbase = wrap(gbase + 2, Z::NGS);
+      k = k + 1 == S ? 0 : k + 1;
+    }
+  }
+};
+
+// Spatial terms of every lane's slots, 12 - |p - q|^2 log2(e) / sigma_s^2, -inf
+// outside the pixel's window and for padding patches.
+template <int R>
+__device__ __forceinline__ void spatial_table(float* t, float ks2) {
+  using G = HGeom<R>;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int e = wave; e < G::NI * 8; e += 4 * Sched<R>::S) {
+    const int i = e >> 3, s = e & 7;
+    const int p = 4 * i + lk, rp = p / G::NCQ, cq = p - rp * G::NCQ;
+    const int ty = 2 * rp + (s >> 2) - (li >> 2) - R, tx = 4 * cq + (s & 3) - (li & 3) - R;
+    const bool in = p < G::NP && ty >= -R && ty <= R && tx >= -R && tx <= R;
+    t[(i * 64 + lane) * 8 + s] =
+        in ? fmaf(-(float)(ty * ty + tx * tx), ks2, kLog2WScale) : -__builtin_inff();
+  }
+}
+
+// Every sweep of one segment.
+template <int R, int MODE>
+__device__ __forceinline__ void segment(const View& v, int x0, int b0, int len, float* lds) {
+  const int nblk = (v.D + 15) / 16, nb = sweep_blocks(nblk);
+  for (int q0 = 0; q0 < nblk; q0 += nb) {
+    // the state a sweep leaves is read by the next one in the same wave (block
+    // rows and lanes keep their waves): program order is enough.  A fence of
+    // the whole device here cost 56 us a segment.
+    if (nb == 4) Worker<R, MODE, 4>(lds).sweep(v, x0, b0, len, q0, nblk);
+    else if (nb == 3) Worker<R, MODE, 3>(lds).sweep(v, x0, b0, len, q0, nblk);
+    else if (nb == 2) Worker<R, MODE, 2>(lds).sweep(v, x0, b0, len, q0, nblk);
+    else Worker<R, MODE, 1>(lds).sweep(v, x0, b0, len, q0, nblk);
+  }
+}
+
+template <int R, int MODE, int QUEUE>
+__global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args a) {
+  extern __shared__ float lds[];
+  float* tab = lds + Lds<R>::tab / 4;
+  if constexpr (QUEUE) {
+    // round k of G workgroups covers entries [k G, (k + 1) G); workgroup b (XCD
+    // b % 8) takes entry k G + (b % 8) G / 8 + b / 8, so that each XCD works on
+    // a contiguous run of the list (neighbouring strips, longest first)
+    const int G = (int)gridDim.x, b = (int)blockIdx.x;
+    const int at = G % 8 == 0 ? (b % 8) * (G / 8) + b / 8 : b;
+    float ks2 = __builtin_nanf("");
+    for (int s = at; s < a.n; s += G) {
+      const Seg e = a.segs[s];
+      const View v = bilh::view_of(a.descs[e.desc]);
+      // the pairs of a launch may differ in sigma_s; the last sweep's final
+      // barrier is behind every read of the table, a sweep's first one ahead
+      if (v.ks2 != ks2) {
+        ks2 = v.ks2;
+        spatial_table<R>(tab, ks2);
+      }
+      segment<R, MODE>(v, e.x0, e.b0, e.len, lds);
+    }
+  } else {
+    spatial_table<R>(tab, a.v[0].ks2);
+    // banded: XCD x = b % 8 owns a band of strips; its workgroups run adjacent
+    // strips of one vertical range at a time, whose shared halo columns meet
+    // in its L2
+    int c0 = 0, bc = a.tx, me = blockIdx.x, step = gridDim.x;
+    if (a.banded) {
+      const int bw = (a.tx + 7) / 8;
+      c0 = (blockIdx.x % 8) * bw;
+      bc = a.tx - c0 < bw ? (a.tx - c0 > 0 ? a.tx - c0 : 0) : bw;
+      me = blockIdx.x / 8;
+      step = gridDim.x / 8;
+    }
+    const int per = bc * a.nseg, n = a.nvol * per;
+    for (int s = me; s < n; s += step) {
+      const int vol = s >= per ? 1 : 0, rem = s - vol * per;
+      const int seg = rem / bc, strip = c0 + rem - seg * bc;
+      const int b0 = seg * a.len;
+      const int len = min(a.len, a.br - b0);
+      if (len > 0) segment<R, MODE>(a.v[vol], strip * kTW, b0, len, lds);   // uniform
+    }
+  }
+}
+
+template <int R, int MODE, int QUEUE>
+hipError_t set_lds_attr() {
+  static bool done = false;
+  if (!done) {
+    hipError_t e = hipFuncSetAttribute((const void*)agg_stream_kernel<R, MODE, QUEUE>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)Lds<R>::bytes);
+    if (e != hipSuccess) return e;
+    done = true;
+  }
+  return hipSuccess;
+}
+
+// Cut of nvol volumes of tx strips x br block rows over cus workgroups.  A
+// segment costs its block rows plus the phases in which its groups fill and
+// drain and its first row pairs arrive (S + 2); the cut with the smallest
+// number of rounds x segment cost is taken, banded over the XCDs (strips that
+// share halo columns on one L2) unless that costs more than 8 % (few strips).
+// At 1280x720 both volumes of 80 strips take 3 segments a strip, 60 of an
+// XCD's 32 workgroups' two rounds.
+inline void cut_strips(int tx, int br, int nvol, int S, int cus, int& nseg, int& banded) {
+  double best[2] = {1e30, 1e30};
+  int at[2] = {1, 1};
+  for (int k = 1; k <= br && k <= 64; ++k) {
+    const int len = (br + k - 1) / k;
+    if (k > 1 && len == (br + k - 2) / (k - 1)) continue;       // no shorter than with k - 1
+    for (int b = 0; b < 2; ++b) {
+      if (b && (cus % 8 || cus < 8)) continue;
+      const long items = (long)nvol * (b ? (tx + 7) / 8 : tx) * k, w = b ? cus / 8 : cus;
+      const double cost = (double)((items + w - 1) / w) * (len + S + 2);
+      if (cost < best[b]) { best[b] = cost; at[b] = k; }
+    }
+  }
+  banded = best[1] <= 1.08 * best[0] ? 1 : 0;
+  nseg = at[banded];
+}
+
+// One or two volumes of a pair (the same size, radius and sigmas).
+template <int R, int MODE>
+hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s) {
+  Args a{};
+  for (int k = 0; k < nvol; ++k) {
+    const BilPair& b = p[k];
+    if (!b.h2 || b.h2_pitch < bilh::h2_pitch_for<R>(b.W) || (b.h2_pitch & 7) ||
+        b.h2_plane < 16 * (int64_t)h2_rows(R, b.H) * b.h2_pitch || b.W != p[0].W ||
+        b.H != p[0].H || b.D != p[0].D || (b.D > 16 * kMaxNB && !b.state))
+      return hipErrorInvalidValue;
+    a.v[k] = bilh::view_of(b);
+  }
+  hipError_t e = set_lds_attr<R, MODE, 0>();
+  if (e != hipSuccess) return e;
+  const int c = bilm::cu_count_of_current_device(), cus = c > 0 ? c : 256;
+  a.nvol = nvol;
+  a.tx = (p[0].W + kTW - 1) / kTW;
+  a.br = (p[0].H + 3) / 4;
+  cut_strips(a.tx, a.br, nvol, Sched<R>::S, cus, a.nseg, a.banded);
+  a.len = (a.br + a.nseg - 1) / a.nseg;
+  const int grid = a.banded ? cus : std::min(cus, nvol * a.tx * a.nseg);
+  hipLaunchKernelGGL((agg_stream_kernel<R, MODE, 0>), dim3(grid), dim3(256 * Sched<R>::S),
+                     Lds<R>::bytes, s, a);
+  return hipGetLastError();
+}
+
+template <int R>
+hipError_t launch_args(const Plan& P, const BilArgs* a, int nvol, int mode, hipStream_t s) {
+  if (nvol < 1 || nvol > 2 || (mode != 1 && mode != 2)) return hipErrorInvalidValue;
+  BilPair p[2];
+  for (int k = 0; k < nvol; ++k) p[k] = bil::make_pair(P, a[k]);
+  return mode == 2 ? launch_pair<R, 2>(p, nvol, s) : launch_pair<R, 1>(p, nvol, s);
+}
+
+// n segments over many volumes (descs, segs: device arrays).
+template <int R>
+hipError_t launch_queue(const BilPair* descs, const Seg* segs, int n, int n_groups,
+                        hipStream_t s) {
+  hipError_t e = set_lds_attr<R, 1, 1>();
+  if (e != hipSuccess) return e;
+  Args a{};
+  a.descs = descs;
+  a.segs = segs;
+  a.n = n;
+  hipLaunchKernelGGL((agg_stream_kernel<R, 1, 1>), dim3(n_groups), dim3(256 * Sched<R>::S),
+                     Lds<R>::bytes, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace bils
+}  // namespace stereo

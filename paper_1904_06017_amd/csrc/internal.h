@@ -31,7 +31,7 @@ struct Plan {
   int stats_w;        // block-statistics map width: columns [-r, W + r)
   int cw;             // row pitch of the internal cost volume (>= W + D - 1),
                       // stored level-quad-interleaved: [ceil(D/4)][H][cw] float4
-  size_t off_tarw, off_stats, off_cvol, off_dT, off_dsub, off_road;
+  size_t off_tarw, off_stats, off_cvol, off_dT, off_dsub, off_state, off_road;
   size_t ws_bytes;
   int road_blocks;    // partial-sum blocks of the road moments
   // tuning (stereo_plan_set_tuning): levels per aggregation pass by guide type
@@ -44,6 +44,7 @@ struct Plan {
   int agg_engine = 2;   // fused aggregation + selection: 2 matrix cores with split
                         // FP16 operands, 1 matrix cores with FP32 operands, 0 vector ALU
   int h2_pitch = 0;     // row pitch (halves) of the split-FP16 volumes
+  int64_t h2_plane = 0; // halves per block part of them
   size_t h2_tar_off = 0;  // byte offset of the target-anchored one in the volume region
   // differentiable form (F32 plans): levels recomputed per backward tile and
   // the workspace regions it uses (offsets from the workspace base)
@@ -100,8 +101,8 @@ hipError_t launch_block_stats(const Plan& P, const void* img, stereo_dtype dt,
 // quad = 1: level-quad-interleaved float4 layout [levels/4][H][out_pitch]
 // (out_slice, out_pitch in float4 units; d_first a multiple of 4).  quad = 2:
 // split-FP16 volume of the anchor (see BilArgs::h2), out_pitch = stored
-// columns (a multiple of 8), out_slice = 16 H out_pitch, out_w >= out_pitch,
-// pad = column shift (the window radius R), d_first a multiple of 16.
+// columns (a multiple of 8), out_slice = 16 h2_rows(R, H) out_pitch, out_w >=
+// out_pitch, pad = column shift (the window radius R), d_first a multiple of 16.
 // quad = 3 (FP32 images): both the split-FP16 volume in C (as quad 2) and
 // the planar FP32 volume [levels][H][W] in C2, from one pass.  quad = 4:
 // the reference-anchored split volume in C and the target-anchored one in
@@ -139,14 +140,18 @@ struct BilArgs {
   float* Wp;          // mode 5 (nullable): sum_q w(p, q)
   int d_first;        // modes 5, 6: level of the tile's first slice
   // split-FP16 volume of the matrix-core engine with FP16 operands (modes 1,
-  // 2; used when non-NULL), in blocks of 16 levels: level d of column x at
-  // h2[(2 (d >> 4) + part) * h2_plane + 16 y h2_pitch + 64 (s >> 2) +
-  // 4 (d & 15) + (s & 3)], s = x + R; part 0 = FP16 value c_hi of the cost,
-  // part 1 = FP16 value of c - c_hi; columns outside [0, W) and the last
-  // block's levels past D hold zeros
+  // 2; used when non-NULL), in blocks of 16 levels: level d of column x, row y
+  // at h2[(2 (d >> 4) + part) * h2_plane + 32 (t >> 1) h2_pitch + 128 (s >> 2)
+  // + 8 (d & 15) + 4 (t & 1) + (s & 3)], s = x + R, t = y + (R & 1); part 0 =
+  // FP16 value c_hi of the cost, part 1 = FP16 value of c - c_hi; columns
+  // outside [0, W), rows outside [0, H) and the last block's levels past D
+  // hold zeros
   const uint16_t* h2;
-  int64_t h2_plane;   // halves per block part (>= 16 H h2_pitch)
+  int64_t h2_plane;   // halves per block part (>= 16 h2_rows(R, H) h2_pitch)
   int h2_pitch;       // columns per stored row (a multiple of 8)
+  // ranges above 64 levels: selection state kept between the sweeps of 64
+  // levels, h2_state_floats per pixel (16-byte aligned)
+  float* state;
   // backward passes on the split-FP16 matrix cores: max |g'| (float bits),
   // and pass 1's output volume (C' scaled, split; pitch and plane of h2)
   const unsigned int* gmax;
@@ -161,6 +166,19 @@ struct BilArgs {
 // E out = dC = sum_q w C, and A2), float guides only.
 hipError_t launch_bilateral(const Plan& P, const BilArgs& a, int mode,
                             hipStream_t s);
+// Modes 1 and 2 on the split-FP16 matrix cores, n = 1 or 2 volumes of a pair
+// (a[k].h2 set; the same plan) in one launch.
+hipError_t launch_bilateral_h2(const Plan& P, const BilArgs* a, int n, int mode, hipStream_t s);
+// Floats per pixel of BilArgs::state for mode 1 / 2 (0 up to 64 levels).
+inline int h2_state_floats(int D, int mode) { return D <= 64 ? 0 : mode == 2 ? 16 : 4; }
+// The same, mode 1, over segments of many volumes: descs = device array of
+// descriptors (bilateral_pair), segs = n device Seg entries, all of radius R.
+struct Seg {                  // block rows [b0, b0 + len) of the strip at column x0
+  int desc, x0, b0, len;
+};
+constexpr int kSegW = 16, kSegRow = 4;   // strip columns, rows of a block row
+hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n,
+                                     int n_groups, hipStream_t s);
 
 // Backward of the soft-argmin head on the split-FP16 matrix cores, for one
 // level tile (radius R <= kBwd16MaxR, float guide, d_first a multiple of 16):
@@ -169,18 +187,21 @@ hipError_t launch_bilateral(const Plan& P, const BilArgs& a, int mode,
 // max |g'| as float bits), split into a.h2_out (same layout), with aP, A1,
 // Wp as mode 5; pass 2 reads that volume (a.h2) and writes dC planar
 // [levels][H][W] to a.E and A2 as mode 6 (a.cpix: the tile's costs, planar).
-// The stored columns of a.h2_out outside the image are not written: zero
-// them first (launch_h2_pad_zero).
+// The stored columns and rows of a.h2_out outside the image are not written:
+// zero them first (launch_h2_pad_zero).
 constexpr int kBwd16MaxR = 5;
 hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hipStream_t s);
-// Zeros in the stored columns outside [0, W) (all levels, both halves) of
-// the first nblk 16-level blocks of a split-FP16 volume at radius R.
+// Zeros in the stored columns outside [0, W) and rows outside [0, H) (all
+// levels, both halves) of the first nblk 16-level blocks of a split-FP16 volume at radius R.
 hipError_t launch_h2_pad_zero(uint16_t* h2, int64_t plane, int pitch, int W, int H, int R,
                               int nblk, hipStream_t s);
 
 // Row pitch (halves, a multiple of 8) of the split-FP16 volumes at window
 // radius R for width W: covers the halo columns of every 16-pixel tile.
 int h2_pitch(int R, int W);
+// Stored rows (whole pairs) of a split-FP16 volume: image row y is stored row
+// y + (R & 1), so that the window union of every 4-row block starts a pair.
+inline __host__ __device__ int h2_rows(int R, int H) { return (H + (R & 1) + 1) & ~1; }
 // Columns (and so blocks) of a batched NCC job: the extended range
 // [0, W + D - 1) of the quad volume or the stored row of a split-FP16 volume.
 inline int ncc_out_w(const Plan& P) {
@@ -192,7 +213,7 @@ inline int ncc_out_w(const Plan& P) {
 // pairs: pairs = device array of per-pair descriptors (bilateral_pair), tiles
 // = device int triples (pair, x0, y0), counter = device uint zeroed before the
 // launch.  All pairs of one launch share R, the guide type and `levels`.
-// engine 1 (matrix cores): tiles of kMfmaTileW x kMfmaTileH, one workgroup
+// engine 1 (FP32 matrix cores): tiles of kMfmaTileW x kMfmaTileH, one workgroup
 // per CU; engine 0 (vector ALU): tiles of kBilTileW x kBilTileH.
 hipError_t launch_bilateral_persistent(int engine, int R, stereo_dtype gdt, int levels, const void* pairs,
                                        const int* tiles, int n_tiles, unsigned int* counter,
@@ -229,17 +250,15 @@ struct StatsJob {           // grid: gx = ceil((W + 2r) / 64) x ceil(H / 16)
   const void* img; int64_t pitch; float* z; float* isd;
   int W, H, r, gx;
 };
-struct NccJob {             // grid: gx = ceil(out_w / 64) x gy = ceil(H / 32) x level blocks
+struct NccJob {             // grid: gx = ceil(out_w / 64) x gy = ceil(H / 8) x level blocks
   const void* ref; int64_t ref_pitch; const float* tarw;
   const float *zX, *isdX, *zY, *isdY;
-  float* C; int64_t out_pitch, out_slice;
-  int W, H, d_first, d_end, out_w, anchor, gx, gy;
-  int pad;                    // split-FP16 output (quad = 2, 4): column shift
-  float* C2;                  // quad = 4: the target-anchored volume (nullable)
-  // the kernel reaches C and C2 as byte offsets from the launch's base (a
-  // kernel argument, so the compiler knows the stores are global); c2_off
-  // < 0: no C2
-  int64_t c_off, c2_off;
+  int64_t out_pitch, out_slice;
+  int W, H, d_first, d_end, out_w, gx, gy;
+  // the kernel reaches the quad volume (quad = 1, anchor 0) as a byte offset
+  // from the launch's base (a kernel argument, so the compiler knows the
+  // stores are global)
+  int64_t c_off;
 };
 struct LrJob {              // grid: gx = ceil(W / 256) x H rows
   const int16_t* dR; const int16_t* dT; const float* dsub; uint8_t* valid; float* disp;
@@ -251,7 +270,7 @@ struct LrJob {              // grid: gx = ceil(W / 256) x H rows
 };
 int warp_job_blocks(const Plan& P);
 int stats_job_blocks(int W, int H, int r);
-int ncc_job_blocks(const Plan& P, int out_w, int d_first, int d_end, int dc, int quad);
+int ncc_job_blocks(const Plan& P, int out_w, int d_first, int d_end, int dc);
 // Columns a quad = 4 launch covers (its out_w): the stored row plus the
 // levels rounded up to 16, so that every target-anchored column is reached.
 int ncc_both_extent(int out_pitch, int d_first, int d_end);
@@ -260,19 +279,18 @@ WarpJob warp_job(const Plan& P, const void* tar, float* tar_w);
 StatsJob stats_job(const Plan& P, const void* img, int64_t pitch, float* z, float* isd);
 NccJob ncc_job(const Plan& P, const void* ref, const float* tar_w, const float* zX,
                const float* isdX, const float* zY, const float* isdY, float* C, int out_w,
-               int64_t out_pitch, int64_t out_slice, int anchor, int d_first, int d_end,
-               int quad, float* C2, const void* base);
+               int64_t out_pitch, int64_t out_slice, int d_first, int d_end, const void* base);
 LrJob lr_job(const Plan& P, const int16_t* dR, const int16_t* dT, const float* dsub,
              uint8_t* valid, float* disp);
 // jobs / first are device arrays; dt is the element type of the job images
-// (ref for the NCC); stats LDS is sized for max_r; quad as in launch_ncc.
+// (ref for the NCC); stats LDS is sized for max_r.
 hipError_t launch_warp_jobs(stereo_dtype dt, const WarpJob* jobs, const int* first, int n,
                             int blocks, hipStream_t s);
 hipError_t launch_stats_jobs(stereo_dtype dt, const StatsJob* jobs, const int* first, int n,
                              int blocks, int max_r, hipStream_t s);
 // dc: levels per workgroup (16, 32 or 64), the same for every job of the list
-// base: the allocation holding every job's C and C2 (their offsets)
-hipError_t launch_ncc_jobs(int r, stereo_dtype dt, int quad, int dc, const NccJob* jobs,
+// base: the allocation holding every job's volume (their offsets)
+hipError_t launch_ncc_jobs(int r, stereo_dtype dt, int dc, const NccJob* jobs,
                            const int* first, int n, int blocks, char* base, hipStream_t s);
 hipError_t launch_lr_jobs(const LrJob* jobs, const int* first, int n, int blocks,
                           hipStream_t s);
@@ -284,7 +302,7 @@ hipError_t launch_lr_jobs(const LrJob* jobs, const int* first, int n, int blocks
                              const float* isdY, float* C, int out_w, int64_t out_pitch,      \
                              int64_t out_slice, int anchor, int d_first, int d_end,          \
                              int quad, int pad, hipStream_t s, float* C2);                   \
-  hipError_t launch_ncc_jobs_r##N(stereo_dtype dt, int quad, int dc, const NccJob* jobs,     \
+  hipError_t launch_ncc_jobs_r##N(stereo_dtype dt, int dc, const NccJob* jobs,               \
                                   const int* first, int n, int blocks, char* base,          \
                                   hipStream_t s);
 STEREO_NCC_UNIT(1) STEREO_NCC_UNIT(2) STEREO_NCC_UNIT(3) STEREO_NCC_UNIT(4)

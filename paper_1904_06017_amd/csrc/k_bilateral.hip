@@ -19,6 +19,23 @@ hipError_t launch_bilateral_persistent_r7(int, stereo_dtype, int, const void*, c
 hipError_t launch_bilateral_r8(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bilateral_persistent_r8(int, stereo_dtype, int, const void*, const int*, int, unsigned int*, int, hipStream_t);
 
+hipError_t launch_bilateral_h2_r1(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r1(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r2(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r2(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r3(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r3(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r4(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r4(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r5(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r5(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r6(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r6(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r7(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r7(const void*, const Seg*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_r8(const Plan&, const BilArgs*, int, int, hipStream_t);
+hipError_t launch_bilateral_h2_queue_r8(const void*, const Seg*, int, int, hipStream_t);
+
 hipError_t launch_bwd16_r1(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bwd16_r2(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bwd16_r3(const Plan&, const BilArgs&, int, hipStream_t);
@@ -39,27 +56,31 @@ hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hip
 }
 
 namespace bilh {
-// Zeros in the pad columns of every row of the first blocks (both parts):
-// thread t of a row: pad column t / 16 (columns [0, R), then [W + R, pitch)),
-// level t % 16.
+// Zeros in the pad columns of every row, and in the rows outside the image,
+// of the first blocks (both parts).  Row blockIdx.y of the stored rows; thread
+// t: column t / 16 (of an image row: pad columns [0, R), then [W + R, pitch);
+// of a row outside: all), level t % 16.
 __global__ void __launch_bounds__(256) h2_pad_zero_kernel(uint16_t* __restrict__ h2,
-                                                          int64_t plane, int pitch, int W,
+                                                          int64_t plane, int pitch, int W, int H,
                                                           int R) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int npad = pitch - W;
-  if (t >= 16 * npad) return;
-  const int ci = t >> 4, l = t & 15;
-  const int c = ci < R ? ci : W + ci;
-  const int y = blockIdx.y, bp = blockIdx.z;   // bp = 2 block + part
-  h2[(int64_t)bp * plane + (int64_t)y * 16 * pitch + 64 * (c >> 2) + 4 * l + (c & 3)] = 0;
+  const int st = blockIdx.y, y = st - (R & 1), bp = blockIdx.z;   // bp = 2 block + part
+  const bool out = y < 0 || y >= H;
+  const int n = 16 * (out ? pitch : pitch - W);
+  for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) {
+    const int ci = t >> 4, l = t & 15;
+    const int c = out || ci < R ? ci : W + ci;
+    h2[(int64_t)bp * plane + (int64_t)(st >> 1) * 32 * pitch + 128 * (c >> 2) + 8 * l +
+       4 * (st & 1) + (c & 3)] = 0;
+  }
 }
 }  // namespace bilh
 
 hipError_t launch_h2_pad_zero(uint16_t* h2, int64_t plane, int pitch, int W, int H, int R,
                               int nblk, hipStream_t s) {
   if (!h2 || pitch < W + R || nblk <= 0) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((16 * (pitch - W) + 255) / 256), (unsigned)H, (unsigned)(2 * nblk));
-  hipLaunchKernelGGL(bilh::h2_pad_zero_kernel, grid, dim3(256), 0, s, h2, plane, pitch, W, R);
+  const dim3 grid((unsigned)((16 * (pitch - W) + 255) / 256), (unsigned)h2_rows(R, H),
+                  (unsigned)(2 * nblk));
+  hipLaunchKernelGGL(bilh::h2_pad_zero_kernel, grid, dim3(256), 0, s, h2, plane, pitch, W, H, R);
   return hipGetLastError();
 }
 
@@ -73,6 +94,35 @@ hipError_t launch_bilateral(const Plan& P, const BilArgs& a, int mode, hipStream
     case 6: return launch_bilateral_r6(P, a, mode, s);
     case 7: return launch_bilateral_r7(P, a, mode, s);
     case 8: return launch_bilateral_r8(P, a, mode, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_bilateral_h2(const Plan& P, const BilArgs* a, int n, int mode, hipStream_t s) {
+  switch (P.R) {
+    case 1: return launch_bilateral_h2_r1(P, a, n, mode, s);
+    case 2: return launch_bilateral_h2_r2(P, a, n, mode, s);
+    case 3: return launch_bilateral_h2_r3(P, a, n, mode, s);
+    case 4: return launch_bilateral_h2_r4(P, a, n, mode, s);
+    case 5: return launch_bilateral_h2_r5(P, a, n, mode, s);
+    case 6: return launch_bilateral_h2_r6(P, a, n, mode, s);
+    case 7: return launch_bilateral_h2_r7(P, a, n, mode, s);
+    case 8: return launch_bilateral_h2_r8(P, a, n, mode, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n,
+                                     int n_groups, hipStream_t s) {
+  switch (R) {
+    case 1: return launch_bilateral_h2_queue_r1(descs, segs, n, n_groups, s);
+    case 2: return launch_bilateral_h2_queue_r2(descs, segs, n, n_groups, s);
+    case 3: return launch_bilateral_h2_queue_r3(descs, segs, n, n_groups, s);
+    case 4: return launch_bilateral_h2_queue_r4(descs, segs, n, n_groups, s);
+    case 5: return launch_bilateral_h2_queue_r5(descs, segs, n, n_groups, s);
+    case 6: return launch_bilateral_h2_queue_r6(descs, segs, n, n_groups, s);
+    case 7: return launch_bilateral_h2_queue_r7(descs, segs, n, n_groups, s);
+    case 8: return launch_bilateral_h2_queue_r8(descs, segs, n, n_groups, s);
     default: return hipErrorInvalidValue;
   }
 }

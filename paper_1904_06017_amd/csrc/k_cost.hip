@@ -241,9 +241,8 @@ int warp_job_blocks(const Plan& P) { return ((P.W + 255) / 256) * P.H; }
 int stats_job_blocks(int W, int H, int r) {
   return ((W + 2 * r + ST_TX - 1) / ST_TX) * ((H + ST_TY - 1) / ST_TY);
 }
-int ncc_job_blocks(const Plan& P, int out_w, int d_first, int d_end, int dc, int quad) {
-  const int tx = quad == 4 ? NC_TX4 : NC_TX;
-  return ((out_w + tx - 1) / tx) * ((P.H + NC_TY - 1) / NC_TY) *
+int ncc_job_blocks(const Plan& P, int out_w, int d_first, int d_end, int dc) {
+  return ((out_w + NC_TX - 1) / NC_TX) * ((P.H + NC_TY - 1) / NC_TY) *
          ((d_end - d_first + dc - 1) / dc);
 }
 int ncc_both_extent(int out_pitch, int d_first, int d_end) {
@@ -271,19 +270,15 @@ StatsJob stats_job(const Plan& P, const void* img, int64_t pitch, float* z, floa
 
 NccJob ncc_job(const Plan& P, const void* ref, const float* tar_w, const float* zX,
                const float* isdX, const float* zY, const float* isdY, float* C, int out_w,
-               int64_t out_pitch, int64_t out_slice, int anchor, int d_first, int d_end,
-               int quad, float* C2, const void* base) {
+               int64_t out_pitch, int64_t out_slice, int d_first, int d_end, const void* base) {
   NccJob J{};
-  J.C2 = C2;
   J.c_off = reinterpret_cast<const char*>(C) - static_cast<const char*>(base);
-  J.c2_off = C2 ? reinterpret_cast<const char*>(C2) - static_cast<const char*>(base) : -1;
   J.ref = ref; J.ref_pitch = P.p.pitch_ref; J.tarw = tar_w;
   J.zX = zX; J.isdX = isdX; J.zY = zY; J.isdY = isdY;
-  J.C = C; J.out_pitch = out_pitch; J.out_slice = out_slice;
+  J.out_pitch = out_pitch; J.out_slice = out_slice;
   J.W = P.W; J.H = P.H; J.d_first = d_first; J.d_end = d_end < 0 ? P.D : d_end;
-  J.out_w = out_w; J.anchor = anchor;
-  const int tx = quad == 4 ? NC_TX4 : NC_TX;
-  J.gx = (out_w + tx - 1) / tx; J.gy = (P.H + NC_TY - 1) / NC_TY;
+  J.out_w = out_w;
+  J.gx = (out_w + NC_TX - 1) / NC_TX; J.gy = (P.H + NC_TY - 1) / NC_TY;
   return J;
 }
 
@@ -310,18 +305,18 @@ hipError_t launch_stats_jobs(stereo_dtype dt, const StatsJob* jobs, const int* f
 }
 
 
-hipError_t launch_ncc_jobs(int r, stereo_dtype dt, int quad, int dc, const NccJob* jobs,
+hipError_t launch_ncc_jobs(int r, stereo_dtype dt, int dc, const NccJob* jobs,
                            const int* first, int n, int blocks, char* base, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
   switch (r) {
-    case 1: return launch_ncc_jobs_r1(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 2: return launch_ncc_jobs_r2(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 3: return launch_ncc_jobs_r3(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 4: return launch_ncc_jobs_r4(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 5: return launch_ncc_jobs_r5(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 6: return launch_ncc_jobs_r6(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 7: return launch_ncc_jobs_r7(dt, quad, dc, jobs, first, n, blocks, base, s);
-    case 8: return launch_ncc_jobs_r8(dt, quad, dc, jobs, first, n, blocks, base, s);
+    case 1: return launch_ncc_jobs_r1(dt, dc, jobs, first, n, blocks, base, s);
+    case 2: return launch_ncc_jobs_r2(dt, dc, jobs, first, n, blocks, base, s);
+    case 3: return launch_ncc_jobs_r3(dt, dc, jobs, first, n, blocks, base, s);
+    case 4: return launch_ncc_jobs_r4(dt, dc, jobs, first, n, blocks, base, s);
+    case 5: return launch_ncc_jobs_r5(dt, dc, jobs, first, n, blocks, base, s);
+    case 6: return launch_ncc_jobs_r6(dt, dc, jobs, first, n, blocks, base, s);
+    case 7: return launch_ncc_jobs_r7(dt, dc, jobs, first, n, blocks, base, s);
+    case 8: return launch_ncc_jobs_r8(dt, dc, jobs, first, n, blocks, base, s);
     default: return hipErrorInvalidValue;
   }
 }

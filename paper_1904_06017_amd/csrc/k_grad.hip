@@ -905,7 +905,7 @@ stereo_status stereo_soft_forward(stereo_plan_t plan, const float* ref, const fl
   if (P.agg_engine == 2) {
     // split-FP16 reference-anchored volume for the FP16-operand matrix cores
     uint16_t* vR = at<uint16_t>(ws, P.off_cvol);
-    const int64_t plane = 16 * (int64_t)P.H * P.h2_pitch;
+    const int64_t plane = P.h2_plane;
     HIPC(launch_ncc(P, ref, tarw, m.zX, m.isdX, m.zY, m.isdY, reinterpret_cast<float*>(vR),
                     P.h2_pitch, P.h2_pitch, plane, 0, stream, 0, -1, 2, P.R), "ncc");
     a.h2 = vR;
@@ -927,7 +927,9 @@ stereo_status stereo_soft_forward(stereo_plan_t plan, const float* ref, const fl
   a.sm_dh = saved + 2 * HW;
   a.disp = disp_soft;
   a.plane[0] = plane[0]; a.plane[1] = plane[1]; a.plane[2] = plane[2];
-  HIPC(launch_bilateral(P, a, 2, stream), "aggregation + soft-argmin");
+  a.state = at<float>(ws, P.off_state);
+  HIPC(a.h2 ? launch_bilateral_h2(P, &a, 1, 2, stream) : launch_bilateral(P, a, 2, stream),
+       "aggregation + soft-argmin");
   return STEREO_OK;
 }
 
@@ -1030,7 +1032,7 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
            grad_disp, HW,
            reinterpret_cast<unsigned int*>(R_(GR_GMAX)));
     HIPC(launch_h2_pad_zero(at<uint16_t>(ws, P.off_cvol + P.h2_tar_off),
-                            16 * (int64_t)H * P.h2_pitch, P.h2_pitch, W, H, P.R, (DT + 15) / 16,
+                            P.h2_plane, P.h2_pitch, W, H, P.R, (DT + 15) / 16,
                             stream), "pad columns of C'");
   }
   for (int d0 = 0; d0 < D; d0 += DT) {
@@ -1042,7 +1044,7 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
       // pass 1 writes C' split for pass 2
       uint16_t* hC = at<uint16_t>(ws, P.off_cvol);
       uint16_t* hG = at<uint16_t>(ws, P.off_cvol + P.h2_tar_off);
-      const int64_t hplane = 16 * (int64_t)H * P.h2_pitch;
+      const int64_t hplane = P.h2_plane;
       HIPC(launch_ncc(P, ref, tarw, m.zX, m.isdX, m.zY, m.isdY, reinterpret_cast<float*>(hC),
                       P.h2_pitch, P.h2_pitch, hplane, 0, stream, d0, d0 + nl, 3, P.R, Ct),
            "ncc tile (split and planar)");

@@ -13,9 +13,9 @@ hipError_t launch_ncc_r5(const Plan& P, const void* ref, const float* tar_w, con
   return launch_ncc_r<5, float>(P, (const float*)ref, tar_w, zX, isdX, zY, isdY, C, out_w,
                                  out_pitch, out_slice, anchor, d_first, d_end, quad, pad, s, C2);
 }
-hipError_t launch_ncc_jobs_r5(stereo_dtype dt, int quad, int dc, const NccJob* jobs,
+hipError_t launch_ncc_jobs_r5(stereo_dtype dt, int dc, const NccJob* jobs,
                               const int* first, int n, int blocks, char* base, hipStream_t s) {
-  if (dt == STEREO_U8) return ncc_jobs_r<5, uint8_t>(quad, dc, jobs, first, n, blocks, base, s);
-  return ncc_jobs_r<5, float>(quad, dc, jobs, first, n, blocks, base, s);
+  if (dt == STEREO_U8) return ncc_jobs_r<5, uint8_t>(dc, jobs, first, n, blocks, base, s);
+  return ncc_jobs_r<5, float>(dc, jobs, first, n, blocks, base, s);
 }
 }  // namespace stereo

@@ -64,24 +64,29 @@ struct NccGeom {
 // inside the last quad are written as 0), QUAD = 0 the planar layout
 // [levels][H][pitch].  QUAD = 2 writes the split-FP16 volumes of the
 // FP16-operand matrix-core aggregation (anchor 0 over the extended columns,
-// d_first = 0): blocks of 16 levels, each [part][H][pitch / 4 column quads]
-// [16 levels][4 columns] halves, i.e. level d of stored column s = x + pad at
-// ((2 (d >> 4) + part) H + y) 16 pitch + 64 (s >> 2) + 4 (d & 15) + (s & 3),
-// out_slice = 16 H pitch, out_pitch = pitch; part 0 = FP16 rounding of the
-// cost, part 1 = FP16 rounding of the remainder; the anchor decides which
+// d_first = 0): blocks of 16 levels, each [part][row pairs][pitch / 4 column
+// quads][16 levels][2 rows][4 columns] halves, i.e. level d of stored column
+// s = x + pad, stored row t = y + (pad & 1) at (2 (d >> 4) + part) out_slice +
+// 32 (t >> 1) pitch + 128 (s >> 2) + 8 (d & 15) + 4 (t & 1) + (s & 3),
+// out_slice = 16 h2_rows pitch, out_pitch = pitch; part 0 = FP16 rounding of
+// the cost, part 1 = FP16 rounding of the remainder; the anchor decides which
 // volume (0: reference-anchored, 1: target-anchored).  The tiles start pad
-// columns left of their 64-column boundary, so a lane quad is a stored column
-// quad and, after a transpose within the quad, each lane writes 4 columns of
-// one level as 8 bytes; the grid's columns cover the stored row
-// (out_w >= out_pitch), columns outside [0, W) and the last block's levels at
-// or past d_end are written as zeros.  QUAD = 4 writes both anchors' split
+// columns left of their 64-column boundary and pad & 1 rows above their
+// 8-row boundary, so a lane quad is a stored column quad, a tile holds whole
+// row pairs and, after a transpose within the quad, each lane writes 4 columns
+// of both rows of a pair of one level as 16 bytes (a lane quad 64 contiguous
+// bytes; writing each row on its own, 8 bytes a lane, the launch of both
+// volumes at 1280x720, 64 levels, r = 3 took 0.111 against 0.104 ms);
+// the grid covers the stored rows and columns (out_w >= out_pitch), columns
+// and rows outside the image and the last block's levels at or past d_end are
+// written as zeros.  QUAD = 4 writes both anchors' split
 // volumes from one pass (the target-anchored one to C2 when non-NULL): the
 // cost of reference column x at level d is also the target-anchored cost of
 // column m = x - d, the same two blocks and the same products.  Tiles step
 // by NC_TX4 = 60 columns; lane x + k holds level d + k of target column m,
 // so three lane shifts (level k from k lanes to the right) line a quad of
 // lanes up with a stored column quad of that volume, after which the same
-// transpose gives 8-byte stores.  The last quad of lanes only feeds the
+// transpose gives the same stores.  The last quad of lanes only feeds the
 // shifts.  The grid covers x < out_w = stored row + the 16-rounded levels,
 // so that every target column, pads included, is written at every level.
 constexpr int NC_TX4 = 60;
@@ -189,7 +194,8 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   // split-FP16 output: the tile starts pad columns left of 64 bx, so that
   // lane l writes stored column 64 bx + l and a lane quad is a column quad
   const int x0 = QUAD == 4 ? bx * NC_TX4 - pad : bx * NC_TX - (QUAD >= 2 ? pad : 0);
-  const int y0 = by * NC_TY;
+  const int rsh = QUAD >= 2 ? pad & 1 : 0;           // row shift of the stored volume
+  const int y0 = by * NC_TY - rsh;
   const int d0 = d_first + bz * DC;
   const int SW = W + 2 * r;
   // image column of A[.][0] and B[.][0]
@@ -224,7 +230,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   // level offset boff reads for lane c - boff
   ncc_stage<NC_TY * G::ZW, NT>(tid, [&](int i) {
     const int t = i / G::ZW, c = i - t * G::ZW;
-    const int64_t rowo = (int64_t)min(y0 + t, H - 1) * SW;
+    const int64_t rowo = (int64_t)min(max(y0 + t, 0), H - 1) * SW;
     const int cb = min(max(zxo + c, -r), W - 1 + r) + r;
     return make_float2(gld(zm + rowo + cb), gld(im + rowo + cb));
   }, [&](int i, float2 v) { Zs[i] = v.x; Is[i] = v.y; });
@@ -233,7 +239,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   // rows' stores)
   ncc_stage<NC_TY * NC_TX, NT>(tid, [&](int i) {
     const int t = i / NC_TX, c = i - t * NC_TX;
-    const int64_t rowo = (int64_t)min(y0 + t, H - 1) * SW;
+    const int64_t rowo = (int64_t)min(max(y0 + t, 0), H - 1) * SW;
     const int cb = min(max(x0 + c, -r), W - 1 + r) + r;
     return make_float2(gld(za + rowo + cb), gld(ia + rowo + cb));
   }, [&](int i, float2 v) { ZA[i] = v.x; IA[i] = v.y * inv_n; });
@@ -255,6 +261,12 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
 #pragma unroll
     for (int i = 0; i < K; ++i) ring[k][i] = 0.0f;
 
+  // split-FP16 output: the first row of the pair being formed (its halves hi
+  // and lo of the reference- and target-anchored volume), kept until the
+  // second; the row loop is unrolled so that a row's place in its pair is static
+  uint2 v0h{}, v0l{}, u0h{}, u0l{};
+  const int rows = QUAD >= 2 ? (H + rsh + 1) & ~1 : H;   // stored rows
+#pragma unroll (QUAD >= 2 ? G::ROWS : 1)
   for (int yb = 0; yb < G::ROWS; yb += K) {
 #pragma unroll
     for (int s = 0; s < K; ++s) {
@@ -277,7 +289,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
           ring[k][s] = h;
         }
         const int y = y0 + yy - 2 * r;        // output row completed by this input row
-        if (yy >= 2 * r && y < H &&
+        if (yy >= 2 * r && (QUAD >= 2 ? y + rsh < rows : y < H) &&
             (QUAD == 4 ? true : QUAD >= 2 ? x + pad < out_pitch : x < out_w)) {
           const float zA = ZA[(yy - 2 * r) * NC_TX + lane];
           const float iA = IA[(yy - 2 * r) * NC_TX + lane];
@@ -297,7 +309,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
             cq[k] = fmaf(-S * iA, iB, fmaf(zA, zB, 1.0f));
             if (!QUAD)
               C[(int64_t)(d - d_first) * out_slice + (int64_t)y * out_pitch + x] = cq[k];
-            if (QUAD == 3 && x >= 0 && x < W)      // and the planar copy [level][H][W]
+            if (QUAD == 3 && x >= 0 && x < W && y >= 0 && y < H)   // and the planar copy [level][H][W]
               C2[((int64_t)(d - d_first) * H + y) * W + x] = cq[k];
           }
           if (QUAD == 1) {
@@ -309,10 +321,12 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
           if (QUAD >= 2) {
             // this wave's 4 levels of the lane quad's 4 columns, transposed so
             // that lane c of the quad holds level 4 wave + c of all 4 columns;
-            // columns outside the image and levels past d_end are zeros
+            // columns and rows outside the image and levels past d_end are zeros
+            const bool second = (yy - 2 * r) & 1;
+            const bool yin = y >= 0 && y < H;
             float v[NC_DW];
 #pragma unroll
-            for (int k = 0; k < NC_DW; ++k) v[k] = (x >= 0 && x < W) ? cq[k] : 0.0f;
+            for (int k = 0; k < NC_DW; ++k) v[k] = (yin && x >= 0 && x < W) ? cq[k] : 0.0f;
             // the target-anchored copy (QUAD 4): level k from lane + k, all
             // for target column m = x - (first level of the wave)
             const int db = d0 + wave * NC_DW;
@@ -322,35 +336,42 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
               for (int k = 0; k < NC_DW; ++k) u[k] = k ? __shfl_down(cq[k], k, 64) : cq[k];
               const int m = x - db;
 #pragma unroll
-              for (int k = 0; k < NC_DW; ++k) u[k] = (m >= 0 && m < W) ? u[k] : 0.0f;
+              for (int k = 0; k < NC_DW; ++k) u[k] = (yin && m >= 0 && m < W) ? u[k] : 0.0f;
             }
             quad_transpose4(v);
             const int dl = db + (lane & 3);
-            const bool full = QUAD != 4 || lane < NC_TX4;
-            if (dl < ((d_end + 15) & ~15) && full) {
-              // stored column quad of row y, level dl
-              const int sq = (QUAD == 4 ? NC_TX4 / 4 : 16) * bx + (lane >> 2);
-              if (QUAD != 4 || 4 * sq < out_pitch) {
-                uint2 hi, lo;
-                split4_f16(v, hi, lo);
-                const int64_t off = (int64_t)(2 * ((dl - d_first) >> 4)) * out_slice +
-                                    (int64_t)y * 16 * out_pitch + 64 * sq + 4 * (dl & 15);
-                *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(C) + off) = hi;
-                *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(C) + out_slice + off) = lo;
+            const bool full = (QUAD != 4 || lane < NC_TX4) && dl < ((d_end + 15) & ~15);
+            // block of level dl, row pair of row y
+            const int64_t off = (int64_t)(2 * ((dl - d_first) >> 4)) * out_slice +
+                                (int64_t)((y + rsh) >> 1) * 32 * out_pitch + 8 * (dl & 15);
+            uint2 hi, lo;
+            split4_f16(v, hi, lo);
+            if (second) {
+              const int sq = (QUAD == 4 ? NC_TX4 / 4 : 16) * bx + (lane >> 2);  // column quad
+              if (full && (QUAD != 4 || 4 * sq < out_pitch)) {
+                _Float16* o = reinterpret_cast<_Float16*>(C) + off + 128 * sq;
+                *reinterpret_cast<uint4*>(o) = make_uint4(v0h.x, v0h.y, hi.x, hi.y);
+                *reinterpret_cast<uint4*>(o + out_slice) = make_uint4(v0l.x, v0l.y, lo.x, lo.y);
               }
+            } else {
+              v0h = hi;
+              v0l = lo;
             }
             if (QUAD == 4 && C2) {
               quad_transpose4(u);
-              // target-anchored stored column quad: x0 + pad = 60 bx and the
-              // wave's first level are multiples of 4
-              const int s1 = NC_TX4 * bx + 4 * (lane >> 2) - db;
-              if (dl < ((d_end + 15) & ~15) && full && s1 >= 0 && s1 + 4 <= out_pitch) {
-                uint2 hi, lo;
-                split4_f16(u, hi, lo);
-                const int64_t off = (int64_t)(2 * ((dl - d_first) >> 4)) * out_slice +
-                                    (int64_t)y * 16 * out_pitch + 16 * s1 + 4 * (dl & 15);
-                *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(C2) + off) = hi;
-                *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(C2) + out_slice + off) = lo;
+              split4_f16(u, hi, lo);
+              if (second) {
+                // target-anchored stored column quad: x0 + pad = 60 bx and the
+                // wave's first level are multiples of 4
+                const int s1 = NC_TX4 * bx + 4 * (lane >> 2) - db;
+                if (full && s1 >= 0 && s1 + 4 <= out_pitch) {
+                  _Float16* o = reinterpret_cast<_Float16*>(C2) + off + 32 * s1;
+                  *reinterpret_cast<uint4*>(o) = make_uint4(u0h.x, u0h.y, hi.x, hi.y);
+                  *reinterpret_cast<uint4*>(o + out_slice) = make_uint4(u0l.x, u0l.y, lo.x, lo.y);
+                }
+              } else {
+                u0h = hi;
+                u0l = lo;
               }
             }
           }
@@ -410,7 +431,7 @@ __device__ __forceinline__ int job_of(const int* __restrict__ first, int n, int 
   return cnt - 1;
 }
 
-template <int r, typename T, int QUAD, int DC>
+template <int r, typename T, int DC>
 __global__ void __launch_bounds__(16 * DC)
 ncc_jobs_kernel(const NccJob* __restrict__ jobs, const int* __restrict__ first, int n,
                 char* __restrict__ base) {
@@ -420,11 +441,10 @@ ncc_jobs_kernel(const NccJob* __restrict__ jobs, const int* __restrict__ first, 
   const int l = blockIdx.x - first[j];
   const int gxy = J.gx * J.gy;
   const int bz = l / gxy, rem = l - bz * gxy;
-  float* C = reinterpret_cast<float*>(base + J.c_off);
-  float* C2 = J.c2_off >= 0 ? reinterpret_cast<float*>(base + J.c2_off) : nullptr;
-  ncc_body<r, T, QUAD, DC>(static_cast<const T*>(J.ref), J.ref_pitch, J.tarw, J.W, J.H, J.d_first,
-                       J.d_end, J.zX, J.isdX, J.zY, J.isdY, C, J.out_w, J.out_pitch,
-                       J.out_slice, J.anchor, J.pad, sm, rem % J.gx, rem / J.gx, bz, C2);
+  ncc_body<r, T, 1, DC>(static_cast<const T*>(J.ref), J.ref_pitch, J.tarw, J.W, J.H, J.d_first,
+                        J.d_end, J.zX, J.isdX, J.zY, J.isdY,
+                        reinterpret_cast<float*>(base + J.c_off), J.out_w, J.out_pitch,
+                        J.out_slice, 0, 0, sm, rem % J.gx, rem / J.gx, bz);
 }
 
 // Dynamic LDS above the 64 KB default (large radii at 64 levels), set once
@@ -434,7 +454,7 @@ hipError_t ncc_allow_lds() {
   static bool done = false;
   constexpr size_t bytes = NccGeom<r, DC>::lds_bytes;
   if (!done && bytes > 64 * 1024) {
-    const void* k = JOBS ? (const void*)ncc_jobs_kernel<r, T, QUAD, DC>
+    const void* k = JOBS ? (const void*)ncc_jobs_kernel<r, T, DC>
                          : (const void*)ncc_kernel<r, T, QUAD, DC>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
@@ -449,7 +469,8 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
                           int out_w, int64_t out_pitch, int64_t out_slice, int anchor,
                           int d_first, int d_end, int quad, int pad,
                           hipStream_t s, float* C2) {
-  dim3 grid((out_w + NC_TX - 1) / NC_TX, (P.H + NC_TY - 1) / NC_TY,
+  const int rows = quad >= 2 ? P.H + (pad & 1) : P.H;      // rows from the first tile's origin
+  dim3 grid((out_w + NC_TX - 1) / NC_TX, (rows + NC_TY - 1) / NC_TY,
             (d_end - d_first + DC - 1) / DC);
   if (quad == 4) {
     // both anchors' split volumes (C, and C2 when non-NULL)
@@ -528,33 +549,21 @@ hipError_t launch_ncc_r(const Plan& P, const T* ref, const float* tar_w, const f
 
 
 template <int r, typename T, int DC>
-hipError_t ncc_jobs_rdc(int quad, const NccJob* jobs, const int* first, int n, int blocks,
-                        char* base, hipStream_t s) {
-  hipError_t e = quad == 4 ? ncc_allow_lds<r, T, 4, DC, 1>()
-                 : quad == 2 ? ncc_allow_lds<r, T, 2, DC, 1>()
-                 : quad ? ncc_allow_lds<r, T, 1, DC, 1>() : ncc_allow_lds<r, T, 0, DC, 1>();
+hipError_t ncc_jobs_rdc(const NccJob* jobs, const int* first, int n, int blocks, char* base,
+                        hipStream_t s) {
+  hipError_t e = ncc_allow_lds<r, T, 1, DC, 1>();
   if (e != hipSuccess) return e;
-  if (quad == 4)
-    hipLaunchKernelGGL((ncc_jobs_kernel<r, T, 4, DC>), dim3(blocks), dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
-  else if (quad == 2)
-    hipLaunchKernelGGL((ncc_jobs_kernel<r, T, 2, DC>), dim3(blocks), dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
-  else if (quad)
-    hipLaunchKernelGGL((ncc_jobs_kernel<r, T, 1, DC>), dim3(blocks), dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
-  else
-    hipLaunchKernelGGL((ncc_jobs_kernel<r, T, 0, DC>), dim3(blocks), dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
+  hipLaunchKernelGGL((ncc_jobs_kernel<r, T, DC>), dim3(blocks), dim3(16 * DC),
+                     (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
   return hipGetLastError();
 }
 template <int r, typename T>
-hipError_t ncc_jobs_r(int quad, int dc, const NccJob* jobs, const int* first, int n, int blocks,
-                      char* base, hipStream_t s) {
+hipError_t ncc_jobs_r(int dc, const NccJob* jobs, const int* first, int n, int blocks, char* base,
+                      hipStream_t s) {
   switch (dc) {
-    case 64: return ncc_jobs_rdc<r, T, 64>(quad, jobs, first, n, blocks, base, s);
-    case 32: return ncc_jobs_rdc<r, T, 32>(quad, jobs, first, n, blocks, base, s);
-    default: return ncc_jobs_rdc<r, T, 16>(quad, jobs, first, n, blocks, base, s);
+    case 64: return ncc_jobs_rdc<r, T, 64>(jobs, first, n, blocks, base, s);
+    case 32: return ncc_jobs_rdc<r, T, 32>(jobs, first, n, blocks, base, s);
+    default: return ncc_jobs_rdc<r, T, 16>(jobs, first, n, blocks, base, s);
   }
 }
 

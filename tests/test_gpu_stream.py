@@ -1,0 +1,88 @@
+"""The streamed split-FP16 aggregation at the sizes where its cuts fall: strip
+and block-row remainders, level blocks and sweeps (16 levels each, 64 per
+sweep), every window radius, against the FP64 oracle; both volumes in one
+launch against one launch per volume; the soft-argmin over several sweeps."""
+import ctypes
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+from scipy import ndimage
+
+import oracle.soft as SO
+import oracle.stereo as OS
+from synth import workload
+from tests import parity_rules as PR
+
+pytestmark = pytest.mark.gpu
+api = pytest.importorskip("paper_1904_06017_amd.api")
+
+# (R, width, height, levels): one pixel and one level either side of a strip
+# (16 columns), a block row (4 rows), a level block and a sweep
+SIZES = [(1, 16, 4, 3), (1, 33, 9, 17), (2, 47, 13, 16), (2, 90, 30, 65), (3, 64, 12, 64),
+         (3, 95, 31, 40), (4, 49, 27, 33), (4, 17, 70, 96), (5, 130, 41, 128), (5, 31, 6, 30),
+         (6, 81, 18, 66), (7, 112, 45, 64), (7, 97, 23, 129), (8, 65, 50, 48), (8, 50, 21, 81)]
+
+
+def _pair(R, W, H, D, dtype):
+    rng = np.random.Generator(np.random.PCG64(1000 * R + W))
+    t = 128.0 + 6.0 * ndimage.gaussian_filter(rng.normal(0.0, 20.0, (H, W + D)), 1.0)
+    ref, tar = t[:, :W], t[:, D // 3:D // 3 + W]
+    if dtype == "u8":
+        return (np.clip(np.rint(x), 0, 255).astype(np.uint8) for x in (ref, tar))
+    return (np.ascontiguousarray(x, np.float32) for x in (ref, tar))
+
+
+def _workload(R, W, H, D, dtype, **kw):
+    return replace(workload("c1"), name="edge", width=W, height=H, num_disp=D, dtype=dtype,
+                   bil_radius=R, sigma_s=0.6 * R + 0.7, sigma_r=12.0, ncc_radius=2, **kw)
+
+
+def _host(x):
+    torch.cuda.synchronize()
+    return x.cpu().numpy()
+
+
+@pytest.mark.parametrize("R,W,H,D", SIZES)
+def test_match_at_cut_edges(R, W, H, D):
+    dtype = "u8" if R % 2 else "f32"
+    w = _workload(R, W, H, D, dtype, perspective=False, delta_p=0.0)
+    ref, tar = _pair(R, W, H, D, dtype)
+    plan = api.Plan.from_workload(w)
+    dref, dtar = torch.from_numpy(ref).cuda(), torch.from_numpy(tar).cuda()
+    out = api.match(plan, dref, dtar, want_target=True)
+    got = {k: _host(v) for k, v in out.items()}
+    ora = OS.match(ref, tar, w, keep_volumes=True)
+    PR.check_selection(w, ora, got["dint_R"], got["dint_T"], got["dsub"], got["valid"],
+                       got["disp"])
+    # the profiled form launches the volumes one by one
+    two = {k: torch.empty_like(v) for k, v in out.items()}
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(7)]
+    for e in ev:
+        e.record()
+    lib, ws = api._lib.load(), plan.workspace("cuda")
+    api.check(lib.stereo_match_profiled(
+        plan.handle, api._p(dref), api._p(dtar), api._p(two["dint_R"]), api._p(two["dint_T"]),
+        api._p(two["dsub"]), api._p(two["valid"]), api._p(two["disp"]), api._p(ws),
+        plan.workspace_bytes, (ctypes.c_void_p * 7)(*[e.cuda_event for e in ev]),
+        api._stream()))
+    for k in got:
+        assert np.array_equal(got[k], _host(two[k]), equal_nan=True), k
+
+
+@pytest.mark.parametrize("R,W,H,D", [(3, 50, 18, 64), (4, 33, 21, 65), (7, 63, 30, 140)])
+def test_soft_forward_over_sweeps(R, W, H, D):
+    """The softmax state carried between sweeps: FP32 sums of E in [0, 2] over
+    T = 0.1 keep the exponents within 2e-5, so the soft level of D levels is
+    within 2e-5 D of the oracle's (its softmax weights move by at most that
+    relative amount)."""
+    w = _workload(R, W, H, D, "f32", perspective=True, delta_p=float(D // 3),
+                  plane=(float(D // 3), 0.0, 0.0))
+    ref, tar = _pair(R, W, H, D, "f32")
+    plan = api.Plan.from_workload(w)
+    disp, saved = api.soft_forward(plan, torch.from_numpy(ref).cuda(),
+                                   torch.from_numpy(tar).cuda(), w.plane)
+    fwd = SO.soft_forward(ref, tar, w.plane, w)
+    assert np.abs(_host(saved)[2] - fwd["dh"]).max() <= 2e-5 * D
+    assert np.abs(_host(disp) - fwd["disp"]).max() <= 2e-5 * D
