@@ -1,12 +1,12 @@
 // Batched form: many stereo pairs of uneven size and disparity range in one
-// captured graph of a dozen launches.  The cheap stages (warp, block
-// statistics, NCC volume, left-right check) run as one launch per stage and
-// element type (per NCC radius) over the blocks of every pair; the dominant
-// stage, the aggregation + WTA of both cost volumes of every pair, runs as
-// one persistent launch per (radius, guide type) group that takes tiles of
-// all pairs of the group from a work queue, largest disparity range first.
-// Every block and tile runs the same code as the per-pair path, so each
-// pair's result is bitwise the plain path's.
+// captured graph.  The cheap stages (warp, block statistics, left-right check,
+// and the NCC of engines 0 and 1) run as one launch per stage and element type
+// (per NCC radius) over the blocks of every pair; the dominant stage, the
+// aggregation + WTA of both cost volumes of every pair, runs as one launch per
+// radius (engines 0 and 1: per radius and guide type) over the strip segments
+// or tiles of all its pairs, longest first.  Every block, segment and tile
+// runs the same code as the per-pair path, so each pair's result is bitwise
+// the plain path's.
 #include <algorithm>
 #include <cstring>
 #include <new>

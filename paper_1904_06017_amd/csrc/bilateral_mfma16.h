@@ -1,6 +1,7 @@
-// Bilateral cost aggregation, Eqs. (10)-(11), fused with winner-take-all
-// selection and sub-pixel refinement (Sec. 3.2.2, Eq. 13) or the soft-argmin
-// head, on the matrix cores with FP16 operands split in two.
+// Operands and geometry of the bilateral aggregation, Eqs. (10)-(11), on the
+// matrix cores with FP16 operands split in two: shared by the forward kernel
+// (bilateral_stream.h) and the backward passes (bilateral_mfma16_bwd.h), whose
+// tile staging is also here.
 //
 // As in the FP32 matrix-core kernel, the aggregated costs of a 4x4 block of
 // pixels p and 16 levels d are the product E[p][d] = sum_q w(p, q) C(q, d)
@@ -34,12 +35,9 @@
 // cycle to 16-byte reads but 119 to 8-byte ones (12 waves, this access
 // pattern): with rows stored singly (two 8-byte reads per patch and part) the
 // products of a pass took 2630 cycles, now 2000, near the 1800 of the matrix
-// cores alone.  A workgroup (12 waves) owns a 16 x 12 pixel tile; each pass of 16 levels
-// copies the halo slab (2 parts x (12 + 2R) rows x HXP columns x 16 levels)
-// global -> LDS with direct-to-LDS loads into one of two buffers while the
-// other is being multiplied, one barrier per pass.  Rows outside the image
-// read clamped (finite) data, and the levels of the last block past D are
-// zeros; their weights are zero or their outputs unused.
+// cores alone.  Rows and columns outside the image and the levels of
+// the last block past D are zeros; their weights are zero or their outputs
+// unused.
 //
 // Per pixel the result depends on the pixel's block and the levels only, so
 // per-pair and queued launches are bitwise equal.  The summation order

@@ -18,12 +18,16 @@
 // reads (LDS) and products (matrix cores) overlap in every wave and across
 // the waves of a SIMD, and no weight is kept for longer than its product.
 //
-// What bounds it (1280x720, D = 64, R = 7, per block row and SIMD): about
-// 2400 cycles of weights on the vector ALU, 2400 of products and 2600 of LDS
-// reads, close to each other.  The form before (a tile's weights kept in
-// registers over passes of one level block each, every wave in the same
-// phase between barriers) spent 10200 cycles on the first pass of a tile,
-// vector ALU only, and 3600 on each other, matrix cores and LDS only.
+// What bounds it: per block row and SIMD (D = 64, R = 7) about 2400 cycles of
+// products, 2400 of weights on the vector ALU and 2600 of LDS reads.  Products
+// and vector ALU work overlap only in part on a SIMD (48 products of four waves
+// take 870 cycles alone, with 192 FMAs 1320, with 48 exponentials 890), so 4000
+// to 4300 cycles are the floor of a phase; it takes 5400.  The form before (a
+// tile's weights kept in registers over passes of one level block each, every
+// wave in the same phase between barriers) spent 10200 cycles on the first
+// pass of a tile, vector ALU only, and 3600 on each other, matrix cores and
+// LDS only.  1280x720, R = 7, both volumes: D = 64 0.475 -> 0.338 ms, D = 128
+// 0.84 -> 0.678 ms; 640x480, R = 5, D = 48: 0.107 -> 0.079 ms.
 #pragma once
 #include "bilateral_mfma16.h"
 
