@@ -312,8 +312,8 @@ def batched(args, scenes):
     if engine == 2:
         issued = sum(2 * 3 * 2.0 * mfma16_k(w.bil_radius) * w.width * w.height * w.num_disp
                      for w in ws)
-        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_mfma16.h")
-        roof = dict(kernel="agg_mfma16_kernel, queued (all groups of the batch)", bound="mfma",
+        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_stream.h")
+        roof = dict(kernel="agg_stream_kernel, queued (all groups of the batch)", bound="mfma",
                     achieved=round(achieved, 2), peak=MI355X_FP16_MFMA_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / MI355X_FP16_MFMA_TFLOPS, 4),
                     issued_frac=round(issued / (agg_ms / 1e3) / 1e12 / MI355X_FP16_MFMA_TFLOPS, 4),
@@ -415,9 +415,9 @@ def run(args):
         # over its patch-padded window union (mfma16_k positions per
         # pixel-level) and every product is three FP16 MFMAs (hi.hi, hi.lo,
         # lo.hi), so the issued FP16 flops are 3 x 2 x mfma16_k per element
-        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_mfma16.h")
+        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_stream.h")
         issued = 3 * 2.0 * mfma16_k(w.bil_radius) * elements
-        roof = dict(kernel="agg_mfma16_kernel (aggregation + fused WTA, both volumes)",
+        roof = dict(kernel="agg_stream_kernel (aggregation + fused WTA, both volumes)",
                     bound="mfma", achieved=round(achieved, 2), peak=MI355X_FP16_MFMA_TFLOPS,
                     unit="TFLOP/s", frac=round(achieved / MI355X_FP16_MFMA_TFLOPS, 4),
                     issued_tflops=round(issued / agg_s / 1e12, 1),
@@ -718,10 +718,10 @@ def fwd_bwd(args):
     flops = 2 * 2.0 * taps * el
     dom_ms = max(p1, p2)
     achieved = flops / (dom_ms / 1e3) / 1e12
-    if engine == 2 and R <= 5:
+    if engine == 2:
         issued = 2 * 3 * 2.0 * mfma16_k(R) * el
-        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_mfma16_bwd.h")
-        roof = dict(kernel="agg_mfma16_bwd_kernel (slower of the two passes)", bound="mfma",
+        src = os.path.join(ROOT, "paper_1904_06017_amd", "csrc", "bilateral_stream.h")
+        roof = dict(kernel="agg_stream_kernel modes 3/4 (slower of the two passes)", bound="mfma",
                     achieved=round(achieved, 2), peak=MI355X_FP16_MFMA_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / MI355X_FP16_MFMA_TFLOPS, 4),
                     issued_tflops=round(issued / (dom_ms / 1e3) / 1e12, 1),

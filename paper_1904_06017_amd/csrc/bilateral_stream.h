@@ -46,7 +46,6 @@ using bilh::u4;
 using bilh::View;
 
 constexpr int kMaxNB = 4;               // level blocks per sweep
-static_assert(kTW == kSegW, "strips as the batch's segments");
 
 // Products of the S states of a block and the row pairs they read, relative
 // to the block's first: state k takes products [ps(k), ps(k + 1)).  In phase
@@ -78,7 +77,8 @@ struct Sched {
   }
 };
 
-template <int R, int NB>
+// MODE 1: winner-take-all, 2: soft-argmin, 3 / 4: pass 1 / 2 of its backward.
+template <int R, int NB, int MODE>
 struct SGeom {
   using G = HGeom<R>;
   using C = Sched<R>;
@@ -95,20 +95,28 @@ struct SGeom {
   static constexpr int NGV = 2 * 2 * G::HXP;             // guide values of two pairs
   static constexpr int NCP = 8 * NB;                     // wave copies of two pairs
   static constexpr int KPW = (NCP + kWaves - 1) / kWaves;
-  // selection scratch of the group that finishes: a row of levels per pixel
+  // Scratch of the group that finishes a block row.  MODE 1: a row of levels
+  // per pixel; 3: C' of the block row, [level][4 rows][16 columns] dwords with
+  // the level stride that spreads a write over the banks, two by phase; 4: the
+  // costs at its pixels, [wave][level][16 pixels], two by block row.
   static constexpr int EROW = 64 * NB + 16;
+  static constexpr int CLEV = 65;                        // dwords per level (MODE 3)
+  static constexpr int CBLK = 16 * NB * CLEV * 4;        // bytes of one of the two
+  static constexpr int PBLK = 4 * NB * 1024;
+  static constexpr int SCRATCH =
+      MODE == 1 ? 64 * EROW : MODE == 3 ? 2 * CBLK : MODE == 4 ? 2 * PBLK : 0;
   static constexpr size_t lds_bytes = (size_t)NSLOT * SLOTB + (size_t)NGS * GSB +
-                                      sizeof(float) * G::STAB + 64 * (size_t)EROW;
+                                      sizeof(float) * G::STAB + SCRATCH;
   static_assert(lds_bytes <= 160 * 1024, "LDS budget");
   static_assert((2 * NB - 1) * CHB < 65536, "operand offsets must fit a DS immediate");
   static_assert(NGV <= kThreads, "one guide value per thread");
 };
 
 // LDS of a launch, laid out for kMaxNB blocks whatever a sweep takes: ring,
-// guide ring, spatial terms, selection scratch.
-template <int R>
+// guide ring, spatial terms, scratch.
+template <int R, int MODE>
 struct Lds {
-  using Z = SGeom<R, kMaxNB>;
+  using Z = SGeom<R, kMaxNB, MODE>;
   static constexpr int gring = Z::NSLOT * Z::SLOTB;
   static constexpr int tab = gring + Z::NGS * Z::GSB;
   static constexpr int scratch = tab + (int)sizeof(float) * HGeom<R>::STAB;
@@ -127,15 +135,44 @@ struct Args {
   int n;
 };
 
+// A backward pass (v[0] of Args: the split-FP16 input volume, v.D = levels of
+// the level tile, and the FP32 guide).  Six products per operand pair instead
+// of three: the weights, and the weights times the guide difference.
+// 1280x720, D = 48, R = 5: pass 1 398 -> 284 us, pass 2 292 us either way
+// (tiles of 32x16 pixels, their weights kept in registers, before).
+struct Back {
+  float* out;                           // pass 2: dC planar [D][H][W]
+  uint16_t* h2out;                      // pass 1: C' S, split-FP16 volume (as v)
+  const float* cpix;                    // pass 2: C planar [D][H][W]
+  const unsigned* gmax;                 // max |g'| over the image (float bits): the scale S
+  const float *sm_m, *sm_logZ, *sm_dh, *gD;
+  float *aP, *A1, *A2, *Wp;             // Wp nullable
+  float invT, one_minus_c1;
+  int d_first;                          // level of the tile's first slice
+  int d_all;                            // levels of the whole range (the bound on |d - dh|)
+};
+
+// Power-of-two scale that puts a bound m on |C'| in [2^13, 2^14) (bits: m
+// as a float): FP16 keeps its range for every value up to the bound.
+__device__ inline float cprime_scale(unsigned bits) {
+  const int ex = (int)((bits >> 23) & 0xFF);
+  if (ex == 0xFF || bits == 0) return 1.0f;          // non-finite or zero: no scaling
+  int e = ex - 126;                                   // max = f 2^e, f in [0.5, 1)
+  if (e < -80) e = -80;
+  const int k = 14 - e;                               // scale 2^k, |k| <= 114
+  return ldexpf(1.0f, k);
+}
+
 // Level blocks per sweep for nblk blocks: even shares of at most kMaxNB.
 inline __host__ __device__ int sweep_blocks(int nblk) {
   const int n = (nblk + kMaxNB - 1) / kMaxNB;
   return (nblk + n - 1) / n;
 }
 
-// x = hi + lo in FP16 for a pair of values (the conversions of bilh::split8,
-// left to the compiler so that it sees the hazards of the matrix cores
-// reading them); m1 = -1, opaque, keeps the remainder one mixed-precision FMA.
+// x = hi + lo in FP16 (round to nearest) for a pair of values: lo rounds the
+// remainder x - hi, which is exact in FP32.  Not inline assembly: the matrix
+// cores read the results, and the compiler has to see that hazard.  m1 = -1,
+// opaque, keeps the remainder one mixed-precision FMA.
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split_pair(float a, float b, float m1, unsigned& hi, unsigned& lo) {
@@ -183,8 +220,10 @@ template <int R, int MODE, int NB>
 struct Worker {
   using G = HGeom<R>;
   using C = Sched<R>;
-  using Z = SGeom<R, NB>;
+  using Z = SGeom<R, NB, MODE>;
+  using L = Lds<R, MODE>;
   static constexpr int S = C::S;
+  static constexpr bool TWO = MODE >= 3;             // the second weight w (G(p) - G(q))
 
   char* ring;
   char* gring;
@@ -193,9 +232,8 @@ struct Worker {
   int lane, wave, group, bx, li, lk;
 
   __device__ __forceinline__ explicit Worker(float* lds)
-      : ring(reinterpret_cast<char*>(lds)), gring(ring + Lds<R>::gring),
-        scratch(ring + Lds<R>::scratch),
-        tab(reinterpret_cast<const float*>(ring + Lds<R>::tab)) {
+      : ring(reinterpret_cast<char*>(lds)), gring(ring + L::gring), scratch(ring + L::scratch),
+        tab(reinterpret_cast<const float*>(ring + L::tab)) {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     group = wave >> 2;
@@ -210,7 +248,8 @@ struct Worker {
   // (q0 + NB)) of the volume's nblk level blocks.  first / last: the first /
   // last sweep of the strip's levels; between sweeps the selection state of a
   // pixel is kept in v.state.
-  __device__ __forceinline__ void sweep(const View& v, int x0, int b0, int len, int q0, int nblk) {
+  __device__ __forceinline__ void sweep(const View& v, const Back& bk, int x0, int b0, int len,
+                                        int q0, int nblk) {
     const bool first = q0 == 0, last = q0 + NB >= nblk;
     const int pair0 = 2 * b0 - (R >> 1);             // stored pair of ring pair 0
     const int plast = (v.H - 1 + (R & 1)) >> 1;
@@ -302,12 +341,35 @@ struct Worker {
     // level), read one phase ahead: at its use it would wait behind the copies.
     float4 st = make_float4(3.402823466e38f, 0.f, 0.f, 0.f);
     int stD = 0;
-    auto fetch_state = [&](int b) {
+    // Backward: the scales and, of pass 1, -(m + log Z), g' and dh at the pixel
+    // (st.x, st.y, st.z), of pass 2 the copies of its costs into the scratch.
+    const float kr_inv = 1.0f / kr;
+    float cscale = 1.0f;
+    if constexpr (TWO)
+      cscale = cprime_scale(__builtin_bit_cast(
+          unsigned, __builtin_bit_cast(float, *bk.gmax) * fabsf(bk.one_minus_c1) * bk.invT *
+                        (float)(bk.d_all > 1 ? bk.d_all - 1 : 1)));
+    auto fetch_state = [&](int b, char* __restrict__ swr) {
       int ln = lane;
       asm volatile("" : "+v"(ln));
       const int py = 4 * (b0 + b) + ((ln >> 2) & 3), px = x0 + 4 * bx + (ln & 3);
       const int64_t pix = py < v.H && px < v.W ? (int64_t)py * v.W + px : 0;
-      if (MODE == 1) {
+      if constexpr (MODE == 3) {
+        st.x = -(bk.sm_m[pix] + bk.sm_logZ[pix]);
+        st.y = bk.gD[pix] * (bk.one_minus_c1 * -bk.invT);
+        st.z = bk.sm_dh[pix];
+      } else if constexpr (MODE == 4) {
+        // copy c: 4 levels (lane >> 4) of the wave's 16 pixels (lane & 15)
+        char* const dst = swr + (b & 1) * Z::PBLK + bx * NB * 1024;
+#pragma unroll
+        for (int c = 0; c < 4 * NB; ++c) {
+          int d = 4 * c + (ln >> 4);
+          d = d < v.D ? d : v.D - 1;
+          __builtin_amdgcn_global_load_lds(
+              (BILM_GLOBAL void*)(bk.cpix + (int64_t)d * v.H * v.W + pix),
+              (BILM_LOCAL void*)(dst + 256 * c), 4, 0, 0);
+        }
+      } else if (MODE == 1) {
         st = v.state[pix];
         stD = v.dint[pix];
       } else {
@@ -316,13 +378,69 @@ struct Worker {
     };
     // Selection over the block's levels: the lane holds E of pixel li at
     // levels 16 (q0 + q) + 4 lk .. + 3 in acc[q].
-    auto finish = [&](int b) {
+    auto finish = [&](int b, const char* __restrict__ srd) {
       int ln = lane;
       asm volatile("" : "+v"(ln));                  // worked out here, not kept live
       const int lk = ln >> 4, pr = (ln >> 2) & 3, pc = ln & 3, lane = ln;
       const int py = 4 * (b0 + b) + pr, px = x0 + 4 * bx + pc;
       const bool in = py < v.H && px < v.W;
       const int64_t pix = in ? (int64_t)py * v.W + px : 0;
+      if constexpr (TWO) {
+        // lane: levels 16 q + 4 lk + j of pixel li, acc[q][0] = sum w B,
+        // acc[q][1] = sum w (G'(p) - G'(q)) B, both with the weights' 2^12
+        float ca = 0.0f, cb = 0.0f;
+        if constexpr (MODE == 3) {
+          float ws = wsum;                             // W_p 2^12
+          ws += __shfl_xor(ws, 16);
+          ws += __shfl_xor(ws, 32);
+          const float rinv = 1.0f / ws, oscale = rinv * (4096.0f * cscale);
+          unsigned* const blk = reinterpret_cast<unsigned*>(scratch + (b & 1) * Z::CBLK) +
+                                16 * pr + 4 * bx + pc;
+#pragma unroll
+          for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int d = 16 * q + 4 * lk + j;
+              const float ev = acc[q][0][j] * rinv;
+              const float Pd = __builtin_amdgcn_exp2f(fmaf(-ev, bk.invT, st.x) * 1.4426950408889634f);
+              const float dE = in && d < v.D ? st.y * Pd * ((float)(bk.d_first + d) - st.z) : 0.0f;
+              ca = fmaf(dE, ev, ca);
+              cb = fmaf(dE, acc[q][1][j], cb);
+              const float o = dE * oscale;             // S dE / W_p
+              const _Float16 hi = (_Float16)o, lo = (_Float16)(o - (float)hi);
+              blk[d * Z::CLEV] = (unsigned)__builtin_bit_cast(uint16_t, hi) |
+                                 ((unsigned)__builtin_bit_cast(uint16_t, lo) << 16);
+            }
+          ca += lane_value(ca, lane ^ 16);
+          ca += lane_value(ca, lane ^ 32);
+          cb += lane_value(cb, lane ^ 16);
+          cb += lane_value(cb, lane ^ 32);
+          // one lane per pixel adds this launch's sum (atomic adds without a
+          // return value: no wait; one add per pixel and launch, so the order
+          // is fixed)
+          if (lk == 0 && in) {
+            atomicAdd(bk.aP + pix, ca);
+            atomicAdd(bk.A1 + pix, cb * (kr_inv / 4096.0f));
+            if (bk.Wp) bk.Wp[pix] = ws * (1.0f / 4096.0f);
+          }
+        } else {
+          const float unscale = 1.0f / (4096.0f * cscale);
+          const float* const cp = reinterpret_cast<const float*>(srd + (b & 1) * Z::PBLK + bx * NB * 1024) +
+                                  (ln & 15);
+#pragma unroll
+          for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int d = 16 * q + 4 * lk + j;
+              cb = fmaf(in && d < v.D ? cp[16 * d] : 0.0f, acc[q][1][j], cb);
+              if (in && d < v.D) bk.out[((int64_t)d * v.H + py) * v.W + px] = acc[q][0][j] * unscale;
+            }
+          cb += lane_value(cb, lane ^ 16);
+          cb += lane_value(cb, lane ^ 32);
+          if (lk == 0 && in) atomicAdd(bk.A2 + pix, -cb * unscale * kr_inv);
+        }
+        return;
+      }
       f4 e[NB];
 #pragma unroll
       for (int q = 0; q < NB; ++q) e[q] = acc[q][0] + acc[q][1];
@@ -448,6 +566,46 @@ struct Worker {
       }
     };
 
+    // Pass 1: C' of block row b, left in the scratch by the phase before, out to
+    // the split volume by the group that formed it.  A chunk is the 4 columns
+    // of a level of a stored row, 8 bytes of each half; 32 lanes write a quad's
+    // 256 bytes.  The strip's 16 columns start R & 3 into a stored quad and a
+    // block row R & 1 into a pair: chunks shared with a neighbour go out value
+    // by value.
+    auto flush = [&](int b) {
+      constexpr int e = R & 1, QO = R & 3;
+      constexpr int NPR = 2 + e, NQ = (kTW + QO + 3) / 4;
+      const unsigned* const blk = reinterpret_cast<const unsigned*>(scratch + (b & 1) * Z::CBLK);
+      int c = bx * 64 + lane;
+      asm volatile("" : "+v"(c));
+      const int l = (c >> 1) & 15, par = c & 1;
+#pragma unroll 1
+      for (int u = c >> 5; u < NPR * NQ * NB; u += 8) {
+        const int q = u / (NPR * NQ), rem = u - q * (NPR * NQ);
+        const int prn = rem / NQ, qd = rem - prn * NQ;
+        const int row = 2 * prn + par - e, c0 = 4 * qd - QO;
+        if (row < 0 || row > 3 || 4 * (b0 + b) + row >= v.H) continue;
+        const unsigned* src = blk + (16 * q + l) * Z::CLEV + 16 * row;
+        const int64_t o = (int64_t)(2 * q) * v.plane + (int64_t)(2 * (b0 + b) + prn) * rows +
+                          128 * (((x0 + R) >> 2) + qd) + 8 * l + 4 * par;
+        if (c0 >= 0 && c0 + 3 < kTW && x0 + c0 + 3 < v.W) {
+          const unsigned w0 = src[c0], w1 = src[c0 + 1], w2 = src[c0 + 2], w3 = src[c0 + 3];
+          *reinterpret_cast<uint2*>(bk.h2out + o) =
+              make_uint2((w0 & 0xFFFFu) | (w1 << 16), (w2 & 0xFFFFu) | (w3 << 16));
+          *reinterpret_cast<uint2*>(bk.h2out + o + v.plane) =
+              make_uint2((w0 >> 16) | (w1 & 0xFFFF0000u), (w2 >> 16) | (w3 & 0xFFFF0000u));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (c0 + k < 0 || c0 + k >= kTW || x0 + c0 + k >= v.W) continue;
+            const unsigned w = src[c0 + k];
+            bk.h2out[o + k] = (uint16_t)w;
+            bk.h2out[o + v.plane + k] = (uint16_t)(w >> 16);
+          }
+        }
+      }
+    };
+
     float m1 = -1.0f;
     asm volatile("" : "+s"(m1));
     int base = 0, gbase = 0;                          // ring slots of pair 2 t
@@ -514,15 +672,39 @@ struct Worker {
           lo[j] = lb;
         }
         const h8 aH = __builtin_bit_cast(h8, hi), aL = __builtin_bit_cast(h8, lo);
-        if constexpr (MODE == 2) {
+        if constexpr (MODE == 2 || MODE == 3) {
 #pragma unroll
           for (int q = 0; q < 8; ++q) wsum += (float)aH[q] + (float)aL[q];
         }
+        u4 ghi, glo;
+        if constexpr (TWO) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {                // g = G'(q) - G'(p)
+            unsigned hb, lb;
+            split_pair(-g[2 * j] * w[2 * j], -g[2 * j + 1] * w[2 * j + 1], m1, hb, lb);
+            ghi[j] = hb;
+            glo[j] = lb;
+          }
+        }
+        const h8 cH = __builtin_bit_cast(h8, ghi), cL = __builtin_bit_cast(h8, glo);
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
           const u4 bh = *reinterpret_cast<const u4*>(rd + oa + 2 * q * Z::CHB);
           const u4 bl = *reinterpret_cast<const u4*>(rd + oa + (2 * q + 1) * Z::CHB);
           const h8 bH = __builtin_bit_cast(h8, bh), bL = __builtin_bit_cast(h8, bl);
+          if constexpr (TWO) {
+            f4 cw = i < 1 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][0];
+            f4 cg = i < 1 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][1];
+            cw = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, aH, cw, 0, 0, 0);
+            cg = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, cH, cg, 0, 0, 0);
+            cw = __builtin_amdgcn_mfma_f32_16x16x32_f16(bL, aH, cw, 0, 0, 0);
+            cg = __builtin_amdgcn_mfma_f32_16x16x32_f16(bL, cH, cg, 0, 0, 0);
+            acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, aL, cw, 0, 0, 0);
+            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bH, cL, cg, 0, 0, 0);
+            // keeps the operand reads of later blocks out of the registers
+            if (q & 1) __builtin_amdgcn_sched_barrier(0);
+            continue;
+          }
           f4 c = i < 2 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][i & 1];
           // costs as the first operand: the result has a pixel per lane column
           // and four consecutive levels per lane
@@ -544,16 +726,18 @@ struct Worker {
     // parameters the compiler knows that and does not wait for them before
     // the phase's first LDS read.
     auto phase = [&](int t, char* __restrict__ wr, const char* __restrict__ rd,
-                     const char* __restrict__ grd, const float* __restrict__ tb) {
+                     const char* __restrict__ grd, const float* __restrict__ tb,
+                     char* __restrict__ swr, const char* __restrict__ srd) {
       const int b = t - k;                            // block row of this wave
       const int js = wrap(base + Z::WHI + 1, Z::NSLOT), gs = wrap(gbase + Z::GHI + 1, Z::NGS);
       copy_pairs(2 * t + Z::WHI + 1, js, wr);
       unsigned raw = 0;
       if (gw) raw = guide_raw(2 * t + Z::GHI + 1);
-      if (!first && k == S - 1 && b >= 0) fetch_state(b);
-      if (k == 0 && b >= S) {
+      if ((TWO || !first) && k == S - 1 && b >= 0 && b < len) fetch_state(b, swr);
+      if (MODE == 3 && k == 1 && b >= S) flush(b - S);
+      if (k == 0 && b >= S && b - S < len) {
         priority(3);
-        finish(b - S);
+        finish(b - S, srd);
       }
       if (b >= 0 && b < len) {
         if (k == 0) products(Int<0>{}, rd, grd, tb);
@@ -567,8 +751,9 @@ struct Worker {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
     };
-    for (int t = 0; t < len + S; ++t) {
-      phase(t, ring, ring, gring, tab);
+    // the last block row's C' leaves one phase after its selection
+    for (int t = 0; t < len + S + (MODE == 3 ? 1 : 0); ++t) {
+      phase(t, ring, ring, gring, tab, scratch, scratch);
       base = wrap(base + 2, Z::NSLOT);
       gbase = wrap(gbase + 2, Z::NGS);
       k = k + 1 == S ? 0 : k + 1;
@@ -595,23 +780,24 @@ __device__ __forceinline__ void spatial_table(float* t, float ks2) {
 
 // Every sweep of one segment.
 template <int R, int MODE>
-__device__ __forceinline__ void segment(const View& v, int x0, int b0, int len, float* lds) {
+__device__ __forceinline__ void segment(const View& v, const Back& bk, int x0, int b0, int len,
+                                        float* lds) {
   const int nblk = (v.D + 15) / 16, nb = sweep_blocks(nblk);
   for (int q0 = 0; q0 < nblk; q0 += nb) {
     // the state a sweep leaves is read by the next one in the same wave (block
     // rows and lanes keep their waves): program order is enough.  A fence of
     // the whole device here cost 56 us a segment.
-    if (nb == 4) Worker<R, MODE, 4>(lds).sweep(v, x0, b0, len, q0, nblk);
-    else if (nb == 3) Worker<R, MODE, 3>(lds).sweep(v, x0, b0, len, q0, nblk);
-    else if (nb == 2) Worker<R, MODE, 2>(lds).sweep(v, x0, b0, len, q0, nblk);
-    else Worker<R, MODE, 1>(lds).sweep(v, x0, b0, len, q0, nblk);
+    if (nb == 4) Worker<R, MODE, 4>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else if (nb == 3) Worker<R, MODE, 3>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else if (nb == 2) Worker<R, MODE, 2>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else Worker<R, MODE, 1>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
   }
 }
 
 template <int R, int MODE, int QUEUE>
-__global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args a) {
+__global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args a, Back bk) {
   extern __shared__ float lds[];
-  float* tab = lds + Lds<R>::tab / 4;
+  float* tab = lds + Lds<R, MODE>::tab / 4;
   if constexpr (QUEUE) {
     // round k of G workgroups covers entries [k G, (k + 1) G); workgroup b (XCD
     // b % 8) takes entry k G + (b % 8) G / 8 + b / 8, so that each XCD works on
@@ -628,7 +814,7 @@ __global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args
         ks2 = v.ks2;
         spatial_table<R>(tab, ks2);
       }
-      segment<R, MODE>(v, e.x0, e.b0, e.len, lds);
+      segment<R, MODE>(v, bk, e.x0, e.b0, e.len, lds);
     }
   } else {
     spatial_table<R>(tab, a.v[0].ks2);
@@ -649,7 +835,7 @@ __global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args
       const int seg = rem / bc, strip = c0 + rem - seg * bc;
       const int b0 = seg * a.len;
       const int len = min(a.len, a.br - b0);
-      if (len > 0) segment<R, MODE>(a.v[vol], strip * kTW, b0, len, lds);   // uniform
+      if (len > 0) segment<R, MODE>(a.v[vol], bk, strip * kTW, b0, len, lds);   // uniform
     }
   }
 }
@@ -660,7 +846,7 @@ hipError_t set_lds_attr() {
   if (!done) {
     hipError_t e = hipFuncSetAttribute((const void*)agg_stream_kernel<R, MODE, QUEUE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)Lds<R>::bytes);
+                                       (int)Lds<R, MODE>::bytes);
     if (e != hipSuccess) return e;
     done = true;
   }
@@ -693,7 +879,7 @@ inline void cut_strips(int tx, int br, int nvol, int S, int cus, int& nseg, int&
 
 // One or two volumes of a pair (the same size, radius and sigmas).
 template <int R, int MODE>
-hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s) {
+hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s, const Back& bk = Back{}) {
   Args a{};
   for (int k = 0; k < nvol; ++k) {
     const BilPair& b = p[k];
@@ -713,7 +899,7 @@ hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s) {
   a.len = (a.br + a.nseg - 1) / a.nseg;
   const int grid = a.banded ? cus : std::min(cus, nvol * a.tx * a.nseg);
   hipLaunchKernelGGL((agg_stream_kernel<R, MODE, 0>), dim3(grid), dim3(256 * Sched<R>::S),
-                     Lds<R>::bytes, s, a);
+                     (Lds<R, MODE>::bytes), s, a, bk);
   return hipGetLastError();
 }
 
@@ -723,6 +909,34 @@ hipError_t launch_args(const Plan& P, const BilArgs* a, int nvol, int mode, hipS
   BilPair p[2];
   for (int k = 0; k < nvol; ++k) p[k] = bil::make_pair(P, a[k]);
   return mode == 2 ? launch_pair<R, 2>(p, nvol, s) : launch_pair<R, 1>(p, nvol, s);
+}
+
+// Pass 1 or 2 of the backward for one level tile (at most 64 levels, float
+// guide).
+template <int R>
+hipError_t launch_back(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
+  const BilPair p = bil::make_pair(P, a);
+  if (p.D > 16 * kMaxNB || p.g_u8 || !a.gmax || (pass == 1 && !a.h2_out) ||
+      (pass == 2 && (!a.cpix || !a.E)))
+    return hipErrorInvalidValue;
+  Back b{};
+  b.out = a.E;
+  b.h2out = a.h2_out;
+  b.cpix = a.cpix;
+  b.gmax = a.gmax;
+  b.sm_m = a.sm_m;
+  b.sm_logZ = a.sm_logZ;
+  b.sm_dh = a.sm_dh;
+  b.gD = a.gD;
+  b.aP = a.aP;
+  b.A1 = a.A1;
+  b.A2 = a.A2;
+  b.Wp = a.Wp;
+  b.invT = p.o.invT;
+  b.one_minus_c1 = p.o.one_minus_c1;
+  b.d_first = a.d_first;
+  b.d_all = P.D;
+  return pass == 1 ? launch_pair<R, 3>(&p, 1, s, b) : launch_pair<R, 4>(&p, 1, s, b);
 }
 
 // n segments over many volumes (descs, segs: device arrays).
@@ -736,7 +950,7 @@ hipError_t launch_queue(const BilPair* descs, const Seg* segs, int n, int n_grou
   a.segs = segs;
   a.n = n;
   hipLaunchKernelGGL((agg_stream_kernel<R, 1, 1>), dim3(n_groups), dim3(256 * Sched<R>::S),
-                     Lds<R>::bytes, s, a);
+                     (Lds<R, 1>::bytes), s, a, Back{});
   return hipGetLastError();
 }
 

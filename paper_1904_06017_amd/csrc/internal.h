@@ -181,7 +181,7 @@ hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, 
                                      int n_groups, hipStream_t s);
 
 // Backward of the soft-argmin head on the split-FP16 matrix cores, for one
-// level tile (radius R <= kBwd16MaxR, float guide, d_first a multiple of 16):
+// level tile (at most 64 levels, float guide, d_first a multiple of 16):
 // pass 1 reads the tile's split costs (a.h2) and writes C' = dE / W_p, times
 // a power of two set by the bound max |g'| |1 - c1| (D - 1) / T (*a.gmax =
 // max |g'| as float bits), split into a.h2_out (same layout), with aP, A1,
@@ -189,7 +189,6 @@ hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, 
 // [levels][H][W] to a.E and A2 as mode 6 (a.cpix: the tile's costs, planar).
 // The stored columns and rows of a.h2_out outside the image are not written:
 // zero them first (launch_h2_pad_zero).
-constexpr int kBwd16MaxR = 5;
 hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hipStream_t s);
 // Zeros in the stored columns outside [0, W) and rows outside [0, H) (all
 // levels, both halves) of the first nblk 16-level blocks of a split-FP16 volume at radius R.

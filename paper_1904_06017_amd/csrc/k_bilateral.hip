@@ -1,5 +1,5 @@
 // Dispatch of the aggregation launches over the compiled window radii.
-#include "bilateral_mfma16_bwd.h"
+#include "bilateral_mfma16.h"
 
 namespace stereo {
 hipError_t launch_bilateral_r1(const Plan&, const BilArgs&, int, hipStream_t);
@@ -41,16 +41,21 @@ hipError_t launch_bwd16_r2(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bwd16_r3(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bwd16_r4(const Plan&, const BilArgs&, int, hipStream_t);
 hipError_t launch_bwd16_r5(const Plan&, const BilArgs&, int, hipStream_t);
+hipError_t launch_bwd16_r6(const Plan&, const BilArgs&, int, hipStream_t);
+hipError_t launch_bwd16_r7(const Plan&, const BilArgs&, int, hipStream_t);
+hipError_t launch_bwd16_r8(const Plan&, const BilArgs&, int, hipStream_t);
 
 hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
   if ((pass != 1 && pass != 2) || (a.d_first & 15)) return hipErrorInvalidValue;
-  static_assert(kBwd16MaxR == 5, "one launcher per compiled radius");
   switch (P.R) {
     case 1: return launch_bwd16_r1(P, a, pass, s);
     case 2: return launch_bwd16_r2(P, a, pass, s);
     case 3: return launch_bwd16_r3(P, a, pass, s);
     case 4: return launch_bwd16_r4(P, a, pass, s);
     case 5: return launch_bwd16_r5(P, a, pass, s);
+    case 6: return launch_bwd16_r6(P, a, pass, s);
+    case 7: return launch_bwd16_r7(P, a, pass, s);
+    case 8: return launch_bwd16_r8(P, a, pass, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -1,5 +1,4 @@
 // Aggregation kernels instantiated for window radius R = 1.
-#include "bilateral_mfma16_bwd.h"
 #include "bilateral_stream.h"
 
 namespace stereo {
@@ -24,6 +23,6 @@ hipError_t launch_bilateral_persistent_r1(int engine, stereo_dtype gdt, int leve
   return bil::launch_persistent_r<1>(gdt, levels, p, tiles, n_tiles, counter, n_groups, s);
 }
 hipError_t launch_bwd16_r1(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
-  return bilh::launch_bwd_args<1>(P, a, pass, s);
+  return bils::launch_back<1>(P, a, pass, s);
 }
 }  // namespace stereo

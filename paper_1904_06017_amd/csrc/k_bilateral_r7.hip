@@ -22,4 +22,7 @@ hipError_t launch_bilateral_persistent_r7(int engine, stereo_dtype gdt, int leve
   if (engine == 1) return bilm::launch_queue_r<7>(gdt, p, tiles, n_tiles, counter, n_groups, s);
   return bil::launch_persistent_r<7>(gdt, levels, p, tiles, n_tiles, counter, n_groups, s);
 }
+hipError_t launch_bwd16_r7(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
+  return bils::launch_back<7>(P, a, pass, s);
+}
 }  // namespace stereo

@@ -22,4 +22,7 @@ hipError_t launch_bilateral_persistent_r8(int engine, stereo_dtype gdt, int leve
   if (engine == 1) return bilm::launch_queue_r<8>(gdt, p, tiles, n_tiles, counter, n_groups, s);
   return bil::launch_persistent_r<8>(gdt, levels, p, tiles, n_tiles, counter, n_groups, s);
 }
+hipError_t launch_bwd16_r8(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
+  return bils::launch_back<8>(P, a, pass, s);
+}
 }  // namespace stereo

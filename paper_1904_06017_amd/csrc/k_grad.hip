@@ -103,8 +103,8 @@ guide_finish_kernel(const GT* __restrict__ g, int64_t gpitch, const float* __res
 // then the target-side sums along the diagonals (the second pass re-reads C
 // and dC; one fused pass with the diagonals exchanged through LDS, or read
 // through the caches, measured slower).
-// max |g| over n values into *out (float bits; non-negative floats order as
-// their bits), one atomic per workgroup (atomics on one address serialise);
+// max |g| over the finite of n values into *out (float bits; non-negative
+// floats order as their bits), one atomic per workgroup (atomics on one address serialise);
 // *out is zeroed before the launch.  Four independent loads per thread and
 // round.
 __global__ void __launch_bounds__(256) absmax_kernel(const float* __restrict__ g, int64_t n,
@@ -117,7 +117,8 @@ __global__ void __launch_bounds__(256) absmax_kernel(const float* __restrict__ g
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int64_t i = i0 + k * stride;
-      v[k] = i < n ? fabsf(g[i]) : 0.0f;
+      const float x = i < n ? fabsf(g[i]) : 0.0f;
+      v[k] = x <= 3.402823466e38f ? x : 0.0f;
     }
     m = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
   }
@@ -1020,10 +1021,11 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
   }
 
   const int n = (2 * r + 1) * (2 * r + 1);
-  // the aggregation passes on the split-FP16 matrix cores where they fit
-  // (small radii: two weight operands per lane) and the level tiles start on
-  // 16-level blocks; elsewhere on the vector ALU
-  const bool mc = P.agg_engine == 2 && P.R <= kBwd16MaxR && (D <= DT || DT % 16 == 0);
+  // the aggregation passes on the split-FP16 matrix cores where the level
+  // tiles start on 16-level blocks (the volumes are stored by those); elsewhere
+  // on the vector ALU: 317x243, D = 40, R = 7 takes 201 + 196 us there, 49 +
+  // 39 us here
+  const bool mc = P.agg_engine == 2 && (D <= DT || DT % 16 == 0);
   if (mc) {
     // max |g'| (the scale of C' in pass 1) and zeros in the pad columns of
     // the C' volume, which the passes never write

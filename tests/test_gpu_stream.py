@@ -86,3 +86,52 @@ def test_soft_forward_over_sweeps(R, W, H, D):
     fwd = SO.soft_forward(ref, tar, w.plane, w)
     assert np.abs(_host(saved)[2] - fwd["dh"]).max() <= 2e-5 * D
     assert np.abs(_host(disp) - fwd["disp"]).max() <= 2e-5 * D
+
+
+@pytest.mark.parametrize("R,W,H,D", [(1, 16, 4, 16), (2, 33, 9, 17), (3, 47, 31, 64), (4, 31, 14, 65),
+                                     (5, 65, 13, 33), (6, 49, 27, 40), (6, 130, 22, 64),
+                                     (7, 81, 18, 70), (7, 17, 45, 48), (8, 50, 21, 30),
+                                     (8, 97, 12, 129)])
+def test_backward_at_cut_edges(R, W, H, D):
+    """Both backward passes at strip, block-row, level-block and level-tile
+    remainders.  FP32 exponents E / T <= 20 leave the softmax weights within
+    2e-6, which the block variances of this texture amplify by less than 50:
+    each gradient within 1e-4 of the FP64 adjoint in L2, and of the vector
+    ALU's.  The plane terms cancel: 1e-3 of the largest, as for that one."""
+    w = _workload(R, W, H, D, "f32", perspective=True, delta_p=float(D // 3),
+                  plane=(float(D // 3), 0.01, 0.0))
+    ref, tar = _pair(R, W, H, D, "f32")
+    rng = np.random.Generator(np.random.PCG64(R + W))
+    g = ndimage.gaussian_filter(rng.normal(size=(H, W)), 1.5).astype(np.float32)
+    fwd = SO.soft_forward(ref, tar, w.plane, w)
+    exact = SO.soft_backward(ref, tar, w.plane, w, fwd, g.astype(np.float64))
+    dref, dtar, dg = (torch.from_numpy(x).cuda() for x in (ref, tar, g))
+    got = []
+    for engine in (2, 0):
+        plan = api.Plan.from_workload(w)
+        plan.set_tuning("agg_engine", engine)
+        _, saved = api.soft_forward(plan, dref, dtar, w.plane)
+        got.append([_host(x).astype(np.float64)
+                    for x in api.backward(plan, dref, dtar, w.plane, saved, dg)])
+    for a, v, e, tol in zip(*got, exact, (1e-4, 1e-4, 1e-3)):
+        assert np.linalg.norm(a - e) <= tol * np.linalg.norm(e)
+        assert np.linalg.norm(a - v) <= tol * np.linalg.norm(e)
+
+
+def test_backward_keeps_its_scale_beside_an_infinite_gradient():
+    """The FP16 scale of pass 2's input comes from the finite gradients alone:
+    a pixel whose gradient is infinite leaves the others, far from it, where
+    they are without it (1e-6: the same products at the same scale, other
+    neighbours)."""
+    R, W, H, D = 6, 96, 80, 32
+    w = _workload(R, W, H, D, "f32", perspective=True, delta_p=10.0, plane=(10.0, 0.0, 0.0))
+    ref, tar = _pair(R, W, H, D, "f32")
+    g = np.full((H, W), 1e-6, np.float32)
+    dref, dtar = torch.from_numpy(ref).cuda(), torch.from_numpy(tar).cuda()
+    plan = api.Plan.from_workload(w)
+    _, saved = api.soft_forward(plan, dref, dtar, w.plane)
+    plain = _host(api.backward(plan, dref, dtar, w.plane, saved, torch.from_numpy(g).cuda())[0])
+    g[2, 2] = np.inf
+    odd = _host(api.backward(plan, dref, dtar, w.plane, saved, torch.from_numpy(g).cuda())[0])
+    far = (slice(60, None), slice(None))
+    assert np.linalg.norm(odd[far] - plain[far]) <= 1e-6 * np.linalg.norm(plain[far])
