@@ -673,8 +673,10 @@ struct Worker {
         }
         const h8 aH = __builtin_bit_cast(h8, hi), aL = __builtin_bit_cast(h8, lo);
         if constexpr (MODE == 2 || MODE == 3) {
+          // hi + lo as one mixed-precision FMA: two conversions and an addition
+          // take 152 against 140 us (soft-argmin, 1280x720, D = 48, R = 5)
 #pragma unroll
-          for (int q = 0; q < 8; ++q) wsum += (float)aH[q] + (float)aL[q];
+          for (int q = 0; q < 8; ++q) wsum += fmaf((float)aH[q], -m1, (float)aL[q]);
         }
         u4 ghi, glo;
         if constexpr (TWO) {
