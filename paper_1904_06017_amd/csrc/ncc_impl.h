@@ -3,6 +3,7 @@
 // per-radius instantiation units (k_ncc_r1 .. r8) and the dispatch in
 // k_cost.hip (which instantiates none of them).
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -401,6 +402,24 @@ __device__ __forceinline__ void ncc_body(const T* __restrict__ ref, int64_t ref_
                                   isdY, C, out_w, out_pitch, out_slice, pad, sm, bx, by, bz, C2);
 }
 
+// Order of a launch's workgroups: XCD k (workgroups k mod 8) owns per
+// consecutive tiles (rows of nx tiles), cut in runs of chunk tiles, and covers
+// a run at each of the level blocks in turn.  The level blocks of a tile
+// read the same images and statistics, so a run is as long as their bytes stay
+// in the XCD's L2 beside the stores (kRunBytes of its 4 MB): longer runs also
+// keep the stores on fewer volumes' blocks at a time.  Both split volumes,
+// tiles in x, y, level order over all XCDs -> this one: 1280x720, 64 levels
+// 104 -> 97 us, 128 levels 214 -> 182 us (one run an XCD; 195 us in two);
+// 1917x1075, 96 levels, FP32 images 501 -> 363 us (three runs of 2.2 MB;
+// 387 us in two of 3.3 MB, 525 in one of 6.6 MB, 415 in runs of 8 tiles).
+// The planar and interleaved forms (64-level blocks, one or two in all) deal
+// the tiles out one by one instead: 133 against 136 us for both planar volumes.
+struct NccGrid {                        // grid: 8 chunk x level blocks x runs
+  int nx, tiles, per, chunk;
+  int step_x, step;                     // tile of XCD x, place i: x step_x + i step
+};
+constexpr int64_t kRunBytes = 3 << 20;
+
 template <int r, typename T, int QUAD, int DC>
 __global__ void __launch_bounds__(16 * DC)
 ncc_kernel(const T* __restrict__ ref, int64_t ref_pitch,
@@ -408,11 +427,14 @@ ncc_kernel(const T* __restrict__ ref, int64_t ref_pitch,
            const float* __restrict__ zX, const float* __restrict__ isdX,
            const float* __restrict__ zY, const float* __restrict__ isdY,
            float* __restrict__ C, int out_w, int64_t out_pitch,
-           int64_t out_slice, int anchor, int pad, float* __restrict__ C2) {
+           int64_t out_slice, int anchor, int pad, float* __restrict__ C2, NccGrid g) {
   extern __shared__ float sm[];
+  const int i = blockIdx.z * g.chunk + (blockIdx.x >> 3);
+  const int t = (int)(blockIdx.x & 7) * g.step_x + i * g.step, by = t / g.nx;
+  if (i >= g.per || t >= g.tiles) return;            // uniform
   ncc_body<r, T, QUAD, DC>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY, isdY, C,
-                       out_w, out_pitch, out_slice, anchor, pad, sm, blockIdx.x, blockIdx.y,
-                       blockIdx.z, C2);
+                       out_w, out_pitch, out_slice, anchor, pad, sm, t - by * g.nx, by,
+                       blockIdx.y, C2);
 }
 
 
@@ -470,17 +492,26 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
                           int d_first, int d_end, int quad, int pad,
                           hipStream_t s, float* C2) {
   const int rows = quad >= 2 ? P.H + (pad & 1) : P.H;      // rows from the first tile's origin
-  dim3 grid((out_w + NC_TX - 1) / NC_TX, (rows + NC_TY - 1) / NC_TY,
-            (d_end - d_first + DC - 1) / DC);
+  const int tx = quad == 4 ? NC_TX4 : NC_TX;
+  NccGrid g;
+  g.nx = (out_w + tx - 1) / tx;
+  g.tiles = g.nx * ((rows + NC_TY - 1) / NC_TY);
+  g.per = (g.tiles + 7) / 8;
+  // ref, tarw and four statistics a pixel
+  const int64_t bytes = (int64_t)g.per * tx * NC_TY * (sizeof(T) + 5 * sizeof(float));
+  const int runs = quad >= 2 ? (int)std::min<int64_t>((bytes + kRunBytes - 1) / kRunBytes, g.per) : 1;
+  g.step_x = quad >= 2 ? g.per : 1;
+  g.step = quad >= 2 ? 1 : 8;
+  g.chunk = (g.per + runs - 1) / runs;
+  const dim3 grid(8 * g.chunk, (d_end - d_first + DC - 1) / DC, (g.per + g.chunk - 1) / g.chunk);
   if (quad == 4) {
     // both anchors' split volumes (C, and C2 when non-NULL)
-    grid.x = (out_w + NC_TX4 - 1) / NC_TX4;
     hipError_t e = ncc_allow_lds<r, T, 4, DC, 0>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((ncc_kernel<r, T, 4, DC>), grid, dim3(16 * DC),
                        (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
-                       0, pad, C2);
+                       0, pad, C2, g);
     return hipGetLastError();
   }
   if (quad == 3) {
@@ -491,7 +522,7 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
       hipLaunchKernelGGL((ncc_kernel<r, T, 3, DC>), grid, dim3(16 * DC),
                          (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                          d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
-                         anchor, pad, C2);
+                         anchor, pad, C2, g);
       return hipGetLastError();
     }
     return hipErrorInvalidValue;
@@ -503,17 +534,17 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
     hipLaunchKernelGGL((ncc_kernel<r, T, 2, DC>), grid, dim3(16 * DC),
                        (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
-                       anchor, pad, (float*)nullptr);
+                       anchor, pad, (float*)nullptr, g);
   else if (quad)
     hipLaunchKernelGGL((ncc_kernel<r, T, 1, DC>), grid, dim3(16 * DC),
                        (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
-                       anchor, 0, (float*)nullptr);
+                       anchor, 0, (float*)nullptr, g);
   else
     hipLaunchKernelGGL((ncc_kernel<r, T, 0, DC>), grid, dim3(16 * DC),
                        (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
-                       anchor, 0, (float*)nullptr);
+                       anchor, 0, (float*)nullptr, g);
   return hipGetLastError();
 }
 

@@ -135,3 +135,25 @@ def test_backward_keeps_its_scale_beside_an_infinite_gradient():
     odd = _host(api.backward(plan, dref, dtar, w.plane, saved, torch.from_numpy(g).cuda())[0])
     far = (slice(60, None), slice(None))
     assert np.linalg.norm(odd[far] - plain[far]) <= 1e-6 * np.linalg.norm(plain[far])
+
+
+@pytest.mark.parametrize("W,H,D,dtype", [(41, 9, 5, "u8"), (700, 130, 33, "u8"),
+                                         (1931, 1083, 18, "f32"), (2561, 1441, 17, "u8")])
+def test_every_cost_tile_is_written(W, H, D, dtype):
+    """The cost tiles are dealt out by XCD in runs bounded by their input
+    bytes (one, and at the larger sizes two and three runs of level blocks of
+    16, 32 and 64): over a workspace of NaNs every level block size gives the
+    same results, bit for bit, so no tile is left out."""
+    w = _workload(2, W, H, D, dtype, perspective=False, delta_p=0.0)
+    ref, tar = (torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in _pair(2, W, H, D, dtype))
+    want = None
+    for levels in (16, 32, 64):
+        plan = api.Plan.from_workload(w)
+        plan.set_tuning("ncc_levels", levels)
+        plan.workspace("cuda").fill_(255)
+        got = {k: _host(v) for k, v in api.match(plan, ref, tar, want_target=True).items()}
+        if want is None:
+            want = got
+            assert not np.isnan(got["dsub"]).any()
+        for k in got:
+            assert np.array_equal(got[k], want[k], equal_nan=True), (levels, k)
