@@ -90,9 +90,6 @@ hipError_t launch_warp_tracked(const Plan& P, const void* tar, const stereo_plan
 hipError_t launch_block_stats2(const Plan& P, const void* ref, stereo_dtype dt,
                                int64_t ref_pitch, const float* tarw, float* zX, float* isdX,
                                float* zY, float* isdY, hipStream_t s);
-hipError_t launch_block_stats(const Plan& P, const void* img, stereo_dtype dt,
-                              int64_t pitch, float* z, float* isd,
-                              hipStream_t s);
 
 // C[d][y][x], x in [0, out_w): anchor 0 compares the ref block at x with the
 // tar_w block at x - d; anchor 1 the ref block at x + d with tar_w at x.

@@ -104,66 +104,83 @@ warp_tracked_kernel(const T* __restrict__ tar, int64_t pitch, int W, double delt
 // and isd = 1 / sigma (rounded to FP32 once), so that the cost is
 // 1 + zX zY - (S / n) isdX isdY; a flat block (variance below kFlatVar)
 // stores z = isd = 0, which makes its cost exactly 1 without a branch.
-constexpr int ST_TX = 64, ST_TY = 16;
+// LDS reads bound the sums: a thread forms ST_N = 4 neighbouring ones from
+// the 2r + 4 values they share, not each from its own 2r + 1 (both images of a
+// 1280x720 pair, r = 3, 22.4 -> 17.0 us; 320x240, r = 2, 8.6 -> 4.9 us).
+constexpr int ST_TX = 64, ST_TY = 16, ST_N = 4;
 
-__host__ __device__ constexpr size_t stats_lds_bytes(int r) {
-  return sizeof(float) * (size_t)(ST_TX + 2 * r) * (ST_TY + 2 * r) +
-         2 * sizeof(double) * (size_t)ST_TY * (ST_TX + 2 * r);
-}
+template <int r>
+struct StatGeom {
+  static constexpr int K = 2 * r + 1;
+  static constexpr int tw = ST_TX + 2 * r, th = ST_TY + 2 * r;
+  static constexpr int pitch = tw + 1;       // of the column sums: 16 rows on distinct banks
+  static constexpr size_t lds_bytes = sizeof(float) * tw * th + sizeof(double2) * ST_TY * pitch;
+};
 
-template <typename T>
+template <typename T, int r>
 __device__ __forceinline__ void block_stats_body(const T* __restrict__ img, int64_t pitch,
-                                                 int W, int H, int r, float* __restrict__ zmap,
+                                                 int W, int H, float* __restrict__ zmap,
                                                  float* __restrict__ isd, float* tile, int bx,
                                                  int by) {
+  using G = StatGeom<r>;
+  constexpr int tw = G::tw, th = G::th, K = G::K, NT = 256;
   const int SW = W + 2 * r;
-  const int tw = ST_TX + 2 * r, th = ST_TY + 2 * r;
   const int xc0 = bx * ST_TX - r;            // first block centre (image col)
   const int y0 = by * ST_TY;
-  // staged in chunks: four loads of a thread in flight before their stores
-  for (int i0 = threadIdx.x; i0 < tw * th; i0 += 4 * (int)blockDim.x) {
-    float v[4];
+  const int tid = threadIdx.x;
+  // staged in chunks: eight loads of a thread in flight before their stores
+  constexpr int KK = (tw * th + NT - 1) / NT;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = min(i0 + k * (int)blockDim.x, tw * th - 1);
+  for (int k0 = 0; k0 < KK; k0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (k0 + k >= KK) continue;
+      const int i = min(tid + (k0 + k) * NT, tw * th - 1);
       const int yy = i / tw, xx = i - yy * tw;
       const int gy = min(max(y0 - r + yy, 0), H - 1);
       const int gx = min(max(xc0 - r + xx, 0), W - 1);
       v[k] = ld(img + (int64_t)gy * pitch + gx);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * (int)blockDim.x;
-      if (i < tw * th) tile[i] = v[k] - kOffset;
-    }
+    for (int k = 0; k < 8; ++k)
+      if (k0 + k < KK && tid + (k0 + k) * NT < tw * th) tile[tid + (k0 + k) * NT] = v[k] - kOffset;
   }
   // column sums of the block rows of each output row: [ST_TY][tw], x and x^2
-  double* cs = reinterpret_cast<double*>(tile + tw * th);
-  double* cq = cs + ST_TY * tw;
+  double2* cs = reinterpret_cast<double2*>(tile + tw * th);
   __syncthreads();
-  const int k = 2 * r + 1;
-  for (int o = threadIdx.x; o < ST_TY * tw; o += blockDim.x) {
-    const int ty = o / tw, c = o - ty * tw;
-    double sx = 0.0, sq = 0.0;
-    for (int i = 0; i < k; ++i) {
-      const double v = (double)tile[(ty + i) * tw + c];
-      sx += v;
-      sq = fma(v, v, sq);
+  for (int o = tid; o < tw * (ST_TY / ST_N); o += NT) {
+    const int g = o / tw, c = o - g * tw, ty = ST_N * g;
+    double v[K + ST_N - 1];
+#pragma unroll
+    for (int i = 0; i < K + ST_N - 1; ++i) v[i] = (double)tile[(ty + i) * tw + c];
+#pragma unroll
+    for (int n = 0; n < ST_N; ++n) {
+      double sx = 0.0, sq = 0.0;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        sx += v[n + i];
+        sq = fma(v[n + i], v[n + i], sq);
+      }
+      cs[(ty + n) * G::pitch + c] = make_double2(sx, sq);
     }
-    cs[o] = sx;
-    cq[o] = sq;
   }
   __syncthreads();
-  const double inv_n = 1.0 / (double)(k * k);
-  for (int o = threadIdx.x; o < ST_TX * ST_TY; o += blockDim.x) {
-    const int ty = o / ST_TX, tx = o - ty * ST_TX;
-    const int xi = bx * ST_TX + tx;               // map column index
-    const int y = y0 + ty;
+  const double inv_n = 1.0 / (double)(K * K);
+  static_assert(ST_TX * ST_TY == ST_N * NT, "one run of ST_N outputs per thread");
+  const int ty = tid & (ST_TY - 1), tx = (tid / ST_TY) * ST_N, y = y0 + ty;
+  double2 c[K + ST_N - 1];
+#pragma unroll
+  for (int j = 0; j < K + ST_N - 1; ++j) c[j] = cs[ty * G::pitch + tx + j];
+#pragma unroll
+  for (int n = 0; n < ST_N; ++n) {
+    const int xi = bx * ST_TX + tx + n;               // map column index
     if (xi >= SW || y >= H) continue;
     double sx = 0.0, sq = 0.0;
-    for (int j = 0; j < k; ++j) {
-      sx += cs[ty * tw + tx + j];
-      sq += cq[ty * tw + tx + j];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      sx += c[n + j].x;
+      sq += c[n + j].y;
     }
     const double m = sx * inv_n;
     const double var = fma(-m, m, sq * inv_n);
@@ -173,26 +190,33 @@ __device__ __forceinline__ void block_stats_body(const T* __restrict__ img, int6
   }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256)
-block_stats_kernel(const T* __restrict__ img, int64_t pitch, int W, int H, int r,
-                   float* __restrict__ zmap, float* __restrict__ isd) {
-  extern __shared__ float tile[];   // (ST_TY + 2r) x (ST_TX + 2r)
-  block_stats_body<T>(img, pitch, W, H, r, zmap, isd, tile, blockIdx.x, blockIdx.y);
+// f(Int<r>{}) of a block radius (1..8).
+template <typename F>
+__host__ __device__ __forceinline__ void with_radius(int r, F f) {
+  switch (r) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+  }
 }
 
 // Both images of a pair in one launch: blockIdx.z = 0 the reference (T),
 // 1 the warped target (FP32).
-template <typename T>
+template <typename T, int r>
 __global__ void __launch_bounds__(256)
 block_stats2_kernel(const T* __restrict__ ref, int64_t ref_pitch, const float* __restrict__ tarw,
-                    int W, int H, int r, float* __restrict__ zX, float* __restrict__ isdX,
+                    int W, int H, float* __restrict__ zX, float* __restrict__ isdX,
                     float* __restrict__ zY, float* __restrict__ isdY) {
-  extern __shared__ float tile[];
+  extern __shared__ __align__(16) float tile[];
   if (blockIdx.z == 0)
-    block_stats_body<T>(ref, ref_pitch, W, H, r, zX, isdX, tile, blockIdx.x, blockIdx.y);
+    block_stats_body<T, r>(ref, ref_pitch, W, H, zX, isdX, tile, blockIdx.x, blockIdx.y);
   else
-    block_stats_body<float>(tarw, W, W, H, r, zY, isdY, tile, blockIdx.x, blockIdx.y);
+    block_stats_body<float, r>(tarw, W, W, H, zY, isdY, tile, blockIdx.x, blockIdx.y);
 }
 
 template <typename T>
@@ -212,12 +236,15 @@ warp_jobs_kernel(const WarpJob* __restrict__ jobs, const int* __restrict__ first
 template <typename T>
 __global__ void __launch_bounds__(256)
 stats_jobs_kernel(const StatsJob* __restrict__ jobs, const int* __restrict__ first, int n) {
-  extern __shared__ float tile[];
+  extern __shared__ __align__(16) float tile[];
   const int j = job_of(first, n, blockIdx.x);
   const StatsJob& J = jobs[j];
   const int l = blockIdx.x - first[j];
-  block_stats_body<T>(static_cast<const T*>(J.img), J.pitch, J.W, J.H, J.r, J.z, J.isd, tile,
-                      l % J.gx, l / J.gx);
+  auto body = [&](auto rc) {
+    block_stats_body<T, decltype(rc)::value>(static_cast<const T*>(J.img), J.pitch, J.W, J.H, J.z,
+                                             J.isd, tile, l % J.gx, l / J.gx);
+  };
+  with_radius(J.r, body);                            // uniform
 }
 
 hipError_t launch_ncc_any(const Plan& P, const void* ref, const float* tar_w, const float* zX,
@@ -295,7 +322,8 @@ hipError_t launch_warp_jobs(stereo_dtype dt, const WarpJob* jobs, const int* fir
 hipError_t launch_stats_jobs(stereo_dtype dt, const StatsJob* jobs, const int* first, int n,
                              int blocks, int max_r, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
-  const size_t lds = stats_lds_bytes(max_r);
+  size_t lds = 0;
+  with_radius(max_r, [&](auto rc) { lds = StatGeom<decltype(rc)::value>::lds_bytes; });
   if (dt == STEREO_U8)
     hipLaunchKernelGGL(stats_jobs_kernel<uint8_t>, dim3(blocks), dim3(256), lds, s, jobs, first,
                        n);
@@ -365,27 +393,18 @@ hipError_t launch_block_stats2(const Plan& P, const void* ref, stereo_dtype dt,
                                float* zY, float* isdY, hipStream_t s) {
   const int SW = P.W + 2 * P.r;
   dim3 grid((SW + ST_TX - 1) / ST_TX, (P.H + ST_TY - 1) / ST_TY, 2);
-  const size_t lds = stats_lds_bytes(P.r);
-  if (dt == STEREO_U8)
-    hipLaunchKernelGGL(block_stats2_kernel<uint8_t>, grid, dim3(256), lds, s,
-                       (const uint8_t*)ref, ref_pitch, tarw, P.W, P.H, P.r, zX, isdX, zY, isdY);
-  else
-    hipLaunchKernelGGL(block_stats2_kernel<float>, grid, dim3(256), lds, s, (const float*)ref,
-                       ref_pitch, tarw, P.W, P.H, P.r, zX, isdX, zY, isdY);
-  return hipGetLastError();
-}
-
-hipError_t launch_block_stats(const Plan& P, const void* img, stereo_dtype dt,
-                              int64_t pitch, float* z, float* isd, hipStream_t s) {
-  const int SW = P.W + 2 * P.r;
-  dim3 grid((SW + ST_TX - 1) / ST_TX, (P.H + ST_TY - 1) / ST_TY);
-  const size_t lds = stats_lds_bytes(P.r);
-  if (dt == STEREO_U8)
-    hipLaunchKernelGGL(block_stats_kernel<uint8_t>, grid, dim3(256), lds, s,
-                       (const uint8_t*)img, pitch, P.W, P.H, P.r, z, isd);
-  else
-    hipLaunchKernelGGL(block_stats_kernel<float>, grid, dim3(256), lds, s,
-                       (const float*)img, pitch, P.W, P.H, P.r, z, isd);
+  if (P.r < 1 || P.r > STEREO_MAX_NCC_RADIUS) return hipErrorInvalidValue;
+  with_radius(P.r, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    if (dt == STEREO_U8)
+      hipLaunchKernelGGL((block_stats2_kernel<uint8_t, R>), grid, dim3(256),
+                         (StatGeom<R>::lds_bytes), s, (const uint8_t*)ref, ref_pitch, tarw, P.W,
+                         P.H, zX, isdX, zY, isdY);
+    else
+      hipLaunchKernelGGL((block_stats2_kernel<float, R>), grid, dim3(256),
+                         (StatGeom<R>::lds_bytes), s, (const float*)ref, ref_pitch, tarw, P.W,
+                         P.H, zX, isdX, zY, isdY);
+  });
   return hipGetLastError();
 }
 

@@ -157,3 +157,21 @@ def test_every_cost_tile_is_written(W, H, D, dtype):
             assert not np.isnan(got["dsub"]).any()
         for k in got:
             assert np.array_equal(got[k], want[k], equal_nan=True), (levels, k)
+
+
+@pytest.mark.parametrize("r", range(1, 9))
+@pytest.mark.parametrize("W,H", [(5, 3), (64 - 3, 16), (131, 37)])
+def test_block_statistics_of_every_radius(r, W, H):
+    """The statistics kernel has a form per block radius: costs of both
+    volumes at map sizes below, at and beyond its 64 x 16 tiles, within the
+    bound of the cost's FP32 arithmetic."""
+    D = 7
+    dtype = "u8" if r % 2 else "f32"
+    w = replace(_workload(2, W, H, D, dtype, perspective=False, delta_p=0.0), ncc_radius=r)
+    ref, tar = _pair(2, W, H, D, dtype)
+    ora = OS.match(ref, tar, w, keep_volumes=True)
+    plan = api.Plan.from_workload(w)
+    cR, cT = api.cost_volume(plan, torch.from_numpy(ref).cuda(),
+                             torch.from_numpy(np.asarray(tar, np.float32)).cuda())
+    PR.assert_cost_close(_host(cR), ora["C_R"], "C_R")
+    PR.assert_cost_close(_host(cT), ora["C_T"], "C_T")
