@@ -7,21 +7,41 @@
 namespace stereo {
 namespace {
 
-// One thread per pixel walks the levels in order; volume reads are
-// coalesced across the threads of a slice.
+// One thread per pixel walks the levels in order; volume reads are coalesced
+// across the threads of a slice.  Those reads bound it: kLev levels are in
+// flight while the kLev before are compared (1280x720, 64 levels, 236 MB: 75
+// -> 46 us, 5.1 TB/s; before, a level's read waited for the level before it.
+// Four pixels a thread by 16-byte reads: 46 us too).
 __global__ void __launch_bounds__(256)
-wta_kernel(const float* __restrict__ E, int W, int H, int D,
-           int16_t* __restrict__ dint, float* __restrict__ dsub) {
+wta_kernel(const float* __restrict__ E, int64_t HW, int D, int16_t* __restrict__ dint,
+           float* __restrict__ dsub) {
+  constexpr int kLev = 8;
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t HW = (int64_t)W * H;
   if (p >= HW) return;
   float bestE = 3.402823466e38f, Em = 0.0f, Ep = 0.0f, prev = 0.0f;
   int bestD = 0;
-  for (int d = 0; d < D; ++d) {
-    const float e = E[(int64_t)d * HW + p];
-    if (d == bestD + 1) Ep = e;
-    if (e < bestE) { Em = prev; bestE = e; bestD = d; }
-    prev = e;
+  auto load = [&](int d0, float (&e)[kLev]) {
+#pragma unroll
+    for (int k = 0; k < kLev; ++k) e[k] = E[(int64_t)min(d0 + k, D - 1) * HW + p];
+  };
+  auto walk = [&](int d0, const float (&e)[kLev]) {
+#pragma unroll
+    for (int k = 0; k < kLev; ++k) {
+      const int d = d0 + k;
+      if (d < D) {                                   // uniform
+        if (d == bestD + 1) Ep = e[k];
+        if (e[k] < bestE) { Em = prev; bestE = e[k]; bestD = d; }
+        prev = e[k];
+      }
+    }
+  };
+  float e0[kLev], e1[kLev];
+  load(0, e0);
+  for (int d0 = 0; d0 < D; d0 += 2 * kLev) {
+    load(d0 + kLev, e1);
+    walk(d0, e0);
+    load(d0 + 2 * kLev, e0);
+    walk(d0 + kLev, e1);
   }
   dint[p] = (int16_t)bestD;
   if (dsub) {
@@ -147,8 +167,8 @@ lr_jobs_kernel(const LrJob* __restrict__ jobs, const int* __restrict__ first, in
 hipError_t launch_wta(const Plan& P, const float* E, int16_t* dint, float* dsub,
                       hipStream_t s) {
   const int64_t HW = (int64_t)P.W * P.H;
-  hipLaunchKernelGGL(wta_kernel, dim3((unsigned)((HW + 255) / 256)), dim3(256), 0, s,
-                     E, P.W, P.H, P.D, dint, dsub);
+  hipLaunchKernelGGL(wta_kernel, dim3((unsigned)((HW + 255) / 256)), dim3(256), 0, s, E, HW, P.D,
+                     dint, dsub);
   return hipGetLastError();
 }
 

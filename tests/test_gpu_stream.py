@@ -175,3 +175,30 @@ def test_block_statistics_of_every_radius(r, W, H):
                              torch.from_numpy(np.asarray(tar, np.float32)).cuda())
     PR.assert_cost_close(_host(cR), ora["C_R"], "C_R")
     PR.assert_cost_close(_host(cT), ora["C_T"], "C_T")
+
+
+@pytest.mark.parametrize("D", [3, 7, 8, 9, 15, 16, 17, 24, 33, 64])
+def test_selection_over_chunks_of_levels(D):
+    """The materialised selection reads its levels in chunks of eight: first
+    minimum, sub-pixel offset and non-finite costs as a plain walk of the
+    levels gives them (the same FP32 arithmetic: equal)."""
+    H, W = 5, 67
+    rng = np.random.Generator(np.random.PCG64(D))
+    E = rng.integers(0, 9, (D, H, W)).astype(np.float32) / 8
+    E[rng.random(E.shape) < 0.1] = np.nan
+    E[rng.random(E.shape) < 0.05] = np.inf
+    E[:, 0, :3] = np.nan
+    best, at = np.full((H, W), np.finfo(np.float32).max, np.float32), np.zeros((H, W), int)
+    for d in range(D):
+        low = E[d] < best
+        best, at = np.where(low, E[d], best), np.where(low, d, at)
+    get = lambda d: np.take_along_axis(E, np.clip(d, 0, D - 1)[None], 0)[0]
+    with np.errstate(all="ignore"):
+        lo, hi = get(at - 1), get(at + 1)
+        den = 2 * lo + 2 * hi - 4 * best
+        off = np.where((at > 0) & (at < D - 1) & (den > 0), (lo - hi) / den, np.float32(0))
+    plan = api.Plan(api.make_params(W, H, D))
+    dint, dsub = api.wta_subpixel(plan, torch.from_numpy(E).cuda())
+    assert np.array_equal(_host(dint), at)
+    assert np.array_equal(_host(dsub), at.astype(np.float32) + off.astype(np.float32),
+                          equal_nan=True)
