@@ -34,6 +34,19 @@
 #include "internal.h"
 
 namespace stereo {
+namespace bilm {
+inline int cu_count_of_current_device() {
+  static int cache[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  if (cache[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cache[dev] = n;
+  }
+  return cache[dev];
+}
+}  // namespace bilm
 namespace bil {
 
 constexpr int kThreads = 512;
@@ -103,8 +116,10 @@ __device__ __forceinline__ float guide_at(const G* g, int64_t pitch, int x, int 
   return static_cast<float>(g[(int64_t)y * pitch + x]);
 }
 
+// Levels [lo, hi) of the pair (lo a multiple of DC; hi the same, or D); all of
+// them for the modes that carry a state over the levels.
 template <int R, int PX, int DC, int TYT, typename GT, int MODE>
-__device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0,
+__device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0, int lo, int hi,
                                                float4* lds4) {
   const float* __restrict__ C = a.C;
   const int64_t c_pitch = a.c_pitch;
@@ -168,7 +183,7 @@ __device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0,
   // element step from level d to d + 1 (the target volume also moves one
   // column to the right per level)
   const uint32_t step = (uint32_t)a.c_slice + (uint32_t)a.shift;
-  for (int d0 = 0; d0 < D; d0 += DC) {
+  for (int d0 = lo; d0 < hi; d0 += DC) {
     // ---- stage the cost halo of this chunk: quads of 4 consecutive levels.
     // Lanes run along columns (coalesced loads); offsets are 32-bit from a
     // uniform base.  Out-of-image halo entries are 0 (their weight is 0).
@@ -250,7 +265,7 @@ __device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0,
     for (int k = 0; k < PX2; ++k)
 #pragma unroll
       for (int j = 0; j < DC2; ++j) acc2[k][j] = 0.0f;
-    const bool first = (d0 == 0);
+    const bool first = (d0 == lo);
 
     for (int dy = 0; dy <= 2 * R; ++dy) {
       const int row = ty + dy;
@@ -459,10 +474,12 @@ __device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0,
 // 128 VGPRs; at 16 levels the LDS allows one.
 template <int R, int PX, int DC, int TYT, typename GT, int MODE>
 __global__ void __launch_bounds__(kThreads, DC == 8 ? 4 : 2)
-bilateral_kernel(BilPair a) {
+bilateral_kernel(BilPair a, int levels) {
   extern __shared__ float4 lds4[];
   using Gm = BilGeom<R, PX, DC, TYT>;
-  bilateral_tile<R, PX, DC, TYT, GT, MODE>(a, blockIdx.x * Gm::TW, blockIdx.y * Gm::TH, lds4);
+  const int lo = blockIdx.z * levels;
+  bilateral_tile<R, PX, DC, TYT, GT, MODE>(a, blockIdx.x * Gm::TW, blockIdx.y * Gm::TH, lo,
+                                           min(lo + levels, a.D), lds4);
 }
 
 // Persistent form: each workgroup takes tiles from a queue (an integer
@@ -481,7 +498,7 @@ bilateral_persistent_kernel(const BilPair* __restrict__ pairs, const int* __rest
     __syncthreads();                       // everyone has read the slot
     if (t >= n_tiles) break;
     const int* e = tiles + 3 * t;          // (pair, x0, y0)
-    bilateral_tile<R, PX, DC, TYT, GT, MODE>(pairs[e[0]], e[1], e[2], lds4);
+    bilateral_tile<R, PX, DC, TYT, GT, MODE>(pairs[e[0]], e[1], e[2], 0, pairs[e[0]].D, lds4);
     __syncthreads();
   }
 }
@@ -522,7 +539,26 @@ hipError_t launch_one(const Plan& P, const BilArgs& a, hipStream_t s) {
     attr_set = true;
   }
   dim3 grid((P.W + Gm::TW - 1) / Gm::TW, (P.H + Gm::TH - 1) / Gm::TH);
-  hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, s, make_pair(P, a));
+  const BilPair b = make_pair(P, a);
+  int levels = (b.D + DC - 1) / DC * DC;
+  if (MODE == 0 || MODE == 4) {
+    // The levels in grid.z parts where that evens out the CUs' shares: a part
+    // of per chunks costs per + 0.05 (every chunk forms its own weights
+    // anyway), two workgroups share a CU, one alone takes 0.62 of the pair's
+    // time.  640x480, D = 48, R = 5 (300 tiles of 256 CUs): 148 us whole, 133 /
+    // 111 / 118 in 2 / 3 / 6 parts; 640x360, D = 30: 76, 66 in 2; 1280x720, D =
+    // 64, R = 7: 647, 622 / 605 / 597 in 2 / 3 / 8; 960x540: the same within 4 %.
+    const int n = levels / DC, c = bilm::cu_count_of_current_device(), cus = c > 0 ? c : 256;
+    const long tiles = (long)grid.x * grid.y;
+    double best = 1e30;
+    for (int per = n; per >= 1; --per) {
+      const int z = (n + per - 1) / per;
+      const long m = (tiles * z + cus - 1) / cus;      // workgroups of the fullest CU
+      const double cost = (double)(m / 2) * (per + 0.05) + (m & 1 ? 0.62 * (per + 0.05) : 0.0);
+      if (cost < best) { best = cost; levels = per * DC; grid.z = z; }
+    }
+  }
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, s, b, levels);
   return hipGetLastError();
 }
 

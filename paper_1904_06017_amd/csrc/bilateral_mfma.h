@@ -537,18 +537,6 @@ agg_wta_mfma_kernel(View one, const BilPair* __restrict__ pairs, const int* __re
   }
 }
 
-inline int cu_count_of_current_device() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (cache[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    cache[dev] = n;
-  }
-  return cache[dev];
-}
-
 template <int R, typename GT, int QUEUE, int MODE>
 hipError_t set_lds_attr() {
   static bool done = false;

@@ -202,3 +202,25 @@ def test_selection_over_chunks_of_levels(D):
     assert np.array_equal(_host(dint), at)
     assert np.array_equal(_host(dsub), at.astype(np.float32) + off.astype(np.float32),
                           equal_nan=True)
+
+
+@pytest.mark.parametrize("W,H,D,levels", [(31, 9, 3, 8), (33, 40, 8, 8), (70, 65, 9, 8), (64, 33, 40, 8),
+                                          (129, 50, 17, 16), (90, 70, 48, 16), (640, 480, 31, 8)])
+def test_aggregation_in_level_parts(W, H, D, levels):
+    """The materialised aggregation cuts its levels into parts by the number
+    of tiles; a level's sum is the same in every cut: equal to the aggregation
+    of that level among eight, alone in its part."""
+    w = _workload(4, W, H, D, "u8")
+    ref, _ = _pair(4, W, H, D, "u8")
+    rng = np.random.Generator(np.random.PCG64(D))
+    cost = torch.from_numpy(rng.random((D, H, W), dtype=np.float32)).cuda()
+    guide = torch.from_numpy(ref).cuda()
+    plan = api.Plan.from_workload(w)
+    plan.set_tuning("agg_levels_u8", levels)
+    whole = _host(api.bilateral_aggregate(plan, guide, cost))
+    few = api.Plan.from_workload(replace(w, num_disp=8))
+    few.set_tuning("agg_levels_u8", 8)
+    for d in {0, D // 2, D - 1}:
+        part = torch.zeros(8, H, W, device="cuda")
+        part[d % 8] = cost[d]
+        assert np.array_equal(whole[d], _host(api.bilateral_aggregate(few, guide, part))[d % 8])
