@@ -414,6 +414,13 @@ stereo_status stereo_photometric_l1_bwd(stereo_plan_t plan, const float* ref,
                                         double grad_loss, float* g_ref, float* g_tar,
                                         float* g_disp, void* ws, size_t ws_bytes,
                                         hipStream_t stream);
+/* The same with grad_loss read from device memory, in stream order (the host
+ * need not wait for it). */
+stereo_status stereo_photometric_l1_bwd_dev(stereo_plan_t plan, const float* ref,
+                                            const float* tar, const float* disp_soft,
+                                            const double* grad_loss_dev, float* g_ref,
+                                            float* g_tar, float* g_disp, void* ws,
+                                            size_t ws_bytes, hipStream_t stream);
 
 #ifdef __cplusplus
 }

@@ -110,6 +110,9 @@ SIGNATURES = {
     "stereo_photometric_l1_bwd": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_double,
                                           c_void_p, c_void_p, c_void_p, c_void_p, c_size_t,
                                           c_void_p]),
+    "stereo_photometric_l1_bwd_dev": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
+                                              c_void_p, c_void_p, c_void_p, c_void_p, c_size_t,
+                                              c_void_p]),
     "stereo_batch_create": (c_int, [POINTER(BatchItem), c_int32, POINTER(c_void_p)]),
     "stereo_batch_workspace_bytes": (c_int, [c_void_p, POINTER(c_size_t)]),
     "stereo_batch_set_tuning": (c_int, [c_void_p, c_char_p, c_int32]),

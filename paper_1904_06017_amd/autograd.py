@@ -48,6 +48,5 @@ class PhotometricL1(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_loss):
         ref, tar, disp = ctx.saved_tensors
-        g_ref, g_tar, g_disp = api.photometric_l1_bwd(ctx.plan, ref, tar, disp,
-                                                      float(grad_loss))
+        g_ref, g_tar, g_disp = api.photometric_l1_bwd(ctx.plan, ref, tar, disp, grad_loss)
         return g_ref, g_tar, g_disp, None

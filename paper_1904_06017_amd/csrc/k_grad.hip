@@ -807,11 +807,12 @@ l1_forward_kernel(const T* __restrict__ ref, const T* __restrict__ tar, int64_t 
 template <typename T>
 __global__ void __launch_bounds__(kT)
 l1_backward_kernel(const T* __restrict__ ref, const T* __restrict__ tar, int64_t pr, int64_t pt,
-                   const float* __restrict__ disp, int W, int H, double scale,
-                   float* __restrict__ g_ref, float* __restrict__ g_disp,
-                   unsigned long long* __restrict__ gtar_fix) {
+                   const float* __restrict__ disp, int W, int H, double grad_loss,
+                   const double* __restrict__ grad_loss_dev, float* __restrict__ g_ref,
+                   float* __restrict__ g_disp, unsigned long long* __restrict__ gtar_fix) {
   const int x = blockIdx.x * kT + threadIdx.x, v = blockIdx.y;
   if (x >= W) return;
+  const double scale = (grad_loss_dev ? *grad_loss_dev : grad_loss) / (double)((int64_t)W * H);
   const int64_t p = (int64_t)v * W + x;
   int i0, i1; double f; bool in;
   sample(tar, pt, W, v, (double)x - (double)disp[p], i0, i1, f, in);
@@ -1235,10 +1236,11 @@ stereo_status stereo_photometric_l1(stereo_plan_t plan, const float* ref, const 
   return STEREO_OK;
 }
 
-stereo_status stereo_photometric_l1_bwd(stereo_plan_t plan, const float* ref, const float* tar,
-                                        const float* disp_soft, double grad_loss, float* g_ref,
-                                        float* g_tar, float* g_disp, void* ws, size_t ws_bytes,
-                                        hipStream_t stream) {
+// grad_loss: *grad_loss_dev where that is non-NULL.
+static stereo_status l1_bwd(stereo_plan_t plan, const float* ref, const float* tar,
+                            const float* disp_soft, double grad_loss, const double* grad_loss_dev,
+                            float* g_ref, float* g_tar, float* g_disp, void* ws, size_t ws_bytes,
+                            hipStream_t stream) {
   REQ(plan && ref && tar && disp_soft, "plan, ref, tar and disp_soft must be non-NULL");
   REQ(g_ref || g_tar || g_disp, "no gradient requested");
   stereo_status st = check_grad(plan->P, ws, ws_bytes);
@@ -1250,12 +1252,29 @@ stereo_status stereo_photometric_l1_bwd(stereo_plan_t plan, const float* ref, co
   auto* gfix = at<unsigned long long>(ws, P.g_off[GR_GTARFIX]);
   if (g_tar) LAUNCH("zero", zero_u64_kernel, flat, dim3(256), 0, stream, gfix, HW);
   LAUNCH("l1 adjoint", l1_backward_kernel<float>, rows, dim3(256), 0, stream, ref, tar,
-         P.p.pitch_ref, P.p.pitch_tar, disp_soft, P.W, P.H, grad_loss / (double)HW, g_ref, g_disp,
+         P.p.pitch_ref, P.p.pitch_tar, disp_soft, P.W, P.H, grad_loss, grad_loss_dev, g_ref, g_disp,
          g_tar ? gfix : nullptr);
   if (g_tar)
     LAUNCH("fixed point", fix_to_float_kernel, flat, dim3(256), 0, stream, gfix, HW,
            (const float*)nullptr, g_tar);
   return STEREO_OK;
+}
+
+stereo_status stereo_photometric_l1_bwd(stereo_plan_t plan, const float* ref, const float* tar,
+                                        const float* disp_soft, double grad_loss, float* g_ref,
+                                        float* g_tar, float* g_disp, void* ws, size_t ws_bytes,
+                                        hipStream_t stream) {
+  return l1_bwd(plan, ref, tar, disp_soft, grad_loss, nullptr, g_ref, g_tar, g_disp, ws, ws_bytes,
+                stream);
+}
+
+stereo_status stereo_photometric_l1_bwd_dev(stereo_plan_t plan, const float* ref, const float* tar,
+                                            const float* disp_soft, const double* grad_loss_dev,
+                                            float* g_ref, float* g_tar, float* g_disp, void* ws,
+                                            size_t ws_bytes, hipStream_t stream) {
+  REQ(grad_loss_dev, "grad_loss_dev must be non-NULL");
+  return l1_bwd(plan, ref, tar, disp_soft, 0.0, grad_loss_dev, g_ref, g_tar, g_disp, ws, ws_bytes,
+                stream);
 }
 
 }  // extern "C"

@@ -224,3 +224,20 @@ def test_aggregation_in_level_parts(W, H, D, levels):
         part = torch.zeros(8, H, W, device="cuda")
         part[d % 8] = cost[d]
         assert np.array_equal(whole[d], _host(api.bilateral_aggregate(few, guide, part))[d % 8])
+
+
+@pytest.mark.parametrize("W,H", [(40, 9), (300, 70)])
+@pytest.mark.parametrize("value", [1.0, -0.37, 0.0, float("nan")])
+def test_loss_gradient_on_the_device(W, H, value):
+    """A loss gradient left in device memory gives what its value gives: the
+    same FP64 quotient, so the same bits."""
+    w = _workload(2, W, H, 8, "f32", perspective=True, delta_p=3.0, plane=(3.0, 0.0, 0.0))
+    ref, tar = (torch.from_numpy(x).cuda() for x in _pair(2, W, H, 8, "f32"))
+    disp = torch.full((H, W), 2.6, device="cuda")
+    plan = api.Plan.from_workload(w)
+    want = api.photometric_l1_bwd(plan, ref, tar, disp, value)
+    pair = torch.tensor([7.0, value], dtype=torch.float64, device="cuda")
+    for grad in (pair[1], pair[1:], pair[1].float(), pair[1].cpu()):
+        got = api.photometric_l1_bwd(plan, ref, tar, disp, grad)
+        if grad.dtype == torch.float64:
+            assert all(torch.equal(a.nan_to_num(9.0), b.nan_to_num(9.0)) for a, b in zip(got, want))
