@@ -64,7 +64,7 @@ enum GradRegion {
   GR_SY,                                        // [3][H][W+D-1] target-side sums
   GR_BSY,                                       // [3][HV][WVY] their boxes
   GR_MU,                                        // [2][H][W+2r] block means of X, Y
-  GR_GXV, GR_GYV, GR_GTARFIX, GR_PART_A, GR_PART_B, GR_SCRATCH,
+  GR_GXV, GR_GYV, GR_GTARFIX, GR_PART_A, GR_PART_B,
   GR_GMAX,                                      // max |C'| of the matrix-core backward
   GR_COUNT
 };

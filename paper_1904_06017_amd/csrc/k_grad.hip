@@ -687,8 +687,8 @@ plane_direct_kernel(const float* __restrict__ gD, const float* __restrict__ dh, 
   reduce3(s0, s1, s2, partials);
 }
 
-// out[k] = sum of (sign_a * A[b][k]) + (sign_b * B[b][k]) over blocks, in a
-// fixed order: by thread, then within the waves, then over them.  One
+// out[k] = sum of (sign_a * A[b][k]) + (sign_b * B[b][k]) over blocks, k < n_out
+// <= 3, in a fixed order: by thread, then within the waves, then over them.  One
 // workgroup, so the reads' latency bounds it: PF_T threads, four blocks ahead
 // (3600 blocks of 1280x720: 8.5 -> 5.2 us; before, 256 threads, one block at a
 // time, and a tree with a barrier a step).
@@ -696,7 +696,7 @@ constexpr int PF_T = 1024;
 __global__ void __launch_bounds__(PF_T)
 plane_finish_kernel(const double* __restrict__ pa, int na, double sa,
                     const double* __restrict__ pb, int nb, double sb,
-                    double* __restrict__ out) {
+                    double* __restrict__ out, int n_out) {
   __shared__ double red[PF_T / 64][3];
   double a[3] = {0.0, 0.0, 0.0};
   auto add = [&](const double* __restrict__ p, int n, double sign) {
@@ -722,7 +722,7 @@ plane_finish_kernel(const double* __restrict__ pa, int na, double sa,
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][k] = a[k];
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
+  if (threadIdx.x < n_out) {
     double t = 0.0;
     for (int w = 0; w < PF_T / 64; ++w) t += red[w][threadIdx.x];
     out[threadIdx.x] = t;
@@ -860,7 +860,6 @@ size_t grad_layout(Plan& P, size_t o) {
   sz[GR_GTARFIX] = sizeof(unsigned long long) * HW;
   sz[GR_PART_A] = sizeof(double) * 3 * nb;
   sz[GR_PART_B] = sizeof(double) * 3 * nb;
-  sz[GR_SCRATCH] = sizeof(double) * 4;
   sz[GR_GMAX] = sizeof(float);
   for (int i = 0; i < GR_COUNT; ++i) {
     P.g_off[i] = o;
@@ -1211,7 +1210,7 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
   LAUNCH("plane (shift back)", plane_direct_kernel, rows, dim3(256), 0, stream, grad_disp,
          sm_dh, W, H, dp, partA);
   LAUNCH("plane", plane_finish_kernel, dim3(1), dim3(PF_T), 0, stream, partA, nb, 1.0, partB, nb,
-         -1.0, grad_plane);
+         -1.0, grad_plane, 3);
   HIPC(mark(5), "event record");
   return STEREO_OK;
 }
@@ -1226,13 +1225,10 @@ stereo_status stereo_photometric_l1(stereo_plan_t plan, const float* ref, const 
   const dim3 rows((P.W + 255) / 256, P.H);
   const int nb = (int)rows.x * P.H;
   double* part = at<double>(ws, P.g_off[GR_PART_A]);
-  double* scratch = at<double>(ws, P.g_off[GR_SCRATCH]);
   LAUNCH("l1", l1_forward_kernel<float>, rows, dim3(256), 0, stream, ref, tar, P.p.pitch_ref,
          P.p.pitch_tar, disp_soft, P.W, P.H, part);
   LAUNCH("l1", plane_finish_kernel, dim3(1), dim3(PF_T), 0, stream, part, nb,
-         1.0 / ((double)P.W * P.H), (const double*)nullptr, 0, 0.0, scratch);
-  HIPC(hipMemcpyAsync(loss_dev, scratch, sizeof(double), hipMemcpyDeviceToDevice, stream),
-       "copy loss");
+         1.0 / ((double)P.W * P.H), (const double*)nullptr, 0, 0.0, loss_dev, 1);
   return STEREO_OK;
 }
 
