@@ -29,7 +29,7 @@ __device__ __forceinline__ float gld(const T* p) {
 //   C = 1 - (S/n - muX muY) / (sdX sdY) = 1 + zX zY - (S/n) isdX isdY,
 // S = sum over the block of X' Y', z = mu / sd, isd = 1 / sd.
 // A workgroup covers NC_TX = 64 output columns (one per lane, conflict-free
-// LDS rows) x NC_TY rows x NC_DC levels (NC_DW per wave).  Each lane walks
+// LDS rows) x TY rows x NC_DC levels (NC_DW per wave).  Each lane walks
 // down its column: for every input row it forms the horizontal sum of the
 // 2r+1 products (fixed order j = -r..r) and keeps the last 2r+1 row sums in a
 // register ring; the block sum is the fixed-order sum of that ring
@@ -41,23 +41,22 @@ __device__ __forceinline__ float gld(const T* p) {
 // per row) and the A side's at the lanes' own columns are staged in LDS with
 // clamped reads.  A wave's NC_DW levels read overlapping windows of the same
 // B row: one window of K + NC_DW - 1 values serves them all.  8-row tiles
-// redo 2r of every 8 + 2r input rows but need a quarter of the LDS of
-// 32-row ones, so more workgroups stay resident to overlap the stores
-// (1280x720, 64 levels, r = 3, both split volumes: 0.111 ms against 0.113 /
-// 0.114 / 0.131 ms with 12- / 16- / 32-row tiles).
+// redo 2r of every 8 + 2r input rows but need a quarter of the LDS of 32-row
+// ones, so more workgroups stay resident to overlap the stores; large launches
+// take 16 rows (kTallWaves).
 constexpr int NC_TX = 64, NC_TY = 8, NC_DC = 16, NC_DW = 4;
 // NC_DC is the default level block; a workgroup of DC levels has DC / 4 waves.
 
-template <int r, int DC = NC_DC>
+template <int r, int DC = NC_DC, int TY = NC_TY>
 struct NccGeom {
   static constexpr int K = 2 * r + 1;
-  static constexpr int ROWS = NC_TY + 2 * r;
+  static constexpr int ROWS = TY + 2 * r;
   static constexpr int AW = NC_TX + 2 * r;
   static constexpr int BW = NC_TX + 2 * r + DC - 1;
   static constexpr int ZW = NC_TX + DC - 1;         // B-side statistics per output row
   // A, B, the B side's and the A side's statistics of the output rows
   static constexpr size_t lds_bytes =
-      sizeof(float) * ((size_t)ROWS * (AW + BW) + 2 * (size_t)NC_TY * (ZW + NC_TX));
+      sizeof(float) * ((size_t)ROWS * (AW + BW) + 2 * (size_t)TY * (ZW + NC_TX));
 };
 
 // QUAD = 1 writes the level-quad-interleaved layout [levels/4][H][pitch]
@@ -172,7 +171,7 @@ __device__ __forceinline__ void ncc_stage(int tid, Get get, Put put) {
 // The anchor is a template parameter: it fixes which register of the B
 // window each level's products read, so the window stays in plain registers
 // (a run-time choice turns every read into an indexed register move).
-template <int r, typename T, int QUAD, int DC, int anchor>
+template <int r, typename T, int QUAD, int DC, int TY, int anchor>
 __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t ref_pitch,
                                            const float* __restrict__ tarw, int W, int H,
                                            int d_first, int d_end,
@@ -183,20 +182,20 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
                                            float* __restrict__ C, int out_w, int64_t out_pitch,
                                            int64_t out_slice, int pad, float* sm, int bx,
                                            int by, int bz, float* __restrict__ C2) {
-  using G = NccGeom<r, DC>;
+  using G = NccGeom<r, DC, TY>;
   constexpr int K = G::K;
   float* As = sm;                         // [ROWS][AW]
   float* Bs = sm + G::ROWS * G::AW;       // [ROWS][BW]
-  float* Zs = Bs + G::ROWS * G::BW;       // [NC_TY][ZW]: z of the B side
-  float* Is = Zs + NC_TY * G::ZW;         // [NC_TY][ZW]: 1/sd of the B side
-  float* ZA = Is + NC_TY * G::ZW;         // [NC_TY][NC_TX]: z of the A side at the lanes
-  float* IA = ZA + NC_TY * NC_TX;         // [NC_TY][NC_TX]: 1/sd of the A side / K^2
+  float* Zs = Bs + G::ROWS * G::BW;       // [TY][ZW]: z of the B side
+  float* Is = Zs + TY * G::ZW;         // [TY][ZW]: 1/sd of the B side
+  float* ZA = Is + TY * G::ZW;         // [TY][NC_TX]: z of the A side at the lanes
+  float* IA = ZA + TY * NC_TX;         // [TY][NC_TX]: 1/sd of the A side / K^2
   const float inv_n = 1.0f / (float)(K * K);
   // split-FP16 output: the tile starts pad columns left of 64 bx, so that
   // lane l writes stored column 64 bx + l and a lane quad is a column quad
   const int x0 = QUAD == 4 ? bx * NC_TX4 - pad : bx * NC_TX - (QUAD >= 2 ? pad : 0);
   const int rsh = QUAD >= 2 ? pad & 1 : 0;           // row shift of the stored volume
-  const int y0 = by * NC_TY - rsh;
+  const int y0 = by * TY - rsh;
   const int d0 = d_first + bz * DC;
   const int SW = W + 2 * r;
   // image column of A[.][0] and B[.][0]
@@ -229,7 +228,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   // B-side statistics: entry c of output row t is the block centred at image
   // column zxo + c (clamped to the map's [-r, W - 1 + r]), the centre that
   // level offset boff reads for lane c - boff
-  ncc_stage<NC_TY * G::ZW, NT>(tid, [&](int i) {
+  ncc_stage<TY * G::ZW, NT>(tid, [&](int i) {
     const int t = i / G::ZW, c = i - t * G::ZW;
     const int64_t rowo = (int64_t)min(max(y0 + t, 0), H - 1) * SW;
     const int cb = min(max(zxo + c, -r), W - 1 + r) + r;
@@ -238,7 +237,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   // A-side statistics of each lane's own column (in LDS, so that the row
   // loop issues no global loads: their wait would also wait for the previous
   // rows' stores)
-  ncc_stage<NC_TY * NC_TX, NT>(tid, [&](int i) {
+  ncc_stage<TY * NC_TX, NT>(tid, [&](int i) {
     const int t = i / NC_TX, c = i - t * NC_TX;
     const int64_t rowo = (int64_t)min(max(y0 + t, 0), H - 1) * SW;
     const int cb = min(max(x0 + c, -r), W - 1 + r) + r;
@@ -382,7 +381,7 @@ __device__ __forceinline__ void ncc_body_a(const T* __restrict__ ref, int64_t re
   }
 }
 
-template <int r, typename T, int QUAD, int DC>
+template <int r, typename T, int QUAD, int DC, int TY>
 __device__ __forceinline__ void ncc_body(const T* __restrict__ ref, int64_t ref_pitch,
                                          const float* __restrict__ tarw, int W, int H,
                                          int d_first, int d_end,
@@ -395,10 +394,10 @@ __device__ __forceinline__ void ncc_body(const T* __restrict__ ref, int64_t ref_
                                          int by, int bz, float* __restrict__ C2 = nullptr) {
   // the both-anchors form always runs from the reference anchor
   if (QUAD != 4 && anchor)
-    ncc_body_a<r, T, QUAD, DC, 1>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY,
+    ncc_body_a<r, T, QUAD, DC, TY, 1>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY,
                                   isdY, C, out_w, out_pitch, out_slice, pad, sm, bx, by, bz, C2);
   else
-    ncc_body_a<r, T, QUAD, DC, 0>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY,
+    ncc_body_a<r, T, QUAD, DC, TY, 0>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY,
                                   isdY, C, out_w, out_pitch, out_slice, pad, sm, bx, by, bz, C2);
 }
 
@@ -420,7 +419,7 @@ struct NccGrid {                        // grid: 8 chunk x level blocks x runs
 };
 constexpr int64_t kRunBytes = 3 << 20;
 
-template <int r, typename T, int QUAD, int DC>
+template <int r, typename T, int QUAD, int DC, int TY>
 __global__ void __launch_bounds__(16 * DC)
 ncc_kernel(const T* __restrict__ ref, int64_t ref_pitch,
            const float* __restrict__ tarw, int W, int H, int d_first, int d_end,
@@ -432,7 +431,7 @@ ncc_kernel(const T* __restrict__ ref, int64_t ref_pitch,
   const int i = blockIdx.z * g.chunk + (blockIdx.x >> 3);
   const int t = (int)(blockIdx.x & 7) * g.step_x + i * g.step, by = t / g.nx;
   if (i >= g.per || t >= g.tiles) return;            // uniform
-  ncc_body<r, T, QUAD, DC>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY, isdY, C,
+  ncc_body<r, T, QUAD, DC, TY>(ref, ref_pitch, tarw, W, H, d_first, d_end, zX, isdX, zY, isdY, C,
                        out_w, out_pitch, out_slice, anchor, pad, sm, t - by * g.nx, by,
                        blockIdx.y, C2);
 }
@@ -463,7 +462,7 @@ ncc_jobs_kernel(const NccJob* __restrict__ jobs, const int* __restrict__ first, 
   const int l = blockIdx.x - first[j];
   const int gxy = J.gx * J.gy;
   const int bz = l / gxy, rem = l - bz * gxy;
-  ncc_body<r, T, 1, DC>(static_cast<const T*>(J.ref), J.ref_pitch, J.tarw, J.W, J.H, J.d_first,
+  ncc_body<r, T, 1, DC, NC_TY>(static_cast<const T*>(J.ref), J.ref_pitch, J.tarw, J.W, J.H, J.d_first,
                         J.d_end, J.zX, J.isdX, J.zY, J.isdY,
                         reinterpret_cast<float*>(base + J.c_off), J.out_w, J.out_pitch,
                         J.out_slice, 0, 0, sm, rem % J.gx, rem / J.gx, bz);
@@ -471,13 +470,13 @@ ncc_jobs_kernel(const NccJob* __restrict__ jobs, const int* __restrict__ first, 
 
 // Dynamic LDS above the 64 KB default (large radii at 64 levels), set once
 // per kernel instantiation.
-template <int r, typename T, int QUAD, int DC, int JOBS>
+template <int r, typename T, int QUAD, int DC, int TY, int JOBS>
 hipError_t ncc_allow_lds() {
   static bool done = false;
-  constexpr size_t bytes = NccGeom<r, DC>::lds_bytes;
+  constexpr size_t bytes = NccGeom<r, DC, TY>::lds_bytes;
   if (!done && bytes > 64 * 1024) {
     const void* k = JOBS ? (const void*)ncc_jobs_kernel<r, T, DC>
-                         : (const void*)ncc_kernel<r, T, QUAD, DC>;
+                         : (const void*)ncc_kernel<r, T, QUAD, DC, TY>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
   }
@@ -485,8 +484,8 @@ hipError_t ncc_allow_lds() {
   return hipSuccess;
 }
 
-template <int r, typename T, int DC>
-hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const float* zX,
+template <int r, typename T, int DC, int TY>
+hipError_t launch_ncc_ty(const Plan& P, const T* ref, const float* tar_w, const float* zX,
                           const float* isdX, const float* zY, const float* isdY, float* C,
                           int out_w, int64_t out_pitch, int64_t out_slice, int anchor,
                           int d_first, int d_end, int quad, int pad,
@@ -495,10 +494,10 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
   const int tx = quad == 4 ? NC_TX4 : NC_TX;
   NccGrid g;
   g.nx = (out_w + tx - 1) / tx;
-  g.tiles = g.nx * ((rows + NC_TY - 1) / NC_TY);
+  g.tiles = g.nx * ((rows + TY - 1) / TY);
   g.per = (g.tiles + 7) / 8;
   // ref, tarw and four statistics a pixel
-  const int64_t bytes = (int64_t)g.per * tx * NC_TY * (sizeof(T) + 5 * sizeof(float));
+  const int64_t bytes = (int64_t)g.per * tx * TY * (sizeof(T) + 5 * sizeof(float));
   const int runs = quad >= 2 ? (int)std::min<int64_t>((bytes + kRunBytes - 1) / kRunBytes, g.per) : 1;
   g.step_x = quad >= 2 ? g.per : 1;
   g.step = quad >= 2 ? 1 : 8;
@@ -506,10 +505,10 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
   const dim3 grid(8 * g.chunk, (d_end - d_first + DC - 1) / DC, (g.per + g.chunk - 1) / g.chunk);
   if (quad == 4) {
     // both anchors' split volumes (C, and C2 when non-NULL)
-    hipError_t e = ncc_allow_lds<r, T, 4, DC, 0>();
+    hipError_t e = ncc_allow_lds<r, T, 4, DC, TY, 0>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ncc_kernel<r, T, 4, DC>), grid, dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
+    hipLaunchKernelGGL((ncc_kernel<r, T, 4, DC, TY>), grid, dim3(16 * DC),
+                       (NccGeom<r, DC, TY>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
                        0, pad, C2, g);
     return hipGetLastError();
@@ -517,35 +516,61 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
   if (quad == 3) {
     // split-FP16 and planar FP32 outputs in one pass (FP32 images only)
     if constexpr (std::is_same<T, float>::value) {
-      hipError_t e = ncc_allow_lds<r, T, 3, DC, 0>();
+      hipError_t e = ncc_allow_lds<r, T, 3, DC, TY, 0>();
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((ncc_kernel<r, T, 3, DC>), grid, dim3(16 * DC),
-                         (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
+      hipLaunchKernelGGL((ncc_kernel<r, T, 3, DC, TY>), grid, dim3(16 * DC),
+                         (NccGeom<r, DC, TY>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                          d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
                          anchor, pad, C2, g);
       return hipGetLastError();
     }
     return hipErrorInvalidValue;
   }
-  hipError_t e = quad == 2 ? ncc_allow_lds<r, T, 2, DC, 0>()
-                 : quad ? ncc_allow_lds<r, T, 1, DC, 0>() : ncc_allow_lds<r, T, 0, DC, 0>();
+  hipError_t e = quad == 2 ? ncc_allow_lds<r, T, 2, DC, TY, 0>()
+                 : quad ? ncc_allow_lds<r, T, 1, DC, TY, 0>() : ncc_allow_lds<r, T, 0, DC, TY, 0>();
   if (e != hipSuccess) return e;
   if (quad == 2)
-    hipLaunchKernelGGL((ncc_kernel<r, T, 2, DC>), grid, dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
+    hipLaunchKernelGGL((ncc_kernel<r, T, 2, DC, TY>), grid, dim3(16 * DC),
+                       (NccGeom<r, DC, TY>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
                        anchor, pad, (float*)nullptr, g);
   else if (quad)
-    hipLaunchKernelGGL((ncc_kernel<r, T, 1, DC>), grid, dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
+    hipLaunchKernelGGL((ncc_kernel<r, T, 1, DC, TY>), grid, dim3(16 * DC),
+                       (NccGeom<r, DC, TY>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
                        anchor, 0, (float*)nullptr, g);
   else
-    hipLaunchKernelGGL((ncc_kernel<r, T, 0, DC>), grid, dim3(16 * DC),
-                       (NccGeom<r, DC>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
+    hipLaunchKernelGGL((ncc_kernel<r, T, 0, DC, TY>), grid, dim3(16 * DC),
+                       (NccGeom<r, DC, TY>::lds_bytes), s, ref, P.p.pitch_ref, tar_w, P.W, P.H,
                        d_first, d_end, zX, isdX, zY, isdY, C, out_w, out_pitch, out_slice,
                        anchor, 0, (float*)nullptr, g);
   return hipGetLastError();
+}
+
+// Rows of a tile: 16 redo 2r of 16 + 2r input rows instead of 2r of 8 + 2r, but
+// make half as many workgroups.  They pay from kTallWaves waves of 16-row tiles
+// on, about a full residency of the chip: frames of 1280x720, 64 levels (17 000
+// waves) 534 -> 520 us, 1917x1075, 96 levels 1940 -> 1900 us, both planar volumes
+// at 1280x720 144 -> 135 us; below it 8 rows are faster: 640x360, 32 levels (2200
+// waves) 100.7 against 105.4 us, 320x240 55.0 against 61.1 us.
+constexpr int64_t kTallWaves = 8192;
+
+template <int r, typename T, int DC>
+hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const float* zX,
+                          const float* isdX, const float* zY, const float* isdY, float* C,
+                          int out_w, int64_t out_pitch, int64_t out_slice, int anchor,
+                          int d_first, int d_end, int quad, int pad,
+                          hipStream_t s, float* C2) {
+  const int tx = quad == 4 ? NC_TX4 : NC_TX;
+  const int64_t waves = (int64_t)((out_w + tx - 1) / tx) * ((P.H + 15) / 16) *
+                        ((d_end - d_first + DC - 1) / DC) * (DC / NC_DW);
+  auto go = [&](auto ty) {
+    return launch_ncc_ty<r, T, DC, decltype(ty)::value>(P, ref, tar_w, zX, isdX, zY, isdY, C, out_w,
+                                                        out_pitch, out_slice, anchor, d_first,
+                                                        d_end, quad, pad, s, C2);
+  };
+  return waves >= kTallWaves ? go(std::integral_constant<int, 16>{})
+                             : go(std::integral_constant<int, NC_TY>{});
 }
 
 template <int r, typename T>
@@ -582,7 +607,7 @@ hipError_t launch_ncc_r(const Plan& P, const T* ref, const float* tar_w, const f
 template <int r, typename T, int DC>
 hipError_t ncc_jobs_rdc(const NccJob* jobs, const int* first, int n, int blocks, char* base,
                         hipStream_t s) {
-  hipError_t e = ncc_allow_lds<r, T, 1, DC, 1>();
+  hipError_t e = ncc_allow_lds<r, T, 1, DC, NC_TY, 1>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((ncc_jobs_kernel<r, T, DC>), dim3(blocks), dim3(16 * DC),
                      (NccGeom<r, DC>::lds_bytes), s, jobs, first, n, base);
