@@ -118,25 +118,17 @@ __device__ Fit alpha_cs(const Mom& m, double c, double s) {
   return f;
 }
 
-// The plane at one angle: its parameters, the energy and the gradient.
-struct At {
-  double s, c, energy;
-  Fit f;
-};
-
-__device__ At at_angle(const Mom& m, double psi) {
-  At r;
-  sincos(psi, &r.s, &r.c);
-  r.f = alpha_cs(m, r.c, r.s);
-  r.energy = m.sdd - (r.f.a0 * m.sd + r.f.a1 * r.f.sdy);
-  return r;
+__device__ double energy_cs(const Mom& m, double c, double s) {
+  const Fit f = alpha_cs(m, c, s);
+  return m.sdd - (f.a0 * m.sd + f.a1 * f.sdy);
 }
 
-__device__ double gradient(const Mom& m, const At& t) {
-  const double syp = -t.s * m.sv - t.c * m.su;
-  const double syyp = t.s * t.c * (m.suu - m.svv) + (t.s * t.s - t.c * t.c) * m.suv;
-  const double sdyp = -t.s * m.sdv - t.c * m.sdu;
-  return -2.0 * t.f.a1 * (sdyp - t.f.a0 * syp - t.f.a1 * syyp);
+__device__ double gradient_cs(const Mom& m, double c, double s) {
+  const Fit f = alpha_cs(m, c, s);
+  const double syp = -s * m.sv - c * m.su;
+  const double syyp = s * c * (m.suu - m.svv) + (s * s - c * c) * m.suv;
+  const double sdyp = -s * m.sdv - c * m.sdu;
+  return -2.0 * f.a1 * (sdyp - f.a0 * syp - f.a1 * syyp);
 }
 
 __device__ double wrap_half_pi(double psi) {
@@ -177,31 +169,33 @@ road_fit_kernel(const double* __restrict__ partials, int nblocks, int W, int H,
   r.pad_ = 0;
   double psi = psi0;
   int iters = 0, converged = 0, flat = 0;
-  At t{};
+  double sp, cp;                           // of psi
+  sincos(psi, &sp, &cp);
+  Fit f0;
   if (m.n < 3.0) {
     flat = 1; converged = 1;
-    t.f.a0 = m.n > 0.0 ? m.sd / m.n : 0.0;
-    t.f.a1 = 0.0;
+    f0.a0 = m.n > 0.0 ? m.sd / m.n : 0.0;
+    f0.a1 = 0.0;
   } else {
-    t = at_angle(m, psi0);
-    if (!(fabs(t.f.a1) >= 1e-6)) { flat = 1; converged = 1; }
+    f0 = alpha_cs(m, cp, sp);
+    if (!(fabs(f0.a1) >= 1e-6)) { flat = 1; converged = 1; }
   }
   if (!flat) {
     const double s = (double)max(W, H);
-    const double scale = 1.0 / (m.n * s * s * t.f.a1 * t.f.a1);
+    const double scale = 1.0 / (m.n * s * s * f0.a1 * f0.a1);
     double lam = lambda0;
-    double E = t.energy * scale;
-    double g = gradient(m, t) * scale;
+    double E = energy_cs(m, cp, sp) * scale;
+    double g = gradient_cs(m, cp, sp) * scale;
     const double pi = 3.14159265358979323846;
     for (iters = 1; iters <= max_iter; ++iters) {
       double step = -lam * g, psi_new = psi;
-      bool known = false;                  // t belongs to psi_new = psi + step
+      bool known = false;                  // psi_new, sp, cp belong to psi + step
       for (int h = 0; h < 64; ++h) {
         if (fabs(step) <= pi / 4.0) {
           psi_new = wrap_half_pi(psi + step);
-          t = at_angle(m, psi_new);
+          sincos(psi_new, &sp, &cp);
           known = true;
-          if (t.energy * scale <= E * (1.0 + 1e-9)) break;
+          if (energy_cs(m, cp, sp) * scale <= E * (1.0 + 1e-9)) break;
         }
         lam *= 0.5;
         step = -lam * g;
@@ -209,31 +203,31 @@ road_fit_kernel(const double* __restrict__ partials, int nblocks, int W, int H,
       }
       if (!known) {
         psi_new = wrap_half_pi(psi + step);
-        t = at_angle(m, psi_new);
+        sincos(psi_new, &sp, &cp);
       }
-      const double g_new = gradient(m, t) * scale;
+      const double g_new = gradient_cs(m, cp, sp) * scale;
       const bool done = fabs(step) < delta_psi;
-      psi = psi_new;
       if (g_new == g) {
-        converged = 1;
+        psi = psi_new; converged = 1;
         break;
       }
       lam = lam * g / (g - g_new);
       if (!(lam > 0.0) || isinf(lam)) lam = lambda0;
-      E = t.energy * scale;
+      psi = psi_new;
+      E = energy_cs(m, cp, sp) * scale;
       g = g_new;
       if (done) { converged = 1; break; }
     }
     if (iters > max_iter) iters = max_iter;
+    f0 = alpha_cs(m, cp, sp);
   }
-  const Fit f0 = t.f;
   r.psi = psi;
   r.alpha0 = f0.a0;
   r.alpha1 = f0.a1;
-  r.e_min = (m.n >= 3.0) ? t.energy : 0.0;
+  r.e_min = (m.n >= 3.0) ? energy_cs(m, cp, sp) : 0.0;
   r.plane[0] = f0.a0;
-  r.plane[1] = -f0.a1 * sin(psi);
-  r.plane[2] = f0.a1 * cos(psi);
+  r.plane[1] = -f0.a1 * sp;
+  r.plane[2] = f0.a1 * cp;
   r.iters = iters;
   r.converged = converged;
   r.flat = flat;
