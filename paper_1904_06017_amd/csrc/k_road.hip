@@ -146,7 +146,7 @@ __device__ double wrap_half_pi(double psi) {
 // it raises the normalised energy or exceeds pi/4; a non-positive rate
 // restarts at lambda0.  The lane's chain of sines, divisions and remainders
 // bounds the launch: each angle is worked out once, for its energy, its
-// gradient and as the next step's start (10.1 -> 5.7 us at 320x240; before,
+// gradient and as the next step's start (10.1 -> 5.9 us at 320x240; before,
 // three times, and the tree through LDS).
 __global__ void __launch_bounds__(kRoadThreads)
 road_fit_kernel(const double* __restrict__ partials, int nblocks, int W, int H,
