@@ -145,9 +145,11 @@ __device__ double wrap_half_pi(double psi) {
 // Eq. (28), lambda_k+1 = lambda_k g_k / (g_k - g_k+1); a step is halved while
 // it raises the normalised energy or exceeds pi/4; a non-positive rate
 // restarts at lambda0.  The lane's chain of sines, divisions and remainders
-// bounds the launch: each angle is worked out once, for its energy, its
-// gradient and as the next step's start (10.1 -> 5.9 us at 320x240; before,
-// three times, and the tree through LDS).
+// bounds the launch: each angle's sine and cosine are formed once, for its
+// energy, its gradient and as the next step's start (10.1 -> 5.9 us at 320x240;
+// before, three times, and the tree through LDS).  Energy and gradient stay
+// separate expressions: e_min cancels, and a plane shared by both, which the
+// compiler fuses otherwise, moved it by up to 3e-10.
 __global__ void __launch_bounds__(kRoadThreads)
 road_fit_kernel(const double* __restrict__ partials, int nblocks, int W, int H,
                 double psi0, double lambda0, double delta_psi, int max_iter,
