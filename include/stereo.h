@@ -384,7 +384,11 @@ stereo_status stereo_soft_forward(stereo_plan_t plan, const float* ref, const fl
  * (guide = ref), the NCC cost of both images, the warp and the shift back.
  * Deterministic: gathers in a fixed order, and fixed-point integer sums
  * (scale 2^44) where the warp scatters into the target image, so per-pixel
- * contributions must stay below 2^19 in magnitude. */
+ * contributions must stay below 2^19 in magnitude.  Range of grad_disp: FP32's
+ * for bil_radius >= 6 and with agg_engine 0 or 1; with agg_engine 2 and
+ * bil_radius <= 5 an intermediate is carried to 2^-39 of its bound, max
+ * |grad_disp| |1 - c1| (D - 1) / T over the finite pixels, so pixels whose
+ * gradient is below about 1e-3 of the largest lose bits in proportion. */
 stereo_status stereo_backward(stereo_plan_t plan, const float* ref, const float* tar,
                               const double plane[3], const float* saved,
                               const float* grad_disp, float* grad_ref, float* grad_tar,

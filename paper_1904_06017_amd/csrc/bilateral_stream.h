@@ -47,6 +47,20 @@ using bilh::View;
 
 constexpr int kMaxNB = 4;               // level blocks per sweep
 
+// Pass 2 of the backward reads C' = dE / W_p, whose range is that of the
+// caller's gradient map: one pixel's may be 1e10 of another's.  FP16 parts
+// share one scale over the image, so a value x keeps 2^-39 of the largest, and
+// what lies 2^-39 below it is lost (a smooth map at R = 7: 6e-8 relative beside
+// its like, 8e-5 at 1e-4 of the largest, nothing at 1e-10).  From R = kWideR on
+// C' and the weights are split into three BF16 numbers instead, x = a + b + c
+// (24 bits at FP32's range, as the FP32 form keeps), and the product takes the
+// six terms down to 2^-24: aa, ab, ba, ac, bb, ca.  Three times the operand
+// bytes of one part leave room for kMaxWide level blocks.  317x243, D = 40, R =
+// 7: pass 2 takes 53 us (39 us on FP16 parts, 196 us on the vector ALU).
+constexpr int kMaxWide = 3;
+constexpr int parts_of(int mode) { return mode == 5 ? 3 : 2; }
+constexpr int max_blocks(int mode) { return mode == 5 ? kMaxWide : kMaxNB; }
+
 // Products of the S states of a block and the row pairs they read, relative
 // to the block's first: state k takes products [ps(k), ps(k + 1)).  In phase
 // t state k works on block row t - k, so it reads pairs lo(k) - 2 k .. hi(k) -
@@ -77,7 +91,8 @@ struct Sched {
   }
 };
 
-// MODE 1: winner-take-all, 2: soft-argmin, 3 / 4: pass 1 / 2 of its backward.
+// MODE 1: winner-take-all, 2: soft-argmin, 3 / 4: pass 1 / 2 of its backward,
+// 5: pass 2 on BF16 parts (R >= kWideR).
 template <int R, int NB, int MODE>
 struct SGeom {
   using G = HGeom<R>;
@@ -87,36 +102,37 @@ struct SGeom {
   static constexpr int WLO = C::wlo(), WHI = C::whi();
   static constexpr int NSLOT = WHI - WLO + 1 + 2;        // pairs of a phase + the next two
   static constexpr int CHB = G::NQH * 256;               // bytes: a pair of one block and part
-  static constexpr int SLOTB = NB * 2 * CHB;
+  static constexpr int PARTS = parts_of(MODE);
+  static constexpr int SLOTB = NB * PARTS * CHB;
   // guide ring: a block's own pixels lie below the pairs of its first state
   static constexpr int GHI = WHI > (R + 3) / 2 ? WHI : (R + 3) / 2;
   static constexpr int NGS = GHI - WLO + 1 + 2;
   static constexpr int GSB = G::NQH * 32;                // bytes: a pair of the guide
   static constexpr int NGV = 2 * 2 * G::HXP;             // guide values of two pairs
-  static constexpr int NCP = 8 * NB;                     // wave copies of two pairs
+  static constexpr int NCP = 4 * PARTS * NB;             // wave copies of two pairs
   static constexpr int KPW = (NCP + kWaves - 1) / kWaves;
   // Scratch of the group that finishes a block row.  MODE 1: a row of levels
   // per pixel; 3: C' of the block row, [level][4 rows][16 columns] dwords with
-  // the level stride that spreads a write over the banks, two by phase; 4: the
-  // costs at its pixels, [wave][level][16 pixels], two by block row.
+  // the level stride that spreads a write over the banks, two by phase; 4, 5:
+  // the costs at its pixels, [wave][level][16 pixels], two by block row.
   static constexpr int EROW = 64 * NB + 16;
   static constexpr int CLEV = 65;                        // dwords per level (MODE 3)
   static constexpr int CBLK = 16 * NB * CLEV * 4;        // bytes of one of the two
   static constexpr int PBLK = 4 * NB * 1024;
   static constexpr int SCRATCH =
-      MODE == 1 ? 64 * EROW : MODE == 3 ? 2 * CBLK : MODE == 4 ? 2 * PBLK : 0;
+      MODE == 1 ? 64 * EROW : MODE == 3 ? 2 * CBLK : MODE >= 4 ? 2 * PBLK : 0;
   static constexpr size_t lds_bytes = (size_t)NSLOT * SLOTB + (size_t)NGS * GSB +
                                       sizeof(float) * G::STAB + SCRATCH;
   static_assert(lds_bytes <= 160 * 1024, "LDS budget");
-  static_assert((2 * NB - 1) * CHB < 65536, "operand offsets must fit a DS immediate");
+  static_assert((PARTS * NB - 1) * CHB < 65536, "operand offsets must fit a DS immediate");
   static_assert(NGV <= kThreads, "one guide value per thread");
 };
 
-// LDS of a launch, laid out for kMaxNB blocks whatever a sweep takes: ring,
+// LDS of a launch, laid out for the most blocks whatever a sweep takes: ring,
 // guide ring, spatial terms, scratch.
 template <int R, int MODE>
 struct Lds {
-  using Z = SGeom<R, kMaxNB, MODE>;
+  using Z = SGeom<R, max_blocks(MODE), MODE>;
   static constexpr int gring = Z::NSLOT * Z::SLOTB;
   static constexpr int tab = gring + Z::NGS * Z::GSB;
   static constexpr int scratch = tab + (int)sizeof(float) * HGeom<R>::STAB;
@@ -142,7 +158,10 @@ struct Args {
 // (tiles of 32x16 pixels, their weights kept in registers, before).
 struct Back {
   float* out;                           // pass 2: dC planar [D][H][W]
-  uint16_t* h2out;                      // pass 1: C' S, split-FP16 volume (as v)
+  uint16_t* h2out;                      // pass 1: C' S, split volume (as v): FP16 parts,
+                                        // R >= kWideR the first two BF16 parts
+  uint16_t* h3out;                      //   and the third, [block] planes of v.plane
+  const uint16_t* h3;                   // pass 2 at R >= kWideR: that third part
   const float* cpix;                    // pass 2: C planar [D][H][W]
   const unsigned* gmax;                 // max |g'| over the image (float bits): the scale S
   const float *sm_m, *sm_logZ, *sm_dh, *gD;
@@ -153,9 +172,16 @@ struct Back {
 };
 
 // Power-of-two scale that puts a bound m on |C'| in [2^13, 2^14) (bits: m
-// as a float): FP16 keeps its range for every value up to the bound.
+// as a float): FP16 keeps its range for every value up to the bound.  BF16 parts
+// have FP32's range: the bound goes to 2^96, where window sums stay below
+// overflow and the parts of values 2^-200 below it above underflow.
+template <int R>
 __device__ inline float cprime_scale(unsigned bits) {
   const int ex = (int)((bits >> 23) & 0xFF);
+  if constexpr (R >= kWideR) {                        // ex = 255: a bound past FP32, < 2^160
+    const int k = 96 - (ex == 0xFF ? 160 : ex - 126);
+    return ldexpf(1.0f, k > 100 ? 100 : k);
+  }
   if (ex == 0xFF || bits == 0) return 1.0f;          // non-finite or zero: no scaling
   int e = ex - 126;                                   // max = f 2^e, f in [0.5, 1)
   if (e < -80) e = -80;
@@ -163,9 +189,9 @@ __device__ inline float cprime_scale(unsigned bits) {
   return ldexpf(1.0f, k);
 }
 
-// Level blocks per sweep for nblk blocks: even shares of at most kMaxNB.
-inline __host__ __device__ int sweep_blocks(int nblk) {
-  const int n = (nblk + kMaxNB - 1) / kMaxNB;
+// Level blocks per sweep for nblk blocks: even shares of at most `most`.
+inline __host__ __device__ int sweep_blocks(int nblk, int most) {
+  const int n = (nblk + most - 1) / most;
   return (nblk + n - 1) / n;
 }
 
@@ -180,6 +206,19 @@ __device__ __forceinline__ void split_pair(float a, float b, float m1, unsigned&
   const f2 r = {fmaf((float)h[0], m1, a), fmaf((float)h[1], m1, b)};
   hi = __builtin_bit_cast(unsigned, h);
   lo = __builtin_bit_cast(unsigned, __builtin_convertvector(r, h2));
+}
+
+// x = p[0] + p[1] + p[2] in BF16 (round to nearest, exact remainders) for a pair
+// of values.
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ void split_wide(float x, float y, unsigned (&p)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p[k] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2{x, y}), b2));
+    x -= __builtin_bit_cast(float, p[k] << 16);
+    y -= __builtin_bit_cast(float, p[k] & 0xFFFF0000u);
+  }
 }
 
 // value of lane q of this lane's row of 16
@@ -255,17 +294,20 @@ struct Worker {
     const int plast = (v.H - 1 + (R & 1)) >> 1;
     const uint32_t rows = 32u * (uint32_t)v.pitch;    // halves per row pair
     // this wave's copies of two row pairs: copy c = half c & 1 of part (c >> 1)
-    // & 1 of block (c >> 2) % NB of pair c / (4 NB)
+    // % PARTS of block (c / (2 PARTS)) % NB of pair c / (2 PARTS NB)
+    constexpr int PARTS = Z::PARTS;
     const uint16_t* csrc[Z::KPW];
     int cdst[Z::KPW], cpair[Z::KPW];
 #pragma unroll
     for (int m = 0; m < Z::KPW; ++m) {
       const int c = wave + Z::kWaves * m;
-      cpair[m] = c >= 4 * NB ? 1 : 0;
-      const int w = c - cpair[m] * 4 * NB, q = w >> 2, part = (w >> 1) & 1, half = w & 1;
+      cpair[m] = c >= 2 * PARTS * NB ? 1 : 0;
+      const int w = c - cpair[m] * 2 * PARTS * NB, q = w / (2 * PARTS), half = w & 1;
+      const int part = (w >> 1) - PARTS * q;
       const int blk = q0 + q < nblk ? q0 + q : nblk - 1;
-      csrc[m] = v.V + (int64_t)(2 * blk + part) * v.plane + 32 * x0 + half * (G::NQH * 64);
-      cdst[m] = (2 * q + part) * Z::CHB + half * (Z::CHB / 2);
+      csrc[m] = (part < 2 ? v.V + (int64_t)(2 * blk + part) * v.plane : bk.h3 + blk * v.plane) +
+                32 * x0 + half * (G::NQH * 64);
+      cdst[m] = (PARTS * q + part) * Z::CHB + half * (Z::CHB / 2);
     }
     // ring pairs j, j + 1 (j + 1 <= jmax) into their slots; slot: of pair j
     const int jmax = 2 * (len - 1) + G::NRP - 1;
@@ -346,7 +388,7 @@ struct Worker {
     const float kr_inv = 1.0f / kr;
     float cscale = 1.0f;
     if constexpr (TWO)
-      cscale = cprime_scale(__builtin_bit_cast(
+      cscale = cprime_scale<R>(__builtin_bit_cast(
           unsigned, __builtin_bit_cast(float, *bk.gmax) * fabsf(bk.one_minus_c1) * bk.invT *
                         (float)(bk.d_all > 1 ? bk.d_all - 1 : 1)));
     auto fetch_state = [&](int b, char* __restrict__ swr) {
@@ -358,12 +400,12 @@ struct Worker {
         st.x = -(bk.sm_m[pix] + bk.sm_logZ[pix]);
         st.y = bk.gD[pix] * (bk.one_minus_c1 * -bk.invT);
         st.z = bk.sm_dh[pix];
-      } else if constexpr (MODE == 4) {
+      } else if constexpr (MODE >= 4) {
         // copy c: 4 levels (lane >> 4) of the wave's 16 pixels (lane & 15)
         char* const dst = swr + (b & 1) * Z::PBLK + bx * NB * 1024;
 #pragma unroll
         for (int c = 0; c < 4 * NB; ++c) {
-          int d = 4 * c + (ln >> 4);
+          int d = 16 * q0 + 4 * c + (ln >> 4);
           d = d < v.D ? d : v.D - 1;
           __builtin_amdgcn_global_load_lds(
               (BILM_GLOBAL void*)(bk.cpix + (int64_t)d * v.H * v.W + pix),
@@ -386,14 +428,14 @@ struct Worker {
       const bool in = py < v.H && px < v.W;
       const int64_t pix = in ? (int64_t)py * v.W + px : 0;
       if constexpr (TWO) {
-        // lane: levels 16 q + 4 lk + j of pixel li, acc[q][0] = sum w B,
+        // lane: levels 16 (q0 + q) + 4 lk + j of pixel li, acc[q][0] = sum w B,
         // acc[q][1] = sum w (G'(p) - G'(q)) B, both with the weights' 2^12
         float ca = 0.0f, cb = 0.0f;
         if constexpr (MODE == 3) {
           float ws = wsum;                             // W_p 2^12
           ws += __shfl_xor(ws, 16);
           ws += __shfl_xor(ws, 32);
-          const float rinv = 1.0f / ws, oscale = rinv * (4096.0f * cscale);
+          const float rinv = 1.0f / ws, oscale = (rinv * 4096.0f) * cscale;
           unsigned* const blk = reinterpret_cast<unsigned*>(scratch + (b & 1) * Z::CBLK) +
                                 16 * pr + 4 * bx + pc;
 #pragma unroll
@@ -407,6 +449,10 @@ struct Worker {
               ca = fmaf(dE, ev, ca);
               cb = fmaf(dE, acc[q][1][j], cb);
               const float o = dE * oscale;             // S dE / W_p
+              if constexpr (R >= kWideR) {             // split when it leaves
+                blk[d * Z::CLEV] = __builtin_bit_cast(unsigned, o);
+                continue;
+              }
               const _Float16 hi = (_Float16)o, lo = (_Float16)(o - (float)hi);
               blk[d * Z::CLEV] = (unsigned)__builtin_bit_cast(uint16_t, hi) |
                                  ((unsigned)__builtin_bit_cast(uint16_t, lo) << 16);
@@ -431,8 +477,8 @@ struct Worker {
           for (int q = 0; q < NB; ++q)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              const int d = 16 * q + 4 * lk + j;
-              cb = fmaf(in && d < v.D ? cp[16 * d] : 0.0f, acc[q][1][j], cb);
+              const int dq = 16 * q + 4 * lk + j, d = 16 * q0 + dq;
+              cb = fmaf(in && d < v.D ? cp[16 * dq] : 0.0f, acc[q][1][j], cb);
               if (in && d < v.D) bk.out[((int64_t)d * v.H + py) * v.W + px] = acc[q][0][j] * unscale;
             }
           cb += lane_value(cb, lane ^ 16);
@@ -588,7 +634,26 @@ struct Worker {
         const unsigned* src = blk + (16 * q + l) * Z::CLEV + 16 * row;
         const int64_t o = (int64_t)(2 * q) * v.plane + (int64_t)(2 * (b0 + b) + prn) * rows +
                           128 * (((x0 + R) >> 2) + qd) + 8 * l + 4 * par;
-        if (c0 >= 0 && c0 + 3 < kTW && x0 + c0 + 3 < v.W) {
+        const bool whole = c0 >= 0 && c0 + 3 < kTW && x0 + c0 + 3 < v.W;
+        if constexpr (R >= kWideR) {
+          float f[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            f[k] = __builtin_bit_cast(float, src[min(max(c0 + k, 0), kTW - 1)]);
+          unsigned p01[3], p23[3];
+          split_wide(f[0], f[1], p01);
+          split_wide(f[2], f[3], p23);
+#pragma unroll
+          for (int part = 0; part < 3; ++part) {
+            uint16_t* const to = part < 2 ? bk.h2out + o + part * v.plane
+                                          : bk.h3out + o - (int64_t)q * v.plane;
+            if (whole) *reinterpret_cast<uint2*>(to) = make_uint2(p01[part], p23[part]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (!whole && c0 + k >= 0 && c0 + k < kTW && x0 + c0 + k < v.W)
+                to[k] = (uint16_t)((k < 2 ? p01 : p23)[part] >> (16 * (k & 1)));
+          }
+        } else if (whole) {
           const unsigned w0 = src[c0], w1 = src[c0 + 1], w2 = src[c0 + 2], w3 = src[c0 + 3];
           *reinterpret_cast<uint2*>(bk.h2out + o) =
               make_uint2((w0 & 0xFFFFu) | (w1 << 16), (w2 & 0xFFFFu) | (w3 << 16));
@@ -663,6 +728,40 @@ struct Worker {
         float w[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) w[q] = __builtin_amdgcn_exp2f(fmaf(-g[q], g[q], sv[q]));
+        if constexpr (MODE == 5) {
+          u4 wp[3], gp[3];                             // parts of w, w (G'(p) - G'(q))
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {                // g = G'(q) - G'(p)
+            unsigned pw[3], pg[3];
+            split_wide(w[2 * j], w[2 * j + 1], pw);
+            split_wide(-g[2 * j] * w[2 * j], -g[2 * j + 1] * w[2 * j + 1], pg);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              wp[k][j] = pw[k];
+              gp[k][j] = pg[k];
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < NB; ++q) {
+            b8 b[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+              b[k] = __builtin_bit_cast(b8, *reinterpret_cast<const u4*>(rd + oa + (3 * q + k) * Z::CHB));
+            f4 cw = i < 1 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][0];
+            f4 cg = i < 1 ? f4{0.f, 0.f, 0.f, 0.f} : acc[q][1];
+#pragma unroll
+            for (int n = 2; n >= 0; --n)               // parts whose order is n, small ones first
+#pragma unroll
+              for (int k = 0; k <= n; ++k) {
+                cw = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], __builtin_bit_cast(b8, wp[n - k]), cw, 0, 0, 0);
+                cg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], __builtin_bit_cast(b8, gp[n - k]), cg, 0, 0, 0);
+              }
+            acc[q][0] = cw;
+            acc[q][1] = cg;
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          continue;
+        }
         u4 hi, lo;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -784,12 +883,13 @@ __device__ __forceinline__ void spatial_table(float* t, float ks2) {
 template <int R, int MODE>
 __device__ __forceinline__ void segment(const View& v, const Back& bk, int x0, int b0, int len,
                                         float* lds) {
-  const int nblk = (v.D + 15) / 16, nb = sweep_blocks(nblk);
+  const int nblk = (v.D + 15) / 16, nb = sweep_blocks(nblk, max_blocks(MODE));
   for (int q0 = 0; q0 < nblk; q0 += nb) {
     // the state a sweep leaves is read by the next one in the same wave (block
     // rows and lanes keep their waves): program order is enough.  A fence of
     // the whole device here cost 56 us a segment.
-    if (nb == 4) Worker<R, MODE, 4>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    if (max_blocks(MODE) == 4 && nb == 4)
+      Worker<R, MODE, max_blocks(MODE)>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
     else if (nb == 3) Worker<R, MODE, 3>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
     else if (nb == 2) Worker<R, MODE, 2>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
     else Worker<R, MODE, 1>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
@@ -919,11 +1019,14 @@ template <int R>
 hipError_t launch_back(const Plan& P, const BilArgs& a, int pass, hipStream_t s) {
   const BilPair p = bil::make_pair(P, a);
   if (p.D > 16 * kMaxNB || p.g_u8 || !a.gmax || (pass == 1 && !a.h2_out) ||
-      (pass == 2 && (!a.cpix || !a.E)))
+      (pass == 2 && (!a.cpix || !a.E)) ||
+      (R >= kWideR && (pass == 1 ? !a.h3_out : !a.h3)))
     return hipErrorInvalidValue;
   Back b{};
   b.out = a.E;
   b.h2out = a.h2_out;
+  b.h3out = a.h3_out;
+  b.h3 = a.h3;
   b.cpix = a.cpix;
   b.gmax = a.gmax;
   b.sm_m = a.sm_m;
@@ -938,7 +1041,8 @@ hipError_t launch_back(const Plan& P, const BilArgs& a, int pass, hipStream_t s)
   b.one_minus_c1 = p.o.one_minus_c1;
   b.d_first = a.d_first;
   b.d_all = P.D;
-  return pass == 1 ? launch_pair<R, 3>(&p, 1, s, b) : launch_pair<R, 4>(&p, 1, s, b);
+  return pass == 1 ? launch_pair<R, 3>(&p, 1, s, b)
+                   : launch_pair<R, (R >= kWideR ? 5 : 4)>(&p, 1, s, b);
 }
 
 // n segments over many volumes (descs, segs: device arrays).

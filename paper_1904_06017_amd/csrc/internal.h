@@ -153,6 +153,10 @@ struct BilArgs {
   // and pass 1's output volume (C' scaled, split; pitch and plane of h2)
   const unsigned int* gmax;
   uint16_t* h2_out;
+  // R >= kWideR: that volume has three BF16 parts, the first two in h2_out / h2
+  // as above, the third in planes of its own, one per block
+  uint16_t* h3_out;
+  const uint16_t* h3;
 };
 // mode 0: write the normalised aggregated volume; mode 1: fused WTA and
 // sub-pixel refinement (the volume never leaves the chip); mode 2: fused
@@ -177,20 +181,24 @@ constexpr int kSegW = 16, kSegRow = 4;   // strip columns, rows of a block row
 hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n,
                                      int n_groups, hipStream_t s);
 
-// Backward of the soft-argmin head on the split-FP16 matrix cores, for one
+// Radii whose backward carries C' in three BF16 parts (FP32's range and bits);
+// below, two FP16 parts under one scale for the image.
+constexpr int kWideR = 6;
+// Backward of the soft-argmin head on the matrix cores, for one
 // level tile (at most 64 levels, float guide, d_first a multiple of 16):
 // pass 1 reads the tile's split costs (a.h2) and writes C' = dE / W_p, times
 // a power of two set by the bound max |g'| |1 - c1| (D - 1) / T (*a.gmax =
-// max |g'| as float bits), split into a.h2_out (same layout), with aP, A1,
-// Wp as mode 5; pass 2 reads that volume (a.h2) and writes dC planar
+// max |g'| as float bits), split into a.h2_out (same layout; and a.h3_out),
+// with aP, A1, Wp as mode 5; pass 2 reads that volume (a.h2, a.h3) and writes dC planar
 // [levels][H][W] to a.E and A2 as mode 6 (a.cpix: the tile's costs, planar).
-// The stored columns and rows of a.h2_out outside the image are not written:
-// zero them first (launch_h2_pad_zero).
+// The stored columns and rows of a.h2_out and a.h3_out outside the image are not
+// written: zero them first (launch_h2_pad_zero).
 hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hipStream_t s);
 // Zeros in the stored columns outside [0, W) and rows outside [0, H) (all
-// levels, both halves) of the first nblk 16-level blocks of a split-FP16 volume at radius R.
-hipError_t launch_h2_pad_zero(uint16_t* h2, int64_t plane, int pitch, int W, int H, int R,
-                              int nblk, hipStream_t s);
+// levels) of the first nblk 16-level blocks of a split volume at radius R: both
+// parts in h2 and, where h3 is non-NULL, the third one there.
+hipError_t launch_h2_pad_zero(uint16_t* h2, uint16_t* h3, int64_t plane, int pitch, int W, int H,
+                              int R, int nblk, hipStream_t s);
 
 // Row pitch (halves, a multiple of 8) of the split-FP16 volumes at window
 // radius R for width W: covers the halo columns of every 16-pixel tile.

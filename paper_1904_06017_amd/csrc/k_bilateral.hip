@@ -62,30 +62,32 @@ hipError_t launch_bilateral_bwd16(const Plan& P, const BilArgs& a, int pass, hip
 
 namespace bilh {
 // Zeros in the pad columns of every row, and in the rows outside the image,
-// of the first blocks (both parts).  Row blockIdx.y of the stored rows; thread
+// of the first blocks (all parts).  Row blockIdx.y of the stored rows; thread
 // t: column t / 16 (of an image row: pad columns [0, R), then [W + R, pitch);
 // of a row outside: all), level t % 16.
 __global__ void __launch_bounds__(256) h2_pad_zero_kernel(uint16_t* __restrict__ h2,
+                                                          uint16_t* __restrict__ h3, int nblk,
                                                           int64_t plane, int pitch, int W, int H,
                                                           int R) {
-  const int st = blockIdx.y, y = st - (R & 1), bp = blockIdx.z;   // bp = 2 block + part
+  const int st = blockIdx.y, y = st - (R & 1), bp = blockIdx.z;   // 2 block + part, then block
+  uint16_t* const to = bp < 2 * nblk ? h2 + (int64_t)bp * plane : h3 + (int64_t)(bp - 2 * nblk) * plane;
   const bool out = y < 0 || y >= H;
   const int n = 16 * (out ? pitch : pitch - W);
   for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) {
     const int ci = t >> 4, l = t & 15;
     const int c = out || ci < R ? ci : W + ci;
-    h2[(int64_t)bp * plane + (int64_t)(st >> 1) * 32 * pitch + 128 * (c >> 2) + 8 * l +
-       4 * (st & 1) + (c & 3)] = 0;
+    to[(int64_t)(st >> 1) * 32 * pitch + 128 * (c >> 2) + 8 * l + 4 * (st & 1) + (c & 3)] = 0;
   }
 }
 }  // namespace bilh
 
-hipError_t launch_h2_pad_zero(uint16_t* h2, int64_t plane, int pitch, int W, int H, int R,
-                              int nblk, hipStream_t s) {
+hipError_t launch_h2_pad_zero(uint16_t* h2, uint16_t* h3, int64_t plane, int pitch, int W, int H,
+                              int R, int nblk, hipStream_t s) {
   if (!h2 || pitch < W + R || nblk <= 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((16 * (pitch - W) + 255) / 256), (unsigned)h2_rows(R, H),
-                  (unsigned)(2 * nblk));
-  hipLaunchKernelGGL(bilh::h2_pad_zero_kernel, grid, dim3(256), 0, s, h2, plane, pitch, W, H, R);
+                  (unsigned)((h3 ? 3 : 2) * nblk));
+  hipLaunchKernelGGL(bilh::h2_pad_zero_kernel, grid, dim3(256), 0, s, h2, h3, nblk, plane, pitch, W,
+                     H, R);
   return hipGetLastError();
 }
 

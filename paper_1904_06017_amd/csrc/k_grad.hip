@@ -851,6 +851,10 @@ size_t grad_layout(Plan& P, size_t o) {
   sz[GR_FA] = f4 * std::max((size_t)DT * HW, HV * ((WVX + 63) / 64) * 64);
   // boxes of alpha; before them the NCC adjoint pass's spills [H][W / 64][64][2]
   sz[GR_BA] = f4 * std::max((size_t)DT * HV * WVX, (size_t)P.H * ((P.W + 63) / 64) * 128);
+  // the third BF16 part of C' at the large radii (pass 1's output; the vector
+  // ALU's passes keep their C' there)
+  if (P.R >= kWideR)
+    sz[GR_GT] = std::max(sz[GR_GT], sizeof(uint16_t) * ((DT + 15) / 16) * (size_t)P.h2_plane);
   sz[GR_BS] = 3 * f4 * HV * WVX;
   sz[GR_SY] = 3 * f4 * (size_t)P.H * (P.W + P.D - 1);
   sz[GR_BSY] = 3 * f4 * HV * WVY;
@@ -1076,10 +1080,10 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
   }
 
   const int n = (2 * r + 1) * (2 * r + 1);
-  // the aggregation passes on the split-FP16 matrix cores where the level
-  // tiles start on 16-level blocks (the volumes are stored by those); elsewhere
-  // on the vector ALU: 317x243, D = 40, R = 7 takes 201 + 196 us there, 49 +
-  // 39 us here
+  // the aggregation passes on the 16-bit matrix cores where the level tiles
+  // start on 16-level blocks (the volumes are stored by those); elsewhere on
+  // the vector ALU: 317x243, D = 40, R = 7 takes 201 + 196 us there, 53 + 53
+  // us here (pass 1, pass 2)
   const bool mc = P.agg_engine == 2 && (D <= DT || DT % 16 == 0);
   if (mc) {
     // max |g'| (the scale of C' in pass 1) and zeros in the pad columns of
@@ -1089,8 +1093,9 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
            grad_disp, HW,
            reinterpret_cast<unsigned int*>(R_(GR_GMAX)));
     HIPC(launch_h2_pad_zero(at<uint16_t>(ws, P.off_cvol + P.h2_tar_off),
-                            P.h2_plane, P.h2_pitch, W, H, P.R, (DT + 15) / 16,
-                            stream), "pad columns of C'");
+                            P.R >= kWideR ? reinterpret_cast<uint16_t*>(Gt) : nullptr, P.h2_plane,
+                            P.h2_pitch, W, H, P.R, (std::min(DT, D) + 15) / 16, stream),
+         "pad columns of C'");
   }
   for (int d0 = 0; d0 < D; d0 += DT) {
     const int nl = std::min(DT, D - d0);
@@ -1109,7 +1114,6 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
       a.h2 = hC; a.h2_plane = hplane; a.h2_pitch = P.h2_pitch;
       a.guide = ref; a.guide_dt = STEREO_F32; a.guide_pitch = P.p.pitch_ref;
       a.levels = nl;
-      a.E = Gt;
       a.sm_m = const_cast<float*>(sm_m);
       a.sm_logZ = const_cast<float*>(sm_logZ);
       a.sm_dh = const_cast<float*>(sm_dh);
@@ -1119,13 +1123,15 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
       a.d_first = d0;
       a.gmax = reinterpret_cast<const unsigned int*>(R_(GR_GMAX));
       a.h2_out = hG;
+      if (P.R >= kWideR) a.h3_out = reinterpret_cast<uint16_t*>(Gt);
       a.plane[0] = plane[0]; a.plane[1] = plane[1]; a.plane[2] = plane[2];
       if (d0 == 0) HIPC(mark(1), "event record");
       HIPC(launch_bilateral_bwd16(P, a, 1, stream), "aggregation + softmax adjoint");
       if (d0 == 0) HIPC(mark(2), "event record");
       if (d0 == 0) HIPC(mark(3), "event record");
       a.h2 = hG;
-      a.h2_out = nullptr;
+      a.h3 = a.h3_out;
+      a.h2_out = a.h3_out = nullptr;
       a.E = gCt;
       a.cpix = Ct;
       HIPC(launch_bilateral_bwd16(P, a, 2, stream), "aggregation adjoint");
