@@ -57,7 +57,13 @@ constexpr int kMaxNB = 4;               // level blocks per sweep
 // six terms down to 2^-24: aa, ab, ba, ac, bb, ca.  Three times the operand
 // bytes of one part leave room for kMaxWide level blocks.  317x243, D = 40, R =
 // 7: pass 2 takes 53 us (39 us on FP16 parts, 196 us on the vector ALU).
+// A product over a block's union also meets values outside a pixel's own
+// window, with weight 0, and 0 x infinity is NaN: so at these radii non-finite
+// values stay out of the operands (C' 0, guide far off), and the pixels whose
+// own window holds one are made NaN at the end.  Such a pixel has a non-finite
+// aP; pass 1 raises a flag where it meets one, without which nothing is looked up.
 constexpr int kMaxWide = 3;
+constexpr float kMaxFloat = 3.402823466e38f;
 constexpr int parts_of(int mode) { return mode == 5 ? 3 : 2; }
 constexpr int max_blocks(int mode) { return mode == 5 ? kMaxWide : kMaxNB; }
 
@@ -164,6 +170,7 @@ struct Back {
   const uint16_t* h3;                   // pass 2 at R >= kWideR: that third part
   const float* cpix;                    // pass 2: C planar [D][H][W]
   const unsigned* gmax;                 // max |g'| over the image (float bits): the scale S
+  unsigned* bad;                        // R >= kWideR: nonzero where some aP is not finite
   const float *sm_m, *sm_logZ, *sm_dh, *gD;
   float *aP, *A1, *A2, *Wp;             // Wp nullable
   float invT, one_minus_c1;
@@ -357,9 +364,11 @@ struct Worker {
       const float f = v.g_u8 ? (float)raw : __builtin_bit_cast(float, raw);
       const bool in = gcol < kTW + 2 * R && y >= 0 && y < v.H && x >= 0 && x < v.W;
       const int sl = wrap(slot + gpr, Z::NGS);
+      const float fs = f * kr;
+      const bool use = MODE == 5 ? in && fabsf(fs) <= kMaxFloat : in;
       if (mine)
         *reinterpret_cast<float*>(gring + sl * Z::GSB + (gcol >> 2) * 32 + grow * 16 +
-                                  (gcol & 3) * 4) = in ? f * kr : kFar;
+                                  (gcol & 3) * 4) = use ? fs : kFar;
     };
 
     // the pairs of phase 0
@@ -387,6 +396,8 @@ struct Worker {
     // (st.x, st.y, st.z), of pass 2 the copies of its costs into the scratch.
     const float kr_inv = 1.0f / kr;
     float cscale = 1.0f;
+    bool any_bad = false;
+    if constexpr (MODE == 5) any_bad = __builtin_amdgcn_readfirstlane((int)*bk.bad) != 0;
     if constexpr (TWO)
       cscale = cprime_scale<R>(__builtin_bit_cast(
           unsigned, __builtin_bit_cast(float, *bk.gmax) * fabsf(bk.one_minus_c1) * bk.invT *
@@ -450,7 +461,7 @@ struct Worker {
               cb = fmaf(dE, acc[q][1][j], cb);
               const float o = dE * oscale;             // S dE / W_p
               if constexpr (R >= kWideR) {             // split when it leaves
-                blk[d * Z::CLEV] = __builtin_bit_cast(unsigned, o);
+                blk[d * Z::CLEV] = __builtin_bit_cast(unsigned, fabsf(o) <= kMaxFloat ? o : 0.0f);
                 continue;
               }
               const _Float16 hi = (_Float16)o, lo = (_Float16)(o - (float)hi);
@@ -468,9 +479,19 @@ struct Worker {
             atomicAdd(bk.aP + pix, ca);
             atomicAdd(bk.A1 + pix, cb * (kr_inv / 4096.0f));
             if (bk.Wp) bk.Wp[pix] = ws * (1.0f / 4096.0f);
+            if (R >= kWideR && !(fabsf(ca) <= kMaxFloat)) *bk.bad = 1u;
           }
         } else {
-          const float unscale = 1.0f / (4096.0f * cscale);
+          float unscale = 1.0f / (4096.0f * cscale);
+          if (any_bad) {                               // uniform; lane lk: every fourth row
+            int hit = 0;
+            for (int y = max(py - R, 0) + lk; y <= min(py + R, v.H - 1); y += 4)
+              for (int x = max(px - R, 0); x <= min(px + R, v.W - 1); ++x)
+                hit |= !(fabsf(bk.aP[(int64_t)y * v.W + x]) <= kMaxFloat);
+            hit |= __shfl_xor(hit, 16);
+            hit |= __shfl_xor(hit, 32);
+            if (hit) unscale = __builtin_nanf("");
+          }
           const float* const cp = reinterpret_cast<const float*>(srd + (b & 1) * Z::PBLK + bx * NB * 1024) +
                                   (ln & 15);
 #pragma unroll
@@ -1029,6 +1050,7 @@ hipError_t launch_back(const Plan& P, const BilArgs& a, int pass, hipStream_t s)
   b.h3 = a.h3;
   b.cpix = a.cpix;
   b.gmax = a.gmax;
+  b.bad = a.gmax + 1;
   b.sm_m = a.sm_m;
   b.sm_logZ = a.sm_logZ;
   b.sm_dh = a.sm_dh;

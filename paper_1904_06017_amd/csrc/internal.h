@@ -65,7 +65,8 @@ enum GradRegion {
   GR_BSY,                                       // [3][HV][WVY] their boxes
   GR_MU,                                        // [2][H][W+2r] block means of X, Y
   GR_GXV, GR_GYV, GR_GTARFIX, GR_PART_A, GR_PART_B,
-  GR_GMAX,                                      // max |C'| of the matrix-core backward
+  GR_GMAX,                                      // max |g'|, non-finite flag of the
+                                                // matrix-core backward
   GR_COUNT
 };
 
@@ -149,9 +150,10 @@ struct BilArgs {
   // ranges above 64 levels: selection state kept between the sweeps of 64
   // levels, h2_state_floats per pixel (16-byte aligned)
   float* state;
-  // backward passes on the split-FP16 matrix cores: max |g'| (float bits),
+  // backward passes on the 16-bit matrix cores: max |g'| (float bits) and a
+  // flag that pass 1 raises at a non-finite aP (both zeroed by the caller),
   // and pass 1's output volume (C' scaled, split; pitch and plane of h2)
-  const unsigned int* gmax;
+  unsigned int* gmax;
   uint16_t* h2_out;
   // R >= kWideR: that volume has three BF16 parts, the first two in h2_out / h2
   // as above, the third in planes of its own, one per block

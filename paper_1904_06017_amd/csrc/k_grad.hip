@@ -864,7 +864,7 @@ size_t grad_layout(Plan& P, size_t o) {
   sz[GR_GTARFIX] = sizeof(unsigned long long) * HW;
   sz[GR_PART_A] = sizeof(double) * 3 * nb;
   sz[GR_PART_B] = sizeof(double) * 3 * nb;
-  sz[GR_GMAX] = sizeof(float);
+  sz[GR_GMAX] = 2 * sizeof(float);
   for (int i = 0; i < GR_COUNT; ++i) {
     P.g_off[i] = o;
     o = align256(o + sz[i]);
@@ -1056,7 +1056,7 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
     float* const reg[kZeroMax] = {aP, A1, A2, SamY, SaX, gXv, gYv,
                                   reinterpret_cast<float*>(gfix), R_(GR_GMAX)};
     const int64_t len[kZeroMax] = {HW, HW, HW, 3 * HW, 2 * HWY, HVWV, (int64_t)HV * WVY,
-                                   2 * HW, 1};
+                                   2 * HW, 2};
     int64_t nmax = 0;
     for (int k = 0; k < kZeroMax; ++k) {
       z.p[k] = reg[k];
@@ -1121,7 +1121,7 @@ stereo_status stereo_backward_profiled(stereo_plan_t plan, const float* ref, con
       a.aP = aP; a.A1 = A1; a.A2 = A2;
       a.Wp = d0 == 0 ? Wp : nullptr;
       a.d_first = d0;
-      a.gmax = reinterpret_cast<const unsigned int*>(R_(GR_GMAX));
+      a.gmax = reinterpret_cast<unsigned int*>(R_(GR_GMAX));
       a.h2_out = hG;
       if (P.R >= kWideR) a.h3_out = reinterpret_cast<uint16_t*>(Gt);
       a.plane[0] = plane[0]; a.plane[1] = plane[1]; a.plane[2] = plane[2];

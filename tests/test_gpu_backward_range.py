@@ -67,3 +67,33 @@ def test_small_gradients_beside_large_ones(R, num_disp, levels, kind):
     got = _backward(w, ref, tar, g, grad_levels=levels)
     for a, e in zip(got[:2], exact[:2]):
         assert np.linalg.norm(a[far] - e[far]) <= 1e-4 * np.linalg.norm(e[far])
+
+
+@pytest.mark.parametrize("R,num_disp", [(6, 32), (7, 70), (8, 40)])
+@pytest.mark.parametrize("what", ["nan", "inf", "image"])
+def test_reach_of_a_non_finite_pixel(R, num_disp, what):
+    """A pixel whose gradient (or reference value) is not finite spoils the
+    pixels whose windows hold it, no others: the same gradients of the reference
+    are finite as in the vector ALU's backward, which sums each pixel's own
+    window, and equal to them; so are the rows of the target's out of reach."""
+    w, ref, tar, g = _setup(R, num_disp)
+    y, x = 46, 43
+    if what == "image":
+        ref[y, x] = np.nan
+    else:
+        g[y, x] = np.float32(what)
+    plan = api.Plan.from_workload(w)
+    dref, dtar, dg = (torch.from_numpy(a).cuda() for a in (ref, tar, g))
+    _, saved = api.soft_forward(plan, dref, dtar, w.plane)
+    out = []
+    for engine in (2, 0):
+        plan.set_tuning("agg_engine", engine)
+        out.append([_host(t) for t in api.backward(plan, dref, dtar, w.plane, saved, dg)])
+    (a, at, _), (v, vt, _) = out
+    assert np.array_equal(np.isfinite(a), np.isfinite(v))
+    assert not np.isfinite(a[y, x]) and np.isfinite(a[0, 0])
+    ok = np.isfinite(v)
+    assert np.linalg.norm(a[ok] - v[ok]) <= 1e-4 * np.linalg.norm(v[ok])
+    reach = R + r if what != "image" else 2 * R + 2 * r + 4
+    far = [i for i in range(H) if abs(i - y) > reach]
+    assert np.linalg.norm(at[far] - vt[far]) <= 1e-4 * np.linalg.norm(vt[far])
