@@ -31,6 +31,7 @@
 #pragma once
 #include <type_traits>
 
+#include "cuts.h"
 #include "internal.h"
 
 namespace stereo {
@@ -471,7 +472,7 @@ __device__ __forceinline__ void bilateral_tile(const BilPair& a, int x0, int y0,
 }
 
 // Two workgroups per CU at 8 levels per pass (16 waves, 4 per SIMD): at most
-// 128 VGPRs; at 16 levels the LDS allows one.
+// 128 VGPRs; at 16 levels, and at R = 8, the LDS allows one.
 template <int R, int PX, int DC, int TYT, typename GT, int MODE>
 __global__ void __launch_bounds__(kThreads, DC == 8 ? 4 : 2)
 bilateral_kernel(BilPair a, int levels) {
@@ -542,21 +543,15 @@ hipError_t launch_one(const Plan& P, const BilArgs& a, hipStream_t s) {
   const BilPair b = make_pair(P, a);
   int levels = (b.D + DC - 1) / DC * DC;
   if (MODE == 0 || MODE == 4) {
-    // The levels in grid.z parts where that evens out the CUs' shares: a part
-    // of per chunks costs per + 0.05 (every chunk forms its own weights
-    // anyway), two workgroups share a CU, one alone takes 0.62 of the pair's
-    // time.  640x480, D = 48, R = 5 (300 tiles of 256 CUs): 148 us whole, 133 /
-    // 111 / 118 in 2 / 3 / 6 parts; 640x360, D = 30: 76, 66 in 2; 1280x720, D =
-    // 64, R = 7: 647, 622 / 605 / 597 in 2 / 3 / 8; 960x540: the same within 4 %.
-    const int n = levels / DC, c = bilm::cu_count_of_current_device(), cus = c > 0 ? c : 256;
-    const long tiles = (long)grid.x * grid.y;
-    double best = 1e30;
-    for (int per = n; per >= 1; --per) {
-      const int z = (n + per - 1) / per;
-      const long m = (tiles * z + cus - 1) / cus;      // workgroups of the fullest CU
-      const double cost = (double)(m / 2) * (per + 0.05) + (m & 1 ? 0.62 * (per + 0.05) : 0.0);
-      if (cost < best) { best = cost; levels = per * DC; grid.z = z; }
-    }
+    // The levels in grid.z parts (level_part).  640x480, D = 48, R = 5 (300 tiles
+    // of 256 CUs): 148 us whole, 133 / 111 / 118 in 2 / 3 / 6 parts; 640x360, D =
+    // 30: 76, 66 in 2; 1280x720, D = 64, R = 7: 647, 622 / 605 / 597 in 2 / 3 / 8;
+    // 960x540: the same within 4 %.
+    constexpr int held = 2 * lds <= 160 * 1024 ? 2 : 1;
+    const int n = levels / DC, c = bilm::cu_count_of_current_device();
+    const int per = level_part((long)grid.x * grid.y, n, c > 0 ? c : 256, held);
+    levels = per * DC;
+    grid.z = (n + per - 1) / per;
   }
   hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, s, b, levels);
   return hipGetLastError();
