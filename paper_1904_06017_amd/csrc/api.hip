@@ -1,6 +1,7 @@
 // C ABI: plans (pure host state), parameter validation, workspace layout and
 // the enqueue entry points declared in include/stereo.h.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -27,6 +28,17 @@ stereo_status fail(stereo_status s, const char* fmt, ...) {
 stereo_status hip_check(hipError_t e, const char* what) {
   if (e == hipSuccess) return STEREO_OK;
   return fail(STEREO_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+int device_cus() {
+  static std::atomic<int> cache[64];
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if ((n = cache[dev].load(std::memory_order_relaxed)) > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+    return 256;
+  cache[dev].store(n, std::memory_order_relaxed);
+  return n;
 }
 
 Consts consts_of(const Plan& P) {

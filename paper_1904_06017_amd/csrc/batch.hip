@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "cuts.h"
 #include "internal.h"
 
 using namespace stereo;
@@ -36,6 +37,8 @@ struct SegGroup {
   std::vector<Seg> segs;
   size_t off;                 // in the workspace
 };
+
+constexpr int kMaxCus = 256;  // of a gfx950 device
 
 // One batched launch of a cheap stage: its jobs (pair, and for statistics
 // which image), the block prefix, and where both live in the workspace.
@@ -65,6 +68,7 @@ struct stereo_batch_s {
   std::vector<size_t> pair_ws;         // offset of each pair's plan workspace
   std::vector<Group> groups;
   std::vector<SegGroup> seg_groups;
+  int seg_cus = 0;                     // CUs that they were cut for
   std::vector<JobList> lists;
   size_t desc_off = 0, desc_bytes = 0; // per-volume descriptors (2 per pair)
   size_t counter_off = 0;
@@ -113,16 +117,18 @@ void ncc_blocks(stereo_batch_s& b) {
   }
 }
 
-// Strip segments of the split-FP16 engine.  Per radius, a pair's strips are
-// cut so that the whole group makes about four segments per workgroup (a
-// segment fills and drains its pipeline of block rows, so short ones cost
-// more), listed in bands of tile_band adjacent strips of one vertical range
-// (their halo columns meet in an XCD's L2) and sorted by cost, longest first.
-void seg_tables(stereo_batch_s& b) {
+// Strip segments of the split-FP16 engine for a device of cus CUs.  Per
+// radius, a pair's strips are cut by the cost of the whole group
+// (segment_rows), listed in bands of tile_band adjacent strips of one vertical
+// range (their halo columns meet in an XCD's L2) and sorted by cost, longest
+// first.  The tables' places in the workspace stay as they are.
+void seg_tables(stereo_batch_s& b, int cus) {
   constexpr int kFill = 6;             // phases a segment takes beyond its block rows
-  constexpr double kShares = 4.0 * 256.0;
   struct V { int pair, vol; double w; };
   struct S { double cost; Seg seg; };
+  std::vector<size_t> off;
+  for (const SegGroup& G : b.seg_groups) off.push_back(G.off);
+  b.seg_cus = cus;
   b.seg_groups.clear();
   std::vector<std::vector<V>> vols;
   for (int i = 0; i < (int)b.plans.size(); ++i) {
@@ -132,14 +138,12 @@ void seg_tables(stereo_batch_s& b) {
     if (g == b.seg_groups.size()) {
       SegGroup G;
       G.R = P.R;
-      G.off = 0;
+      G.off = g < off.size() ? off[g] : 0;
       b.seg_groups.push_back(G);
       vols.emplace_back();
     }
-    // a phase: the weights once per sweep of 64 levels, the products per 16
-    const int nblk = (P.D + 15) / 16;
     for (int vol = 0; vol < (P.p.lr_check ? 2 : 1); ++vol)
-      vols[g].push_back({i, vol, 2.0 * ((nblk + 3) / 4) + nblk});
+      vols[g].push_back({i, vol, block_row_cost((P.D + 15) / 16, 4)});
   }
   for (size_t g = 0; g < b.seg_groups.size(); ++g) {
     double total = 0.0;
@@ -151,8 +155,7 @@ void seg_tables(stereo_batch_s& b) {
     for (const V& v : vols[g]) {
       const Plan& P = b.plans[v.pair];
       const int tx = (P.W + kSegW - 1) / kSegW, br = (P.H + kSegRow - 1) / kSegRow;
-      const int want = std::max(8, (int)(total / kShares / v.w));
-      const int n = std::max(1, (br + want - 1) / want), len = (br + n - 1) / n;
+      const int len = segment_rows(total, v.w, br, cus);
       for (int xb = 0; xb < tx; xb += b.tile_band)
         for (int r = 0; r < br; r += len)
           for (int x = xb; x < std::min(tx, xb + b.tile_band); ++x) {
@@ -219,7 +222,9 @@ void build_layout(stereo_batch_s& b) {
     table(per[gi], b.groups[gi].tiles, b.groups[gi].tiles_off);
     table(per_m[gi], b.groups[gi].tiles_m, b.groups[gi].tiles_m_off);
   }
-  seg_tables(b);
+  // laid out for kMaxCus CUs (fewer CUs make fewer, longer segments), so that
+  // the workspace does not depend on the device
+  seg_tables(b, kMaxCus);
   for (SegGroup& G : b.seg_groups) {
     G.off = o;
     o = align256(o + sizeof(Seg) * G.segs.size());
@@ -291,6 +296,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     return fail(STEREO_ERR_WORKSPACE_TOO_SMALL, "batch workspace %zu < %zu", bytes, b.ws_bytes);
   BREQ((reinterpret_cast<uintptr_t>(ws) & 255) == 0, "workspace must be 256-byte aligned");
   if (b.bound_ws == ws) return STEREO_OK;
+  if (b.seg_cus != std::min(b.cu_count, kMaxCus)) seg_tables(b, std::min(b.cu_count, kMaxCus));
   const int n = (int)b.items.size();
   const size_t pb = bilateral_pair_bytes();
   b.host_desc.assign(b.desc_bytes, 0);

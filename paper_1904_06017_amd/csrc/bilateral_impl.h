@@ -35,19 +35,6 @@
 #include "internal.h"
 
 namespace stereo {
-namespace bilm {
-inline int cu_count_of_current_device() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (cache[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    cache[dev] = n;
-  }
-  return cache[dev];
-}
-}  // namespace bilm
 namespace bil {
 
 constexpr int kThreads = 512;
@@ -548,8 +535,8 @@ hipError_t launch_one(const Plan& P, const BilArgs& a, hipStream_t s) {
     // 30: 76, 66 in 2; 1280x720, D = 64, R = 7: 647, 622 / 605 / 597 in 2 / 3 / 8;
     // 960x540: the same within 4 %.
     constexpr int held = 2 * lds <= 160 * 1024 ? 2 : 1;
-    const int n = levels / DC, c = bilm::cu_count_of_current_device();
-    const int per = level_part((long)grid.x * grid.y, n, c > 0 ? c : 256, held);
+    const int n = levels / DC;
+    const int per = level_part((long)grid.x * grid.y, n, device_cus(), held);
     levels = per * DC;
     grid.z = (n + per - 1) / per;
   }

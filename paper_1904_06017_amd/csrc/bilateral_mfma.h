@@ -557,8 +557,8 @@ hipError_t launch_pair(const BilPair& a, hipStream_t s) {
   hipError_t e = set_lds_attr<R, GT, 0, MODE>();
   if (e != hipSuccess) return e;
   const int n = ((a.W + kTW - 1) / kTW) * ((a.H + kTH - 1) / kTH);
-  const int cus = cu_count_of_current_device();
-  int grid = std::min(n, cus > 0 ? cus : 256);
+  const int cus = device_cus();
+  int grid = std::min(n, cus);
   if (grid >= 8) grid -= grid % 8;               // whole XCD bands
   hipLaunchKernelGGL((agg_wta_mfma_kernel<R, GT, 0, MODE>), dim3(grid), dim3(kThreads), MGeom<R>::lds_bytes, s,
                      view_of(a), (const BilPair*)nullptr, (const int*)nullptr, 0, (unsigned int*)nullptr);

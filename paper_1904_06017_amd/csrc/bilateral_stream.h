@@ -196,12 +196,6 @@ __device__ inline float cprime_scale(unsigned bits) {
   return ldexpf(1.0f, k);
 }
 
-// Level blocks per sweep for nblk blocks: even shares of at most `most`.
-inline __host__ __device__ int sweep_blocks(int nblk, int most) {
-  const int n = (nblk + most - 1) / most;
-  return (nblk + n - 1) / n;
-}
-
 // x = hi + lo in FP16 (round to nearest) for a pair of values: lo rounds the
 // remainder x - hi, which is exact in FP32.  Not inline assembly: the matrix
 // cores read the results, and the compiler has to see that hazard.  m1 = -1,
@@ -1014,7 +1008,7 @@ hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s, const Back& bk
   }
   hipError_t e = set_lds_attr<R, MODE, 0>();
   if (e != hipSuccess) return e;
-  const int c = bilm::cu_count_of_current_device(), cus = c > 0 ? c : 256;
+  const int cus = device_cus();
   a.nvol = nvol;
   a.tx = (p[0].W + kTW - 1) / kTW;
   a.br = (p[0].H + 3) / 4;

@@ -1,8 +1,34 @@
 // How launches are cut into workgroups' shares: host arithmetic on sizes and
 // the number of CUs, without any device call.
 #pragma once
+#include <algorithm>
 
 namespace stereo {
+
+// Level blocks per sweep of the streamed aggregation for nblk blocks: even
+// shares of at most `most`.
+constexpr int sweep_blocks(int nblk, int most) {
+  const int n = (nblk + most - 1) / most;
+  return (nblk + n - 1) / n;
+}
+
+// Cost of a block row of nblk level blocks in sweeps of at most `most`: the
+// weights once per sweep (2), the products per block that a sweep computes
+// (padding of an uneven count included).
+inline double block_row_cost(int nblk, int most) {
+  const int per = sweep_blocks(nblk, most);
+  return (double)((nblk + per - 1) / per) * (2 + per);
+}
+
+// Block rows of a segment of a queued launch: br block rows of cost w each, cut
+// so that the launch (total cost) makes about four segments for each of its
+// cus workgroups.  A segment fills and drains its pipeline of block rows, so
+// it has at least eight.
+inline int segment_rows(double total, double w, int br, int cus) {
+  const int want = std::max(8, (int)(total / (4.0 * cus) / w));
+  const int n = std::max(1, (br + want - 1) / want);
+  return (br + n - 1) / n;
+}
 
 // Levels of a materialised aggregation in parts of `per` chunks each, where
 // that evens out the CUs' shares (tiles: workgroups of one part, chunks: level

@@ -16,6 +16,9 @@ stereo_status fail(stereo_status s, const char* fmt, ...);
 // Map a HIP error (after a launch) to a status; hipSuccess -> STEREO_OK.
 stereo_status hip_check(hipError_t e, const char* what);
 
+// CUs of the calling thread's device (256 where it cannot be asked).
+int device_cus();
+
 constexpr float kOffset = 128.0f;   // NCC is offset invariant; centring the
                                     // intensities keeps FP32 block sums exact
 constexpr float kFlatVar = 1e-6f;   // block variance (gray^2) below which the

@@ -548,12 +548,12 @@ hipError_t launch_ncc_ty(const Plan& P, const T* ref, const float* tar_w, const 
 }
 
 // Rows of a tile: 16 redo 2r of 16 + 2r input rows instead of 2r of 8 + 2r, but
-// make half as many workgroups.  They pay from kTallWaves waves of 16-row tiles
-// on, about a full residency of the chip: frames of 1280x720, 64 levels (17 000
+// make half as many workgroups.  They pay from 32 waves of 16-row tiles a CU
+// on, a full residency (8192 waves of the chip's 256 CUs): frames of 1280x720, 64 levels (17 000
 // waves) 534 -> 520 us, 1917x1075, 96 levels 1940 -> 1900 us, both planar volumes
 // at 1280x720 144 -> 135 us; below it 8 rows are faster: 640x360, 32 levels (2200
 // waves) 100.7 against 105.4 us, 320x240 55.0 against 61.1 us.
-constexpr int64_t kTallWaves = 8192;
+constexpr int64_t kTallWaves = 32;      // a CU
 
 template <int r, typename T, int DC>
 hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const float* zX,
@@ -569,7 +569,7 @@ hipError_t launch_ncc_rdc(const Plan& P, const T* ref, const float* tar_w, const
                                                         out_pitch, out_slice, anchor, d_first,
                                                         d_end, quad, pad, s, C2);
   };
-  return waves >= kTallWaves ? go(std::integral_constant<int, 16>{})
+  return waves >= kTallWaves * device_cus() ? go(std::integral_constant<int, 16>{})
                              : go(std::integral_constant<int, NC_TY>{});
 }
 

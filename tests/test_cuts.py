@@ -14,6 +14,10 @@ WRAP = r"""
 extern "C" int level_part(long tiles, int chunks, int cus, int held) {
   return stereo::level_part(tiles, chunks, cus, held);
 }
+extern "C" int segment_rows(double total, double w, int br, int cus) {
+  return stereo::segment_rows(total, w, br, cus);
+}
+extern "C" int cost(int nblk, int most) { return (int)stereo::block_row_cost(nblk, most); }
 """
 
 
@@ -42,3 +46,22 @@ def test_level_parts_of_workgroups_alone_on_a_cu(cuts, cus, tiles, chunks):
     assert rounds(per) == min(rounds(k) for k in range(1, chunks + 1))
     if t % cus == 0:
         assert per == chunks
+
+
+@pytest.mark.parametrize("cus", [256, 128, 32])
+def test_segments_by_the_number_of_cus(cuts, cus):
+    """A queued launch makes about four segments a workgroup, whatever the
+    number of CUs: strips of 270 block rows, 60 of them in a volume, in 40
+    volumes; and a small launch keeps segments of at least eight block rows."""
+    w, br, strips = 6.0, 270, 60 * 40
+    rows = cuts.segment_rows(ctypes.c_double(w * br * strips), ctypes.c_double(w), br, cus)
+    per = -(-br // rows) * strips / cus
+    # whole strips where they are more than four a workgroup
+    assert rows == br if strips >= 4 * cus else 3.5 <= per <= 5.0
+    assert cuts.segment_rows(ctypes.c_double(w * 60), ctypes.c_double(w), 60, cus) >= 7
+
+
+@pytest.mark.parametrize("nblk,sweeps,per", [(1, 1, 1), (4, 1, 4), (5, 2, 3), (6, 2, 3), (7, 2, 4),
+                                             (8, 2, 4), (9, 3, 3), (16, 4, 4)])
+def test_cost_of_a_block_row_counts_what_its_sweeps_compute(cuts, nblk, sweeps, per):
+    assert cuts.cost(nblk, 4) == sweeps * (2 + per)
