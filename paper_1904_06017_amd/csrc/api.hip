@@ -1,6 +1,5 @@
 // C ABI: plans (pure host state), parameter validation, workspace layout and
 // the enqueue entry points declared in include/stereo.h.
-#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -117,13 +116,17 @@ void layout(Plan& P) {
   P.off_cvol = o;  o = align256(o + (quad_bytes > h2_bytes ? quad_bytes : h2_bytes));
   P.off_dT = o;    o = align256(o + sizeof(int16_t) * (size_t)W * H);
   P.off_dsub = o;  o = align256(o + sizeof(float) * (size_t)W * H);
-  // selection state of ranges above 64 levels: both volumes of a match, or the
-  // soft-argmin forward of a float plan
-  const int state = P.p.dtype == STEREO_F32 ? std::max(2 * h2_state_floats(D, 1), h2_state_floats(D, 2))
-                                            : 2 * h2_state_floats(D, 1);
-  P.off_state = o; o = align256(o + sizeof(float) * (size_t)state * W * H);
+  // selection state of ranges above 64 levels: the reference volume's in the
+  // block statistics, which nothing reads after the volumes are formed; the
+  // target volume's, and the soft-argmin forward's, in a float plan among the
+  // backward's regions, else in one of its own
+  const size_t state = sizeof(float) * (size_t)h2_state_floats(D, 1) * W * H;
+  P.off_state = P.off_stats;
+  P.off_state2 = o;
+  if (P.p.dtype != STEREO_F32) o = align256(o + state);
   P.off_road = o;  o = align256(o + sizeof(double) * 10 * (size_t)P.road_blocks);
   P.ws_bytes = grad_layout(P, o);
+  if (P.p.dtype == STEREO_F32) P.off_state2 = P.g_off[0];
 }
 
 template <typename T>
@@ -428,7 +431,7 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
     b.guide_pitch = P.W;
     b.dint = dT;
     b.dsub = nullptr;
-    b.state = a.state + (size_t)h2_state_floats(P.D, 1) * P.W * P.H;
+    b.state = at<float>(ws, P.off_state2);
   }
   // both volumes in one launch on the split-FP16 matrix cores (more segments
   // to spread over the chip), unless the stages are timed apart

@@ -330,7 +330,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     t.guide_pitch = P.W;
     t.dint = at<int16_t>(pws, P.off_dT);
     t.dsub = nullptr;
-    t.state = a.state + (size_t)h2_state_floats(P.D, 1) * P.W * P.H;
+    t.state = at<float>(pws, P.off_state2);
     bilateral_pair(P, t, b.host_desc.data() + (2 * i + 1) * pb);
   }
   BHIP(hipMemcpyAsync(at<char>(ws, b.desc_off), b.host_desc.data(), b.desc_bytes,

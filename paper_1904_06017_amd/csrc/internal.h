@@ -34,7 +34,7 @@ struct Plan {
   int stats_w;        // block-statistics map width: columns [-r, W + r)
   int cw;             // row pitch of the internal cost volume (>= W + D - 1),
                       // stored level-quad-interleaved: [ceil(D/4)][H][cw] float4
-  size_t off_tarw, off_stats, off_cvol, off_dT, off_dsub, off_state, off_road;
+  size_t off_tarw, off_stats, off_cvol, off_dT, off_dsub, off_state, off_state2, off_road;
   size_t ws_bytes;
   int road_blocks;    // partial-sum blocks of the road moments
   // tuning (stereo_plan_set_tuning): levels per aggregation pass by guide type

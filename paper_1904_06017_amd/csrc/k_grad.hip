@@ -865,6 +865,8 @@ size_t grad_layout(Plan& P, size_t o) {
   sz[GR_PART_A] = sizeof(double) * 3 * nb;
   sz[GR_PART_B] = sizeof(double) * 3 * nb;
   sz[GR_GMAX] = 2 * sizeof(float);
+  // (the forward's selection state, 64 bytes a pixel above 64 levels, begins at
+  // the first: nine maps and three of at least four levels are 84)
   for (int i = 0; i < GR_COUNT; ++i) {
     P.g_off[i] = o;
     o = align256(o + sz[i]);
@@ -987,7 +989,7 @@ stereo_status stereo_soft_forward(stereo_plan_t plan, const float* ref, const fl
   a.sm_dh = saved + 2 * HW;
   a.disp = disp_soft;
   a.plane[0] = plane[0]; a.plane[1] = plane[1]; a.plane[2] = plane[2];
-  a.state = at<float>(ws, P.off_state);
+  a.state = at<float>(ws, P.off_state2);
   HIPC(a.h2 ? launch_bilateral_h2(P, &a, 1, 2, stream) : launch_bilateral(P, a, 2, stream),
        "aggregation + soft-argmin");
   return STEREO_OK;
