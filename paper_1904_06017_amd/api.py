@@ -397,8 +397,10 @@ def photometric_l1_bwd(plan: Plan, ref, tar, disp, grad_loss=1.0):
     g_tar = torch.empty((plan.H, plan.W), dtype=torch.float32, device=dev)
     g_disp = torch.empty((plan.H, plan.W), dtype=torch.float32, device=dev)
     ws = plan.workspace(dev)
+    # (a zero tensor or a sparse one holds no value there and is read by the host)
     if type(grad_loss) is torch.Tensor and grad_loss.device == dev and \
-            grad_loss.dtype == torch.float64 and grad_loss.numel() == 1:
+            grad_loss.dtype == torch.float64 and grad_loss.numel() == 1 and \
+            grad_loss.layout == torch.strided and not grad_loss._is_zerotensor():
         # stays on the device: reading it here would wait for everything before it
         # (a training step 1280x720, 48 levels 1496 -> 1444 us, 317x243, 40 levels 476 -> 462 us)
         grad_loss = grad_loss.resolve_neg()
