@@ -32,3 +32,25 @@ def _check(form, value):
 def test_forms_without_a_value_in_memory(name):
     value = 0.0 if name == "zero" else -0.37
     _check(FORMS[name](value), value)
+
+
+OTHERS = {
+    "float32 on the device": lambda v: torch.tensor(v, dtype=torch.float32, device="cuda"),
+    "float16 on the device": lambda v: torch.tensor([v], dtype=torch.float16, device="cuda"),
+    "float64 on the host": lambda v: torch.tensor([[v]], dtype=F64),
+    "float32 on the host": lambda v: torch.tensor(v, dtype=torch.float32),
+    "int on the device": lambda v: torch.tensor(3, device="cuda"),
+    "negated view": lambda v: torch._neg_view(torch.tensor(-v, dtype=F64, device="cuda")),
+    "column of a matrix": lambda v: torch.full((3, 2), v, dtype=F64, device="cuda")[1:2, 1:],
+    "requires grad": lambda v: torch.tensor(v, dtype=F64, device="cuda", requires_grad=True).clone(),
+    "numpy": lambda v: np.float64(v),
+}
+
+
+@pytest.mark.parametrize("value", [1.0, -0.37, 1e-30, float("inf")])
+@pytest.mark.parametrize("name", list(OTHERS))
+def test_forms_with_a_value_in_memory(name, value):
+    """Of other types than float64 the value read is the type's: a float32 must
+    not be taken for half of a double."""
+    form = OTHERS[name](value)
+    _check(form, float(form.detach() if isinstance(form, torch.Tensor) else form))
