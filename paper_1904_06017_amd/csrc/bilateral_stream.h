@@ -305,7 +305,7 @@ struct Worker {
       cpair[m] = c >= 2 * PARTS * NB ? 1 : 0;
       const int w = c - cpair[m] * 2 * PARTS * NB, q = w / (2 * PARTS), half = w & 1;
       const int part = (w >> 1) - PARTS * q;
-      const int blk = q0 + q < nblk ? q0 + q : nblk - 1;
+      const int blk = q0 + q;
       csrc[m] = (part < 2 ? v.V + (int64_t)(2 * blk + part) * v.plane : bk.h3 + blk * v.plane) +
                 32 * x0 + half * (G::NQH * 64);
       cdst[m] = (PARTS * q + part) * Z::CHB + half * (Z::CHB / 2);
@@ -898,8 +898,9 @@ __device__ __forceinline__ void spatial_table(float* t, float ks2) {
 template <int R, int MODE>
 __device__ __forceinline__ void segment(const View& v, const Back& bk, int x0, int b0, int len,
                                         float* lds) {
-  const int nblk = (v.D + 15) / 16, nb = sweep_blocks(nblk, max_blocks(MODE));
-  for (int q0 = 0; q0 < nblk; q0 += nb) {
+  const int nblk = (v.D + 15) / 16;
+  for (int q0 = 0, nb = 0; q0 < nblk; q0 += nb) {
+    nb = sweep_blocks(nblk - q0, max_blocks(MODE));
     // the state a sweep leaves is read by the next one in the same wave (block
     // rows and lanes keep their waves): program order is enough.  A fence of
     // the whole device here cost 56 us a segment.

@@ -5,19 +5,18 @@
 
 namespace stereo {
 
-// Level blocks per sweep of the streamed aggregation for nblk blocks: even
-// shares of at most `most`.
+// Level blocks of the streamed aggregation's next sweep with nblk blocks still
+// to do: even shares of at most `most`, the larger ones first (13 in sweeps of
+// at most 4: 4, 3, 3, 3).
 constexpr int sweep_blocks(int nblk, int most) {
   const int n = (nblk + most - 1) / most;
   return (nblk + n - 1) / n;
 }
 
 // Cost of a block row of nblk level blocks in sweeps of at most `most`: the
-// weights once per sweep (2), the products per block that a sweep computes
-// (padding of an uneven count included).
+// weights once per sweep (2), the products per block.
 inline double block_row_cost(int nblk, int most) {
-  const int per = sweep_blocks(nblk, most);
-  return (double)((nblk + per - 1) / per) * (2 + per);
+  return 2.0 * ((nblk + most - 1) / most) + nblk;
 }
 
 // Block rows of a segment of a queued launch: br block rows of cost w each, cut

@@ -17,6 +17,7 @@ extern "C" int level_part(long tiles, int chunks, int cus, int held) {
 extern "C" int segment_rows(double total, double w, int br, int cus) {
   return stereo::segment_rows(total, w, br, cus);
 }
+extern "C" int sweep_blocks(int nblk, int most) { return stereo::sweep_blocks(nblk, most); }
 extern "C" int cost(int nblk, int most) { return (int)stereo::block_row_cost(nblk, most); }
 """
 
@@ -61,7 +62,15 @@ def test_segments_by_the_number_of_cus(cuts, cus):
     assert cuts.segment_rows(ctypes.c_double(w * 60), ctypes.c_double(w), 60, cus) >= 7
 
 
-@pytest.mark.parametrize("nblk,sweeps,per", [(1, 1, 1), (4, 1, 4), (5, 2, 3), (6, 2, 3), (7, 2, 4),
-                                             (8, 2, 4), (9, 3, 3), (16, 4, 4)])
-def test_cost_of_a_block_row_counts_what_its_sweeps_compute(cuts, nblk, sweeps, per):
-    assert cuts.cost(nblk, 4) == sweeps * (2 + per)
+@pytest.mark.parametrize("most", [3, 4])
+@pytest.mark.parametrize("nblk", range(1, 17))
+def test_sweeps_compute_every_level_block_once(cuts, nblk, most):
+    """As few sweeps as hold the blocks, none empty, each block in one of them;
+    the cost of a block row counts the weights of each sweep and the blocks."""
+    left, sweeps = nblk, []
+    while left > 0:
+        sweeps.append(cuts.sweep_blocks(left, most))
+        left -= sweeps[-1]
+    assert left == 0 and min(sweeps) >= 1 and max(sweeps) <= most
+    assert len(sweeps) == -(-nblk // most) and max(sweeps) - min(sweeps) <= 1
+    assert cuts.cost(nblk, most) == 2 * len(sweeps) + nblk
