@@ -33,7 +33,7 @@ struct Group {
 // The split-FP16 engine's groups: every volume of one radius, both guide
 // types, as strip segments sorted longest first.
 struct SegGroup {
-  int R;
+  int R, duo;                 // duo: see launch_bilateral_h2_queue
   std::vector<Seg> segs;
   size_t off;                 // in the workspace
 };
@@ -123,7 +123,6 @@ void ncc_blocks(stereo_batch_s& b) {
 // range (their halo columns meet in an XCD's L2) and sorted by cost, longest
 // first.  The tables' places in the workspace stay as they are.
 void seg_tables(stereo_batch_s& b, int cus) {
-  constexpr int kFill = 6;             // phases a segment takes beyond its block rows
   struct V { int pair, vol; double w; };
   struct S { double cost; Seg seg; };
   std::vector<size_t> off;
@@ -138,6 +137,7 @@ void seg_tables(stereo_batch_s& b, int cus) {
     if (g == b.seg_groups.size()) {
       SegGroup G;
       G.R = P.R;
+      G.duo = 0;
       G.off = g < off.size() ? off[g] : 0;
       b.seg_groups.push_back(G);
       vols.emplace_back();
@@ -146,26 +146,35 @@ void seg_tables(stereo_batch_s& b, int cus) {
       vols[g].push_back({i, vol, block_row_cost((P.D + 15) / 16, 4)});
   }
   for (size_t g = 0; g < b.seg_groups.size(); ++g) {
+    SegGroup& G = b.seg_groups[g];
     double total = 0.0;
+    long rows = 0;
     for (const V& v : vols[g]) {
       const Plan& P = b.plans[v.pair];
-      total += v.w * ((P.W + kSegW - 1) / kSegW) * ((P.H + kSegRow - 1) / kSegRow);
+      const long n = (long)((P.W + kSegW - 1) / kSegW) * ((P.H + kSegRow - 1) / kSegRow);
+      total += v.w * n;
+      rows += n;
     }
+    G.duo = G.R <= kDuoR;
+    for (const V& v : vols[g])
+      if (G.R > 2 && !duo_launch((b.plans[v.pair].D + 15) / 16, rows, cus)) G.duo = 0;
+    // phases a segment takes beyond its block rows
+    const int wgs = G.duo ? 2 * cus : cus, fill = G.duo ? 4 : 6;
     std::vector<S> all;
     for (const V& v : vols[g]) {
       const Plan& P = b.plans[v.pair];
       const int tx = (P.W + kSegW - 1) / kSegW, br = (P.H + kSegRow - 1) / kSegRow;
-      const int len = segment_rows(total, v.w, br, cus);
+      const int len = segment_rows(total, v.w, br, wgs);
       for (int xb = 0; xb < tx; xb += b.tile_band)
         for (int r = 0; r < br; r += len)
           for (int x = xb; x < std::min(tx, xb + b.tile_band); ++x) {
             const int l = std::min(len, br - r);
-            all.push_back({v.w * (l + kFill), {2 * v.pair + v.vol, x * kSegW, r, l}});
+            all.push_back({v.w * (l + fill), {2 * v.pair + v.vol, x * kSegW, r, l}});
           }
     }
     std::stable_sort(all.begin(), all.end(), [](const S& a, const S& c) { return a.cost > c.cost; });
-    b.seg_groups[g].segs.clear();
-    for (const S& e : all) b.seg_groups[g].segs.push_back(e.seg);
+    G.segs.clear();
+    for (const S& e : all) G.segs.push_back(e.seg);
   }
 }
 
@@ -222,9 +231,9 @@ void build_layout(stereo_batch_s& b) {
     table(per[gi], b.groups[gi].tiles, b.groups[gi].tiles_off);
     table(per_m[gi], b.groups[gi].tiles_m, b.groups[gi].tiles_m_off);
   }
-  // laid out for kMaxCus CUs (fewer CUs make fewer, longer segments), so that
-  // the workspace does not depend on the device
-  seg_tables(b, kMaxCus);
+  // laid out for two workgroups on each of kMaxCus CUs (fewer make fewer, longer
+  // segments), so that the workspace does not depend on the device
+  seg_tables(b, 2 * kMaxCus);
   for (SegGroup& G : b.seg_groups) {
     G.off = o;
     o = align256(o + sizeof(Seg) * G.segs.size());
@@ -454,11 +463,10 @@ stereo_status enqueue(stereo_batch_s& b, hipStream_t s, hipEvent_t* ev = nullptr
   const void* desc = at<char>(ws, b.desc_off);
   auto group_R = [&](int g) { return b.engine == 2 ? b.seg_groups[g].R : b.groups[g].R; };
   auto run_group = [&](int g, hipStream_t st) -> stereo_status {
-    if (b.engine == 2) {                 // one workgroup per CU holds the whole LDS
+    if (b.engine == 2) {
       const SegGroup& G = b.seg_groups[g];
       const int n = (int)G.segs.size();
-      BHIP(launch_bilateral_h2_queue(G.R, desc, at<Seg>(ws, G.off), n,
-                                     std::max(1, std::min(n, b.cu_count)), st),
+      BHIP(launch_bilateral_h2_queue(G.R, desc, at<Seg>(ws, G.off), n, G.duo, st),
            "batch aggregation");
       return STEREO_OK;
     }

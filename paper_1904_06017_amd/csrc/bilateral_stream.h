@@ -65,16 +65,24 @@ constexpr int kMaxNB = 4;               // level blocks per sweep
 constexpr int kMaxWide = 3;
 constexpr float kMaxFloat = 3.402823466e38f;
 constexpr int parts_of(int mode) { return mode == 5 ? 3 : 2; }
-constexpr int max_blocks(int mode) { return mode == 5 ? kMaxWide : kMaxNB; }
+constexpr int max_blocks(int R, int mode, int duo) {
+  return mode == 5 ? kMaxWide : duo && R > 2 ? kDuoBlocks : kMaxNB;
+}
+// Workgroups that share a CU.  A phase waits for the copies that it issues,
+// about 1 us; at small radii its products do not fill that time, so there two
+// workgroups of two groups each share a CU and one computes while the other
+// waits (DUO: radii 1 and 2, and launches that duo_launch takes).  Match at
+// 1280x720: R = 1, 16 levels 182 -> 134 us; R = 2, 64 levels 348 -> 279 us.
+constexpr int held(int duo) { return duo ? 2 : 1; }
 
 // Products of the S states of a block and the row pairs they read, relative
 // to the block's first: state k takes products [ps(k), ps(k + 1)).  In phase
 // t state k works on block row t - k, so it reads pairs lo(k) - 2 k .. hi(k) -
 // 2 k relative to pair 2 t.
-template <int R>
+template <int R, int DUO>
 struct Sched {
   using G = HGeom<R>;
-  static constexpr int S = G::NI >= 4 ? 4 : 2;
+  static constexpr int S = G::NI >= 4 && !DUO ? 4 : 2;
   // The group in state 0 also selects the levels of its last block: it gets
   // one product less than an even share where that leaves it one.
   static constexpr int ps(int k) {
@@ -99,10 +107,10 @@ struct Sched {
 
 // MODE 1: winner-take-all, 2: soft-argmin, 3 / 4: pass 1 / 2 of its backward,
 // 5: pass 2 on BF16 parts (R >= kWideR).
-template <int R, int NB, int MODE>
+template <int R, int NB, int MODE, int DUO>
 struct SGeom {
   using G = HGeom<R>;
-  using C = Sched<R>;
+  using C = Sched<R, DUO>;
   static constexpr int S = C::S;
   static constexpr int kWaves = 4 * S, kThreads = 64 * kWaves;
   static constexpr int WLO = C::wlo(), WHI = C::whi();
@@ -129,16 +137,16 @@ struct SGeom {
       MODE == 1 ? 64 * EROW : MODE == 3 ? 2 * CBLK : MODE >= 4 ? 2 * PBLK : 0;
   static constexpr size_t lds_bytes = (size_t)NSLOT * SLOTB + (size_t)NGS * GSB +
                                       sizeof(float) * G::STAB + SCRATCH;
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget");
+  static_assert(held(DUO) * lds_bytes <= 160 * 1024, "LDS budget");
   static_assert((PARTS * NB - 1) * CHB < 65536, "operand offsets must fit a DS immediate");
   static_assert(NGV <= kThreads, "one guide value per thread");
 };
 
 // LDS of a launch, laid out for the most blocks whatever a sweep takes: ring,
 // guide ring, spatial terms, scratch.
-template <int R, int MODE>
+template <int R, int MODE, int DUO>
 struct Lds {
-  using Z = SGeom<R, max_blocks(MODE), MODE>;
+  using Z = SGeom<R, max_blocks(R, MODE, DUO), MODE, DUO>;
   static constexpr int gring = Z::NSLOT * Z::SLOTB;
   static constexpr int tab = gring + Z::NGS * Z::GSB;
   static constexpr int scratch = tab + (int)sizeof(float) * HGeom<R>::STAB;
@@ -256,12 +264,12 @@ struct Int {
   static constexpr int value = K;
 };
 
-template <int R, int MODE, int NB>
+template <int R, int MODE, int DUO, int NB>
 struct Worker {
   using G = HGeom<R>;
-  using C = Sched<R>;
-  using Z = SGeom<R, NB, MODE>;
-  using L = Lds<R, MODE>;
+  using C = Sched<R, DUO>;
+  using Z = SGeom<R, NB, MODE, DUO>;
+  using L = Lds<R, MODE, DUO>;
   static constexpr int S = C::S;
   static constexpr bool TWO = MODE >= 3;             // the second weight w (G(p) - G(q))
 
@@ -879,12 +887,12 @@ struct Worker {
 
 // Spatial terms of every lane's slots, 12 - |p - q|^2 log2(e) / sigma_s^2, -inf
 // outside the pixel's window and for padding patches.
-template <int R>
+template <int R, int DUO>
 __device__ __forceinline__ void spatial_table(float* t, float ks2) {
   using G = HGeom<R>;
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int e = wave; e < G::NI * 8; e += 4 * Sched<R>::S) {
+  for (int e = wave; e < G::NI * 8; e += 4 * Sched<R, DUO>::S) {
     const int i = e >> 3, s = e & 7;
     const int p = 4 * i + lk, rp = p / G::NCQ, cq = p - rp * G::NCQ;
     const int ty = 2 * rp + (s >> 2) - (li >> 2) - R, tx = 4 * cq + (s & 3) - (li & 3) - R;
@@ -895,27 +903,28 @@ __device__ __forceinline__ void spatial_table(float* t, float ks2) {
 }
 
 // Every sweep of one segment.
-template <int R, int MODE>
+template <int R, int MODE, int DUO>
 __device__ __forceinline__ void segment(const View& v, const Back& bk, int x0, int b0, int len,
                                         float* lds) {
   const int nblk = (v.D + 15) / 16;
   for (int q0 = 0, nb = 0; q0 < nblk; q0 += nb) {
-    nb = sweep_blocks(nblk - q0, max_blocks(MODE));
+    constexpr int most = max_blocks(R, MODE, DUO);
+    nb = sweep_blocks(nblk - q0, most);
     // the state a sweep leaves is read by the next one in the same wave (block
     // rows and lanes keep their waves): program order is enough.  A fence of
     // the whole device here cost 56 us a segment.
-    if (max_blocks(MODE) == 4 && nb == 4)
-      Worker<R, MODE, max_blocks(MODE)>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
-    else if (nb == 3) Worker<R, MODE, 3>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
-    else if (nb == 2) Worker<R, MODE, 2>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
-    else Worker<R, MODE, 1>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    if (most == 4 && nb == 4) Worker<R, MODE, DUO, most>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else if (nb == 3) Worker<R, MODE, DUO, 3>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else if (nb == 2) Worker<R, MODE, DUO, 2>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
+    else Worker<R, MODE, DUO, 1>(lds).sweep(v, bk, x0, b0, len, q0, nblk);
   }
 }
 
-template <int R, int MODE, int QUEUE>
-__global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args a, Back bk) {
+template <int R, int MODE, int QUEUE, int DUO>
+__global__ void __launch_bounds__((256 * Sched<R, DUO>::S), (held(DUO) * Sched<R, DUO>::S))
+agg_stream_kernel(Args a, Back bk) {
   extern __shared__ float lds[];
-  float* tab = lds + Lds<R, MODE>::tab / 4;
+  float* tab = lds + Lds<R, MODE, DUO>::tab / 4;
   if constexpr (QUEUE) {
     // round k of G workgroups covers entries [k G, (k + 1) G); workgroup b (XCD
     // b % 8) takes entry k G + (b % 8) G / 8 + b / 8, so that each XCD works on
@@ -930,12 +939,12 @@ __global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args
       // barrier is behind every read of the table, a sweep's first one ahead
       if (v.ks2 != ks2) {
         ks2 = v.ks2;
-        spatial_table<R>(tab, ks2);
+        spatial_table<R, DUO>(tab, ks2);
       }
-      segment<R, MODE>(v, bk, e.x0, e.b0, e.len, lds);
+      segment<R, MODE, DUO>(v, bk, e.x0, e.b0, e.len, lds);
     }
   } else {
-    spatial_table<R>(tab, a.v[0].ks2);
+    spatial_table<R, DUO>(tab, a.v[0].ks2);
     // banded: XCD x = b % 8 owns a band of strips; its workgroups run adjacent
     // strips of one vertical range at a time, whose shared halo columns meet
     // in its L2
@@ -953,18 +962,18 @@ __global__ void __launch_bounds__((256 * Sched<R>::S), 1) agg_stream_kernel(Args
       const int seg = rem / bc, strip = c0 + rem - seg * bc;
       const int b0 = seg * a.len;
       const int len = min(a.len, a.br - b0);
-      if (len > 0) segment<R, MODE>(a.v[vol], bk, strip * kTW, b0, len, lds);   // uniform
+      if (len > 0) segment<R, MODE, DUO>(a.v[vol], bk, strip * kTW, b0, len, lds);   // uniform
     }
   }
 }
 
-template <int R, int MODE, int QUEUE>
+template <int R, int MODE, int QUEUE, int DUO>
 hipError_t set_lds_attr() {
   static bool done = false;
   if (!done) {
-    hipError_t e = hipFuncSetAttribute((const void*)agg_stream_kernel<R, MODE, QUEUE>,
+    hipError_t e = hipFuncSetAttribute((const void*)agg_stream_kernel<R, MODE, QUEUE, DUO>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)Lds<R, MODE>::bytes);
+                                       (int)Lds<R, MODE, DUO>::bytes);
     if (e != hipSuccess) return e;
     done = true;
   }
@@ -996,28 +1005,28 @@ inline void cut_strips(int tx, int br, int nvol, int S, int cus, int& nseg, int&
 }
 
 // One or two volumes of a pair (the same size, radius and sigmas).
-template <int R, int MODE>
+template <int R, int MODE, int DUO>
 hipError_t launch_pair(const BilPair* p, int nvol, hipStream_t s, const Back& bk = Back{}) {
   Args a{};
   for (int k = 0; k < nvol; ++k) {
     const BilPair& b = p[k];
     if (!b.h2 || b.h2_pitch < bilh::h2_pitch_for<R>(b.W) || (b.h2_pitch & 7) ||
         b.h2_plane < 16 * (int64_t)h2_rows(R, b.H) * b.h2_pitch || b.W != p[0].W ||
-        b.H != p[0].H || b.D != p[0].D || (b.D > 16 * kMaxNB && !b.state))
+        b.H != p[0].H || b.D != p[0].D || (MODE <= 2 && b.D > 16 * max_blocks(R, MODE, DUO) && !b.state))
       return hipErrorInvalidValue;
     a.v[k] = bilh::view_of(b);
   }
-  hipError_t e = set_lds_attr<R, MODE, 0>();
+  hipError_t e = set_lds_attr<R, MODE, 0, DUO>();
   if (e != hipSuccess) return e;
-  const int cus = device_cus();
+  const int cus = held(DUO) * device_cus();            // workgroups at a time
   a.nvol = nvol;
   a.tx = (p[0].W + kTW - 1) / kTW;
   a.br = (p[0].H + 3) / 4;
-  cut_strips(a.tx, a.br, nvol, Sched<R>::S, cus, a.nseg, a.banded);
+  cut_strips(a.tx, a.br, nvol, Sched<R, DUO>::S, cus, a.nseg, a.banded);
   a.len = (a.br + a.nseg - 1) / a.nseg;
   const int grid = a.banded ? cus : std::min(cus, nvol * a.tx * a.nseg);
-  hipLaunchKernelGGL((agg_stream_kernel<R, MODE, 0>), dim3(grid), dim3(256 * Sched<R>::S),
-                     (Lds<R, MODE>::bytes), s, a, bk);
+  hipLaunchKernelGGL((agg_stream_kernel<R, MODE, 0, DUO>), dim3(grid), dim3(256 * Sched<R, DUO>::S),
+                     (Lds<R, MODE, DUO>::bytes), s, a, bk);
   return hipGetLastError();
 }
 
@@ -1026,7 +1035,14 @@ hipError_t launch_args(const Plan& P, const BilArgs* a, int nvol, int mode, hipS
   if (nvol < 1 || nvol > 2 || (mode != 1 && mode != 2)) return hipErrorInvalidValue;
   BilPair p[2];
   for (int k = 0; k < nvol; ++k) p[k] = bil::make_pair(P, a[k]);
-  return mode == 2 ? launch_pair<R, 2>(p, nvol, s) : launch_pair<R, 1>(p, nvol, s);
+  if constexpr (R <= kDuoR) {
+    const long rows = (long)nvol * ((P.W + kTW - 1) / kTW) * ((P.H + 3) / 4);
+    if (R <= 2 || duo_launch((p[0].D + 15) / 16, rows, device_cus()))
+      return mode == 2 ? launch_pair<R, 2, 1>(p, nvol, s) : launch_pair<R, 1, 1>(p, nvol, s);
+  }
+  if constexpr (R > 2)
+    return mode == 2 ? launch_pair<R, 2, 0>(p, nvol, s) : launch_pair<R, 1, 0>(p, nvol, s);
+  return hipErrorInvalidValue;
 }
 
 // Pass 1 or 2 of the backward for one level tile (at most 64 levels, float
@@ -1058,23 +1074,32 @@ hipError_t launch_back(const Plan& P, const BilArgs& a, int pass, hipStream_t s)
   b.one_minus_c1 = p.o.one_minus_c1;
   b.d_first = a.d_first;
   b.d_all = P.D;
-  return pass == 1 ? launch_pair<R, 3>(&p, 1, s, b)
-                   : launch_pair<R, (R >= kWideR ? 5 : 4)>(&p, 1, s, b);
+  return pass == 1 ? launch_pair<R, 3, 0>(&p, 1, s, b)
+                   : launch_pair<R, (R >= kWideR ? 5 : 4), 0>(&p, 1, s, b);
 }
 
 // n segments over many volumes (descs, segs: device arrays).
-template <int R>
-hipError_t launch_queue(const BilPair* descs, const Seg* segs, int n, int n_groups,
-                        hipStream_t s) {
-  hipError_t e = set_lds_attr<R, 1, 1>();
+template <int R, int DUO>
+hipError_t launch_queue(const BilPair* descs, const Seg* segs, int n, hipStream_t s) {
+  hipError_t e = set_lds_attr<R, 1, 1, DUO>();
   if (e != hipSuccess) return e;
   Args a{};
   a.descs = descs;
   a.segs = segs;
   a.n = n;
-  hipLaunchKernelGGL((agg_stream_kernel<R, 1, 1>), dim3(n_groups), dim3(256 * Sched<R>::S),
-                     (Lds<R, 1>::bytes), s, a, Back{});
+  const int grid = std::max(1, std::min(n, held(DUO) * device_cus()));
+  hipLaunchKernelGGL((agg_stream_kernel<R, 1, 1, DUO>), dim3(grid), dim3(256 * Sched<R, DUO>::S),
+                     (Lds<R, 1, DUO>::bytes), s, a, Back{});
   return hipGetLastError();
+}
+
+// duo: every volume of the list is one that duo_launch takes.
+template <int R>
+hipError_t launch_queue_r(const BilPair* descs, const Seg* segs, int n, int duo, hipStream_t s) {
+  if constexpr (R <= 2) return launch_queue<R, 1>(descs, segs, n, s);
+  else if constexpr (R <= kDuoR)
+    return duo ? launch_queue<R, 1>(descs, segs, n, s) : launch_queue<R, 0>(descs, segs, n, s);
+  else return launch_queue<R, 0>(descs, segs, n, s);
 }
 
 }  // namespace bils

@@ -19,12 +19,31 @@ inline double block_row_cost(int nblk, int most) {
   return 2.0 * ((nblk + most - 1) / most) + nblk;
 }
 
+// Radii whose streamed aggregation may run with two workgroups on a CU, and the
+// level blocks of a sweep that leave the LDS room for them at radii 3 and 4.
+constexpr int kDuoR = 4, kDuoBlocks = 3;
+
+// Radii 3 and 4: two workgroups a CU (1) or one (0), for nblk level blocks and
+// rows block rows in the launch.  Not for four blocks: two sweeps there would
+// need a state between them that plans up to 64 levels have no room for.
+// Where three blocks a sweep make more sweeps than four do, only in launches of
+// at least eight block rows a workgroup; in shorter ones the sweeps' ends cost
+// more than the wait.  Match at R = 4, one workgroup -> two: 1280x720, 16 levels
+// 207 -> 161 us, 80 levels 550 -> 436; 320x240, 80 levels 74.3 -> 66.3; two
+// sweeps -> three: 128 levels, 640x480 251 -> 246, 320x240 86.0 -> 88.9 (soft
+// forward 65.0 -> 69.4).
+inline int duo_launch(int nblk, long rows, int cus) {
+  if (nblk == 4) return 0;
+  if ((nblk + 2) / 3 == (nblk + 3) / 4) return 1;
+  return rows >= 16l * cus ? 1 : 0;
+}
+
 // Block rows of a segment of a queued launch: br block rows of cost w each, cut
 // so that the launch (total cost) makes about four segments for each of its
-// cus workgroups.  A segment fills and drains its pipeline of block rows, so
+// wgs workgroups.  A segment fills and drains its pipeline of block rows, so
 // it has at least eight.
-inline int segment_rows(double total, double w, int br, int cus) {
-  const int want = std::max(8, (int)(total / (4.0 * cus) / w));
+inline int segment_rows(double total, double w, int br, int wgs) {
+  const int want = std::max(8, (int)(total / (4.0 * wgs) / w));
   const int n = std::max(1, (br + want - 1) / want);
   return (br + n - 1) / n;
 }

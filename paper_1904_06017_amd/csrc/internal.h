@@ -183,8 +183,9 @@ struct Seg {                  // block rows [b0, b0 + len) of the strip at colum
   int desc, x0, b0, len;
 };
 constexpr int kSegW = 16, kSegRow = 4;   // strip columns, rows of a block row
-hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n,
-                                     int n_groups, hipStream_t s);
+// duo: every volume is one that duo_launch takes (radii 3 and 4).
+hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n, int duo,
+                                     hipStream_t s);
 
 // Radii whose backward carries C' in three BF16 parts (FP32's range and bits);
 // below, two FP16 parts under one scale for the image.

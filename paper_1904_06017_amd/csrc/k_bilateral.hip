@@ -120,16 +120,16 @@ hipError_t launch_bilateral_h2(const Plan& P, const BilArgs* a, int n, int mode,
 }
 
 hipError_t launch_bilateral_h2_queue(int R, const void* descs, const Seg* segs, int n,
-                                     int n_groups, hipStream_t s) {
+                                     int duo, hipStream_t s) {
   switch (R) {
-    case 1: return launch_bilateral_h2_queue_r1(descs, segs, n, n_groups, s);
-    case 2: return launch_bilateral_h2_queue_r2(descs, segs, n, n_groups, s);
-    case 3: return launch_bilateral_h2_queue_r3(descs, segs, n, n_groups, s);
-    case 4: return launch_bilateral_h2_queue_r4(descs, segs, n, n_groups, s);
-    case 5: return launch_bilateral_h2_queue_r5(descs, segs, n, n_groups, s);
-    case 6: return launch_bilateral_h2_queue_r6(descs, segs, n, n_groups, s);
-    case 7: return launch_bilateral_h2_queue_r7(descs, segs, n, n_groups, s);
-    case 8: return launch_bilateral_h2_queue_r8(descs, segs, n, n_groups, s);
+    case 1: return launch_bilateral_h2_queue_r1(descs, segs, n, duo, s);
+    case 2: return launch_bilateral_h2_queue_r2(descs, segs, n, duo, s);
+    case 3: return launch_bilateral_h2_queue_r3(descs, segs, n, duo, s);
+    case 4: return launch_bilateral_h2_queue_r4(descs, segs, n, duo, s);
+    case 5: return launch_bilateral_h2_queue_r5(descs, segs, n, duo, s);
+    case 6: return launch_bilateral_h2_queue_r6(descs, segs, n, duo, s);
+    case 7: return launch_bilateral_h2_queue_r7(descs, segs, n, duo, s);
+    case 8: return launch_bilateral_h2_queue_r8(descs, segs, n, duo, s);
     default: return hipErrorInvalidValue;
   }
 }

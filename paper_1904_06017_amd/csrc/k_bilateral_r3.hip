@@ -11,9 +11,9 @@ hipError_t launch_bilateral_h2_r3(const Plan& P, const BilArgs* a, int n, int mo
                                   hipStream_t s) {
   return bils::launch_args<3>(P, a, n, mode, s);
 }
-hipError_t launch_bilateral_h2_queue_r3(const void* descs, const Seg* segs, int n, int n_groups,
+hipError_t launch_bilateral_h2_queue_r3(const void* descs, const Seg* segs, int n, int duo,
                                         hipStream_t s) {
-  return bils::launch_queue<3>(static_cast<const bil::BilPair*>(descs), segs, n, n_groups, s);
+  return bils::launch_queue_r<3>(static_cast<const bil::BilPair*>(descs), segs, n, duo, s);
 }
 hipError_t launch_bilateral_persistent_r3(int engine, stereo_dtype gdt, int levels, const void* pairs,
                                            const int* tiles, int n_tiles, unsigned int* counter,

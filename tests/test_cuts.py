@@ -17,6 +17,7 @@ extern "C" int level_part(long tiles, int chunks, int cus, int held) {
 extern "C" int segment_rows(double total, double w, int br, int cus) {
   return stereo::segment_rows(total, w, br, cus);
 }
+extern "C" int duo_launch(int nblk, long rows, int cus) { return stereo::duo_launch(nblk, rows, cus); }
 extern "C" int sweep_blocks(int nblk, int most) { return stereo::sweep_blocks(nblk, most); }
 extern "C" int cost(int nblk, int most) { return (int)stereo::block_row_cost(nblk, most); }
 """
@@ -51,8 +52,8 @@ def test_level_parts_of_workgroups_alone_on_a_cu(cuts, cus, tiles, chunks):
 
 @pytest.mark.parametrize("cus", [256, 128, 32])
 def test_segments_by_the_number_of_cus(cuts, cus):
-    """A queued launch makes about four segments a workgroup, whatever the
-    number of CUs: strips of 270 block rows, 60 of them in a volume, in 40
+    """A queued launch makes about four segments a workgroup, whatever their
+    number: strips of 270 block rows, 60 of them in a volume, in 40
     volumes; and a small launch keeps segments of at least eight block rows."""
     w, br, strips = 6.0, 270, 60 * 40
     rows = cuts.segment_rows(ctypes.c_double(w * br * strips), ctypes.c_double(w), br, cus)
@@ -74,3 +75,17 @@ def test_sweeps_compute_every_level_block_once(cuts, nblk, most):
     assert left == 0 and min(sweeps) >= 1 and max(sweeps) <= most
     assert len(sweeps) == -(-nblk // most) and max(sweeps) - min(sweeps) <= 1
     assert cuts.cost(nblk, most) == 2 * len(sweeps) + nblk
+
+
+@pytest.mark.parametrize("cus", [256, 64])
+@pytest.mark.parametrize("nblk", range(1, 17))
+def test_two_workgroups_on_a_cu(cuts, nblk, cus):
+    """Radii 3 and 4 sweep three level blocks at a time where two workgroups
+    share a CU.  More than one sweep needs a state, which plans above 64 levels
+    (four blocks) have: never at four blocks.  Where it takes more sweeps than
+    four blocks at a time, only with eight block rows a workgroup."""
+    few, many = (cuts.duo_launch(nblk, ctypes.c_long(n), cus) for n in (16 * cus - 1, 16 * cus))
+    if nblk == 4:
+        assert (few, many) == (0, 0)
+    else:
+        assert many == 1 and few == (-(-nblk // 3) == -(-nblk // 4))

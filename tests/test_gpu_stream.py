@@ -241,3 +241,36 @@ def test_loss_gradient_on_the_device(W, H, value):
         got = api.photometric_l1_bwd(plan, ref, tar, disp, grad)
         if grad.dtype == torch.float64:
             assert all(torch.equal(a.nan_to_num(9.0), b.nan_to_num(9.0)) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("R,W,H,D,dtype", [(1, 90, 41, 16, "u8"), (2, 130, 22, 100, "f32"),
+                                           (3, 95, 31, 16, "u8"), (3, 500, 300, 128, "u8"),
+                                           (4, 66, 50, 48, "f32"), (4, 500, 300, 113, "f32")])
+def test_two_workgroups_a_cu_give_the_same_bits(R, W, H, D, dtype):
+    """Small radii run with two workgroups on a CU, radii 3 and 4 by a rule on
+    levels and block rows (at 500 x 300 two volumes in one launch are enough
+    for it, one is not): the match, each volume alone and the queue of a batch,
+    whose other pair has 64 levels and so one workgroup on a CU, agree bit for
+    bit."""
+    w = _workload(R, W, H, D, dtype, perspective=False, delta_p=0.0)
+    ref, tar = (torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in _pair(R, W, H, D, dtype))
+    plan = api.Plan.from_workload(w)
+    out = api.match(plan, ref, tar, want_target=True)
+    got = {k: _host(v) for k, v in out.items()}
+    alone = {k: torch.empty_like(v) for k, v in out.items()}
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(7)]
+    for e in ev:
+        e.record()
+    ws = plan.workspace(ref.device)
+    api.check(api._lib.load().stereo_match_profiled(
+        plan.handle, api._p(ref), api._p(tar), api._p(alone["dint_R"]), api._p(alone["dint_T"]),
+        api._p(alone["dsub"]), api._p(alone["valid"]), api._p(alone["disp"]), api._p(ws),
+        plan.workspace_bytes, (ctypes.c_void_p * 7)(*[e.cuda_event for e in ev]), api._stream()))
+    for k in got:
+        assert np.array_equal(got[k], _host(alone[k]), equal_nan=True), k
+    v = _workload(R, 70, 33, 64, dtype, perspective=False, delta_p=0.0)
+    other = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in _pair(R, 70, 33, 64, dtype)]
+    for pairs in ([(plan, ref, tar)], [(plan, ref, tar), (api.Plan.from_workload(v), *other)]):
+        res = api.Batch(pairs).submit()[0]
+        for k in ("dint_R", "valid", "disp"):
+            assert np.array_equal(got[k], _host(res[k]), equal_nan=True), (len(pairs), k)
