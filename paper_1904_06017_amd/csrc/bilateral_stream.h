@@ -314,7 +314,8 @@ struct Worker {
       const int w = c - cpair[m] * 2 * PARTS * NB, q = w / (2 * PARTS), half = w & 1;
       const int part = (w >> 1) - PARTS * q;
       const int blk = q0 + q;
-      csrc[m] = (part < 2 ? v.V + (int64_t)(2 * blk + part) * v.plane : bk.h3 + blk * v.plane) +
+      csrc[m] = (PARTS == 2 || part < 2 ? v.V + (int64_t)(2 * blk + part) * v.plane
+                                        : bk.h3 + blk * v.plane) +
                 32 * x0 + half * (G::NQH * 64);
       cdst[m] = (PARTS * q + part) * Z::CHB + half * (Z::CHB / 2);
     }
