@@ -31,14 +31,15 @@ struct Group {
 };
 
 // The split-FP16 engine's groups: every volume of one radius, both guide
-// types, as strip segments sorted longest first.
+// types, as strip segments sorted longest first (at radii 3 and 4 those that
+// run with two workgroups on a CU apart from the others).
 struct SegGroup {
   int R, duo;                 // duo: see launch_bilateral_h2_queue
   std::vector<Seg> segs;
   size_t off;                 // in the workspace
 };
 
-constexpr int kMaxCus = 256;  // of a gfx950 device
+constexpr int kCus = 256;     // of a gfx950 device
 
 // One batched launch of a cheap stage: its jobs (pair, and for statistics
 // which image), the block prefix, and where both live in the workspace.
@@ -69,6 +70,7 @@ struct stereo_batch_s {
   std::vector<Group> groups;
   std::vector<SegGroup> seg_groups;
   int seg_cus = 0;                     // CUs that they were cut for
+  size_t seg_off = 0;                  // their tables in the workspace
   std::vector<JobList> lists;
   size_t desc_off = 0, desc_bytes = 0; // per-volume descriptors (2 per pair)
   size_t counter_off = 0;
@@ -119,52 +121,48 @@ void ncc_blocks(stereo_batch_s& b) {
 
 // Strip segments of the split-FP16 engine for a device of cus CUs.  Per
 // radius, a pair's strips are cut by the cost of the whole group
-// (segment_rows), listed in bands of tile_band adjacent strips of one vertical
+// (queue_cut), listed in bands of tile_band adjacent strips of one vertical
 // range (their halo columns meet in an XCD's L2) and sorted by cost, longest
-// first.  The tables' places in the workspace stay as they are.
+// first.  The groups' tables follow each other in the workspace.
 void seg_tables(stereo_batch_s& b, int cus) {
   struct V { int pair, vol; double w; };
   struct S { double cost; Seg seg; };
-  std::vector<size_t> off;
-  for (const SegGroup& G : b.seg_groups) off.push_back(G.off);
   b.seg_cus = cus;
   b.seg_groups.clear();
   std::vector<std::vector<V>> vols;
+  long rows[STEREO_MAX_BIL_RADIUS + 1] = {};         // block rows of a radius
+  for (const Plan& P : b.plans)
+    rows[P.R] += (P.p.lr_check ? 2l : 1l) * ((P.W + kSegW - 1) / kSegW) * ((P.H + kSegRow - 1) / kSegRow);
   for (int i = 0; i < (int)b.plans.size(); ++i) {
     const Plan& P = b.plans[i];
+    const int duo = P.R <= 2 || (P.R <= kDuoR && duo_launch((P.D + 15) / 16, rows[P.R], cus));
     size_t g = 0;
-    while (g < b.seg_groups.size() && b.seg_groups[g].R != P.R) ++g;
+    while (g < b.seg_groups.size() && (b.seg_groups[g].R != P.R || b.seg_groups[g].duo != duo)) ++g;
     if (g == b.seg_groups.size()) {
       SegGroup G;
       G.R = P.R;
-      G.duo = 0;
-      G.off = g < off.size() ? off[g] : 0;
+      G.duo = duo;
       b.seg_groups.push_back(G);
       vols.emplace_back();
     }
     for (int vol = 0; vol < (P.p.lr_check ? 2 : 1); ++vol)
       vols[g].push_back({i, vol, block_row_cost((P.D + 15) / 16, 4)});
   }
+  size_t off = b.seg_off;
   for (size_t g = 0; g < b.seg_groups.size(); ++g) {
     SegGroup& G = b.seg_groups[g];
-    double total = 0.0;
-    long rows = 0;
+    std::vector<QueueVol> q;
     for (const V& v : vols[g]) {
       const Plan& P = b.plans[v.pair];
-      const long n = (long)((P.W + kSegW - 1) / kSegW) * ((P.H + kSegRow - 1) / kSegRow);
-      total += v.w * n;
-      rows += n;
+      q.push_back({v.w, (P.W + kSegW - 1) / kSegW, (P.H + kSegRow - 1) / kSegRow});
     }
-    G.duo = G.R <= kDuoR;
-    for (const V& v : vols[g])
-      if (G.R > 2 && !duo_launch((b.plans[v.pair].D + 15) / 16, rows, cus)) G.duo = 0;
     // phases a segment takes beyond its block rows
     const int wgs = G.duo ? 2 * cus : cus, fill = G.duo ? 4 : 6;
+    const std::vector<int> cut = queue_cut(q, wgs, fill);
     std::vector<S> all;
-    for (const V& v : vols[g]) {
-      const Plan& P = b.plans[v.pair];
-      const int tx = (P.W + kSegW - 1) / kSegW, br = (P.H + kSegRow - 1) / kSegRow;
-      const int len = segment_rows(total, v.w, br, wgs);
+    for (size_t k = 0; k < q.size(); ++k) {
+      const V& v = vols[g][k];
+      const int tx = q[k].tx, br = q[k].br, len = cut[k];
       for (int xb = 0; xb < tx; xb += b.tile_band)
         for (int r = 0; r < br; r += len)
           for (int x = xb; x < std::min(tx, xb + b.tile_band); ++x) {
@@ -175,6 +173,8 @@ void seg_tables(stereo_batch_s& b, int cus) {
     std::stable_sort(all.begin(), all.end(), [](const S& a, const S& c) { return a.cost > c.cost; });
     G.segs.clear();
     for (const S& e : all) G.segs.push_back(e.seg);
+    G.off = off;
+    off += sizeof(Seg) * G.segs.size();
   }
 }
 
@@ -231,13 +231,15 @@ void build_layout(stereo_batch_s& b) {
     table(per[gi], b.groups[gi].tiles, b.groups[gi].tiles_off);
     table(per_m[gi], b.groups[gi].tiles_m, b.groups[gi].tiles_m_off);
   }
-  // laid out for two workgroups on each of kMaxCus CUs (fewer make fewer, longer
-  // segments), so that the workspace does not depend on the device
-  seg_tables(b, 2 * kMaxCus);
-  for (SegGroup& G : b.seg_groups) {
-    G.off = o;
-    o = align256(o + sizeof(Seg) * G.segs.size());
-  }
+  // the segments' tables: room for the shortest, so that the workspace does not
+  // depend on the device, whose number of CUs decides the cut (bind)
+  size_t most = 0;
+  for (const Plan& P : b.plans)
+    most += (P.p.lr_check ? 2 : 1) * (size_t)((P.W + kSegW - 1) / kSegW) *
+            (((P.H + kSegRow - 1) / kSegRow + kMinSegRows - 1) / kMinSegRows);
+  b.seg_off = o;
+  o = align256(o + sizeof(Seg) * most);
+  seg_tables(b, kCus);
   b.counter_off = o;
   o = align256(o + sizeof(unsigned int) * std::max<size_t>(1, b.groups.size()));
   // job lists of the cheap stages, in launch order
@@ -305,7 +307,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     return fail(STEREO_ERR_WORKSPACE_TOO_SMALL, "batch workspace %zu < %zu", bytes, b.ws_bytes);
   BREQ((reinterpret_cast<uintptr_t>(ws) & 255) == 0, "workspace must be 256-byte aligned");
   if (b.bound_ws == ws) return STEREO_OK;
-  if (b.seg_cus != std::min(b.cu_count, kMaxCus)) seg_tables(b, std::min(b.cu_count, kMaxCus));
+  if (b.seg_cus != b.cu_count) seg_tables(b, b.cu_count);
   const int n = (int)b.items.size();
   const size_t pb = bilateral_pair_bytes();
   b.host_desc.assign(b.desc_bytes, 0);

@@ -2,6 +2,8 @@
 // the number of CUs, without any device call.
 #pragma once
 #include <algorithm>
+#include <utility>
+#include <vector>
 
 namespace stereo {
 
@@ -38,14 +40,47 @@ inline int duo_launch(int nblk, long rows, int cus) {
   return rows >= 16l * cus ? 1 : 0;
 }
 
-// Block rows of a segment of a queued launch: br block rows of cost w each, cut
-// so that the launch (total cost) makes about four segments for each of its
-// wgs workgroups.  A segment fills and drains its pipeline of block rows, so
-// it has at least eight.
-inline int segment_rows(double total, double w, int br, int wgs) {
-  const int want = std::max(8, (int)(total / (4.0 * wgs) / w));
-  const int n = std::max(1, (br + want - 1) / want);
-  return (br + n - 1) / n;
+// A volume of a queued launch: tx strips of br block rows of cost w each.
+struct QueueVol {
+  double w;
+  int tx, br;
+};
+constexpr int kMinSegRows = 4;          // block rows of the shortest segment
+
+// Block rows per segment of each volume of a queued launch.  A segment costs its
+// block rows and `fill` more, in which its pipeline fills and drains; segments
+// run longest first, one a workgroup and round.  Of cuts from two segments a
+// workgroup's share down to an eighth of it, the one whose longest workgroup is
+// shortest: four segments a workgroup throughout, the rule before, spent a third
+// of the time on filling where a volume's shares are short.
+inline std::vector<int> queue_cut(const std::vector<QueueVol>& v, int wgs, int fill) {
+  double total = 0.0, best = 1e300;
+  for (const QueueVol& q : v) total += q.w * q.tx * q.br;
+  std::vector<int> at(v.size()), len(v.size());
+  std::vector<double> load(wgs);
+  for (double T = 2.0 * total / wgs; T > 0.12 * total / wgs; T *= 0.93) {
+    std::vector<std::pair<double, long>> runs;         // cost of a segment, how many
+    for (size_t k = 0; k < v.size(); ++k) {
+      const QueueVol& q = v[k];
+      const int want = std::max(kMinSegRows, std::min(q.br, (int)(T / q.w)));
+      const int n = (q.br + want - 1) / want;
+      len[k] = std::max(std::min(kMinSegRows, q.br), (q.br + n - 1) / n);
+      const int full = q.br / len[k], rest = q.br - full * len[k];
+      runs.push_back({q.w * (len[k] + fill), (long)full * q.tx});
+      if (rest) runs.push_back({q.w * (rest + fill), q.tx});
+    }
+    std::sort(runs.begin(), runs.end(), [](const auto& a, const auto& c) { return a.first > c.first; });
+    std::fill(load.begin(), load.end(), 0.0);
+    size_t p = 0;
+    for (const auto& r : runs)
+      for (long c = 0; c < r.second; ++c, p = p + 1 == load.size() ? 0 : p + 1) load[p] += r.first;
+    const double longest = *std::max_element(load.begin(), load.end());
+    if (longest < best) {
+      best = longest;
+      at = len;
+    }
+  }
+  return at;
 }
 
 // Levels of a materialised aggregation in parts of `per` chunks each, where

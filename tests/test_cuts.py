@@ -14,8 +14,12 @@ WRAP = r"""
 extern "C" int level_part(long tiles, int chunks, int cus, int held) {
   return stereo::level_part(tiles, chunks, cus, held);
 }
-extern "C" int segment_rows(double total, double w, int br, int cus) {
-  return stereo::segment_rows(total, w, br, cus);
+extern "C" void queue_cut(int n, const double* w, const int* tx, const int* br, int wgs, int fill,
+                          int* out) {
+  std::vector<stereo::QueueVol> v;
+  for (int k = 0; k < n; ++k) v.push_back({w[k], tx[k], br[k]});
+  const std::vector<int> cut = stereo::queue_cut(v, wgs, fill);
+  for (int k = 0; k < n; ++k) out[k] = cut[k];
 }
 extern "C" int duo_launch(int nblk, long rows, int cus) { return stereo::duo_launch(nblk, rows, cus); }
 extern "C" int sweep_blocks(int nblk, int most) { return stereo::sweep_blocks(nblk, most); }
@@ -50,17 +54,33 @@ def test_level_parts_of_workgroups_alone_on_a_cu(cuts, cus, tiles, chunks):
         assert per == chunks
 
 
-@pytest.mark.parametrize("cus", [256, 128, 32])
-def test_segments_by_the_number_of_cus(cuts, cus):
-    """A queued launch makes about four segments a workgroup, whatever their
-    number: strips of 270 block rows, 60 of them in a volume, in 40
-    volumes; and a small launch keeps segments of at least eight block rows."""
-    w, br, strips = 6.0, 270, 60 * 40
-    rows = cuts.segment_rows(ctypes.c_double(w * br * strips), ctypes.c_double(w), br, cus)
-    per = -(-br // rows) * strips / cus
-    # whole strips where they are more than four a workgroup
-    assert rows == br if strips >= 4 * cus else 3.5 <= per <= 5.0
-    assert cuts.segment_rows(ctypes.c_double(w * 60), ctypes.c_double(w), 60, cus) >= 7
+@pytest.mark.parametrize("wgs", [512, 256, 64])
+@pytest.mark.parametrize("fill", [4, 6])
+@pytest.mark.parametrize("vols", [
+    [(10, 50, 146)] * 2, [(8, 27, 82)] * 2 + [(5, 21, 62)] * 2 + [(4, 14, 43)] * 2,
+    [(9, 20, 60)], [(11, 27, 77)] * 2 + [(9, 21, 62)] * 2 + [(7, 16, 46)] * 2,
+    [(6, 80, 180)] * 2 + [(8, 120, 270)] * 2 + [(5, 40, 120)] * 2, [(3, 1, 1)], [(7, 2, 3)] * 4,
+    [(10, 120, 270)] * 128])
+def test_segments_of_a_queued_launch(cuts, vols, wgs, fill):
+    """Segments run longest first, one a workgroup and round.  The cut covers
+    every strip with segments of at least four block rows (or the strip), and
+    its longest workgroup is at most 1.4 times an even share of the block rows
+    plus the one filling that nothing avoids, or the shortest cut there is."""
+    out = (ctypes.c_int * len(vols))()
+    arr = lambda t, k: (t * len(vols))(*[v[k] for v in vols])
+    cuts.queue_cut(len(vols), arr(ctypes.c_double, 0), arr(ctypes.c_int, 1),
+                   arr(ctypes.c_int, 2), wgs, fill, out)
+
+    def longest(lens):
+        c = sorted((w * (min(n, br - r) + fill) for (w, tx, br), n in zip(vols, lens)
+                    for r in range(0, br, n) for _ in range(tx)), reverse=True)
+        return max(sum(c[p::wgs]) for p in range(min(wgs, len(c))))
+
+    assert all(min(4, br) <= n <= br for n, (_, _, br) in zip(out, vols))
+    share = sum(w * tx * br for w, tx, br in vols) / wgs
+    w = max(v[0] for v in vols)
+    least = longest([min(4, br) for _, _, br in vols])
+    assert longest(out) <= max(1.4 * share + w * fill, least if least < w * 24 else 0)
 
 
 @pytest.mark.parametrize("most", [3, 4])
