@@ -297,9 +297,9 @@ stereo_status stereo_damage_mask(stereo_plan_t plan, const float* disp_t, float 
  * Many pairs of uneven size and disparity range (each with its own plan) in
  * one workspace and one captured graph.  Per pair, results are bitwise those
  * of stereo_match with the same plan.  The aggregation + WTA of both volumes
- * of all pairs runs as one launch per radius R (engines 0 and 1: per R and
- * guide type) over the strip segments (tiles) of all its pairs, longest
- * first. */
+ * of all pairs runs as one launch per radius R (two at R = 3 and 4 where
+ * ranges differ; engines 0 and 1: per R and guide type) over the strip
+ * segments (tiles) of all its pairs, longest first. */
 typedef struct stereo_batch_s* stereo_batch_t;
 typedef struct {
   stereo_plan_t plan;      /* the pair's plan (copied at create)                */

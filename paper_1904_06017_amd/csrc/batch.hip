@@ -3,8 +3,8 @@
 // and the NCC of engines 0 and 1) run as one launch per stage and element type
 // (per NCC radius) over the blocks of every pair; the dominant stage, the
 // aggregation + WTA of both cost volumes of every pair, runs as one launch per
-// radius (engines 0 and 1: per radius and guide type) over the strip segments
-// or tiles of all its pairs, longest first.  Every block, segment and tile
+// radius (two at radii 3 and 4 where ranges differ; engines 0 and 1: per radius
+// and guide type) over the strip segments or tiles of all its pairs, longest first.  Every block, segment and tile
 // runs the same code as the per-pair path, so each pair's result is bitwise
 // the plain path's.
 #include <algorithm>

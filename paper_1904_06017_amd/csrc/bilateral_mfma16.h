@@ -13,6 +13,8 @@
 // 22 significant bits and the dropped w_lo C_lo term is below 2^-22 of the
 // product, so the sums are as accurate as FP32 products; the three FP16
 // products take about a third of the matrix-core time of the FP32 ones.
+// (The backward's second pass at large radii carries both operands in three
+// BF16 numbers: kMaxWide in bilateral_stream.h.)
 // Weights are scaled by 2^12 before the split (the selection and the
 // normalised soft-argmin are scale-free), which keeps the low parts of small
 // weights out of the FP16 subnormal range.

@@ -26,8 +26,9 @@
 // tile's weights kept in registers over passes of one level block each, every
 // wave in the same phase between barriers) spent 10200 cycles on the first
 // pass of a tile, vector ALU only, and 3600 on each other, matrix cores and
-// LDS only.  1280x720, R = 7, both volumes: D = 64 0.475 -> 0.338 ms, D = 128
-// 0.84 -> 0.678 ms; 640x480, R = 5, D = 48: 0.107 -> 0.079 ms.
+// LDS only.  Both volumes, kernel trace of 60 calls each, medians: 1280x720, R =
+// 7, D = 64 0.498 -> 0.388 ms, D = 128 0.792 -> 0.727 ms; 640x480, R = 5, D = 48
+// 0.116 -> 0.088 ms.
 #pragma once
 #include "bilateral_mfma16.h"
 
@@ -165,11 +166,11 @@ struct Args {
   int n;
 };
 
-// A backward pass (v[0] of Args: the split-FP16 input volume, v.D = levels of
-// the level tile, and the FP32 guide).  Six products per operand pair instead
-// of three: the weights, and the weights times the guide difference.
-// 1280x720, D = 48, R = 5: pass 1 398 -> 284 us, pass 2 292 us either way
-// (tiles of 32x16 pixels, their weights kept in registers, before).
+// A backward pass (v[0] of Args: the split input volume, v.D = levels of the
+// level tile, and the FP32 guide).  Six products per operand pair instead of
+// three (twelve on BF16 parts): the weights, and the weights times the guide
+// difference.  1280x720, D = 48, R = 5: pass 1 398 -> 270 us, pass 2 292 us
+// either way (tiles of 32x16 pixels, their weights kept in registers, before).
 struct Back {
   float* out;                           // pass 2: dC planar [D][H][W]
   uint16_t* h2out;                      // pass 1: C' S, split volume (as v): FP16 parts,

@@ -43,7 +43,12 @@ __device__ __forceinline__ void fix_add(unsigned long long* dst, double v) {
 // are staged in LDS once, side by side, and the taps read both at once.  The
 // vector ALU bounds it (per tap an exponential and six operations): 1280x720,
 // R = 5, 46 -> 30 us, 317x243, R = 7, 24 -> 12 us (a run-time radius, two
-// reads and two bounds checks a tap before).
+// reads and two bounds checks a tap before).  The scaled guide is rounded before
+// its differences are formed, as in the passes that form A1 and A2: the sum is
+// then that of a guide moved by half an ulp.  With differences of the raw guide
+// here the two roundings do not cancel: g_ref's error against FP64, geometric
+// means of 8 inputs, R = 5, sigma_r = 12 2.38e-6 here, 2.50e-6 raw; sigma_r = 3
+// 3.31e-6, 4.73e-6; R = 7 2.70e-6, 2.79e-6.
 constexpr int GF_TX = 32, GF_TY = 8;
 template <typename GT, int R>
 __global__ void __launch_bounds__(kT)

@@ -548,11 +548,11 @@ hipError_t launch_ncc_ty(const Plan& P, const T* ref, const float* tar_w, const 
 }
 
 // Rows of a tile: 16 redo 2r of 16 + 2r input rows instead of 2r of 8 + 2r, but
-// make half as many workgroups.  They pay from 32 waves of 16-row tiles a CU
-// on, a full residency (8192 waves of the chip's 256 CUs): frames of 1280x720, 64 levels (17 000
-// waves) 534 -> 520 us, 1917x1075, 96 levels 1940 -> 1900 us, both planar volumes
-// at 1280x720 144 -> 135 us; below it 8 rows are faster: 640x360, 32 levels (2200
-// waves) 100.7 against 105.4 us, 320x240 55.0 against 61.1 us.
+// make half as many workgroups.  They pay from 32 waves of 16-row tiles a CU on,
+// a full residency (8192 waves of the chip's 256 CUs).  Both measured in turn:
+// frames of 1280x720, 64 levels (17 000 waves) take 2.9 % less with 16 rows,
+// 1917x1075, 96 levels 2.1 %, both planar volumes at 1280x720 6.8 %; below it 8
+// rows are faster, at 640x360, 32 levels (2200 waves) by 4.5 %, at 320x240 by 10 %.
 constexpr int64_t kTallWaves = 32;      // a CU
 
 template <int r, typename T, int DC>
