@@ -420,7 +420,7 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
   a.guide_pitch = P.p.pitch_ref;
   a.dint = dint_R;
   a.dsub = ds;
-  a.state = at<float>(ws, P.off_state);
+  a.state = h2_state(P, ws, P.off_state);
   BilArgs v[2] = {a, a};
   if (lr) {
     BilArgs& b = v[1];
@@ -431,7 +431,7 @@ stereo_status match_impl(stereo_plan_t plan, const void* ref, const void* tar,
     b.guide_pitch = P.W;
     b.dint = dT;
     b.dsub = nullptr;
-    b.state = at<float>(ws, P.off_state2);
+    b.state = h2_state(P, ws, P.off_state2);
   }
   // both volumes in one launch on the split-FP16 matrix cores (more segments
   // to spread over the chip), unless the stages are timed apart

@@ -331,7 +331,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     a.guide_pitch = P.p.pitch_ref;
     a.dint = b.items[i].dint_R;
     a.dsub = at<float>(pws, P.off_dsub);
-    a.state = at<float>(pws, P.off_state);
+    a.state = h2_state(P, pws, P.off_state);
     bilateral_pair(P, a, b.host_desc.data() + (2 * i) * pb);
     BilArgs t = a;
     if (b.engine == 2) t.h2 = at<uint16_t>(pws, P.off_cvol + P.h2_tar_off);
@@ -341,7 +341,7 @@ stereo_status bind(stereo_batch_s& b, void* ws, size_t bytes, hipStream_t s) {
     t.guide_pitch = P.W;
     t.dint = at<int16_t>(pws, P.off_dT);
     t.dsub = nullptr;
-    t.state = at<float>(pws, P.off_state2);
+    t.state = h2_state(P, pws, P.off_state2);
     bilateral_pair(P, t, b.host_desc.data() + (2 * i + 1) * pb);
   }
   BHIP(hipMemcpyAsync(at<char>(ws, b.desc_off), b.host_desc.data(), b.desc_bytes,

@@ -151,7 +151,7 @@ struct BilArgs {
   int64_t h2_plane;   // halves per block part (>= 16 h2_rows(R, H) h2_pitch)
   int h2_pitch;       // columns per stored row (a multiple of 8)
   // ranges above 64 levels: selection state kept between the sweeps of 64
-  // levels, h2_state_floats per pixel (16-byte aligned)
+  // levels, h2_state_floats per pixel (16-byte aligned; h2_state)
   float* state;
   // backward passes on the 16-bit matrix cores: max |g'| (float bits) and a
   // flag that pass 1 raises at a non-finite aP (both zeroed by the caller),
@@ -177,6 +177,11 @@ hipError_t launch_bilateral(const Plan& P, const BilArgs& a, int mode,
 hipError_t launch_bilateral_h2(const Plan& P, const BilArgs* a, int n, int mode, hipStream_t s);
 // Floats per pixel of BilArgs::state for mode 1 / 2 (0 up to 64 levels).
 inline int h2_state_floats(int D, int mode) { return D <= 64 ? 0 : mode == 2 ? 16 : 4; }
+// BilArgs::state at offset off of a workspace, NULL where there is none: a launch
+// that needs it is then refused, not given another region.
+inline float* h2_state(const Plan& P, void* ws, size_t off) {
+  return P.D > 64 ? reinterpret_cast<float*>(static_cast<char*>(ws) + off) : nullptr;
+}
 // The same, mode 1, over segments of many volumes: descs = device array of
 // descriptors (bilateral_pair), segs = n device Seg entries, all of radius R.
 struct Seg {                  // block rows [b0, b0 + len) of the strip at column x0

@@ -994,7 +994,7 @@ stereo_status stereo_soft_forward(stereo_plan_t plan, const float* ref, const fl
   a.sm_dh = saved + 2 * HW;
   a.disp = disp_soft;
   a.plane[0] = plane[0]; a.plane[1] = plane[1]; a.plane[2] = plane[2];
-  a.state = at<float>(ws, P.off_state2);
+  a.state = h2_state(P, ws, P.off_state2);
   HIPC(a.h2 ? launch_bilateral_h2(P, &a, 1, 2, stream) : launch_bilateral(P, a, 2, stream),
        "aggregation + soft-argmin");
   return STEREO_OK;
